@@ -60,7 +60,8 @@ sys.path.insert(0, ROOT)
 HBM_PEAK_GBS = 8000.0
 FP32_PEAK_TFLOPS = 78.6  # non-packed FP32 FMA: 256 CUs x 64 lanes x 2 flops x 2.4 GHz
 ROTATE_BYTES = 1 << 30
-KERNEL_SOURCES = ["xr_forward.hip", "xr_backward.hip", "xr_device.hpp", "xr_buffer.hpp", "xr_internal.h"]
+KERNEL_SOURCES = ["xr_forward.hip", "xr_aa.hip", "xr_backward.hip", "xr_device.hpp", "xr_buffer.hpp", "xr_aa.hpp",
+                  "xr_stage.hpp", "xr_gather_walk.hpp", "xr_internal.h"]
 HEADLINE_PROFILE = "c2_bicubic_x2_u8_rgba.md"
 # untimed launches before the per-launch statistics (see time_launches)
 PREROLL_LAUNCHES = 500

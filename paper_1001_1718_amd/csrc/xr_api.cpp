@@ -453,10 +453,12 @@ int check_aa(const xr_tile &t, int32_t filter, const xr_image &src, const xr_ima
     return XR_OK;
 }
 
-// Default antialiased tile: the LDS kernel with the first block whose
-// window fits, else the gather.
+// Default antialiased tile: the LDS kernel where its walk applies or with the
+// first block whose window fits, else the gather.
 xr_tile aa_default_tile(int32_t filter, const xr_image &src, const xr_image &dst)
 {
+    if (xr::antialiased_walk_supported(make_args(src, dst), filter, src.dtype, src.channels))
+        return xr_tile{XR_KERNEL_STRIP_LDS, 64, 4, 1, 1, 0};
     const int blocks[][2] = {{64, 4}, {64, 2}, {32, 2}, {16, 2}};
     for (const auto &b : blocks) {
         const xr_tile t{XR_KERNEL_STRIP_LDS, b[0], b[1], 1, 1, 0};
@@ -510,11 +512,14 @@ int resize_common(const xr_image *src, const xr_image *dst, const xr_tile *tile,
         return rc;
     xr_tile t = resolve_tile(tile, filter, *src, *dst);
     if (is_aa(filter)) {
-        // strip shapes (and the untuned default) mean the default antialiased tile
-        if (t.kernel == XR_KERNEL_STRIP || t.kernel == XR_KERNEL_STRIP_ANY ||
-            (t.kernel == XR_KERNEL_STRIP_LDS && (t.ppt_x != 1 || t.ppt_y != 1)))
+        // strip shapes (and the untuned default) mean the default antialiased
+        // tile, whose LDS blocks fit
+        const bool any = t.kernel == XR_KERNEL_STRIP || t.kernel == XR_KERNEL_STRIP_ANY ||
+                         (t.kernel == XR_KERNEL_STRIP_LDS && (t.ppt_x != 1 || t.ppt_y != 1));
+        if (any)
             t = aa_default_tile(filter, *src, *dst);
-        rc = check_aa(t, filter, *src, *dst);
+        if (!any || t.kernel == XR_KERNEL_GATHER)
+            rc = check_aa(t, filter, *src, *dst);
     } else {
         rc = check_tile(t, src->dtype, src->channels);
     }

@@ -100,6 +100,18 @@ struct alignas(ALIGN) RawBuf {
     unsigned char b[BYTES];
 };
 
+template <int BYTES, int ALIGN>
+__device__ __forceinline__ RawBuf<BYTES, ALIGN> load_raw(const unsigned char *p)
+{
+    return *reinterpret_cast<const RawBuf<BYTES, ALIGN> *>(__builtin_assume_aligned(p, ALIGN));
+}
+
+template <int BYTES, int ALIGN>
+__device__ __forceinline__ void store_raw(unsigned char *p, const RawBuf<BYTES, ALIGN> &v)
+{
+    *reinterpret_cast<RawBuf<BYTES, ALIGN> *>(__builtin_assume_aligned(p, ALIGN)) = v;
+}
+
 constexpr int cgcd(int a, int b) { return b == 0 ? a : cgcd(b, a % b); }
 constexpr int cmin(int a, int b) { return a < b ? a : b; }
 

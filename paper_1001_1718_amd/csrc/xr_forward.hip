@@ -76,18 +76,6 @@ __device__ __forceinline__ void decode(const unsigned char *buf, int i, float (&
 }
 
 
-template <int BYTES, int ALIGN>
-__device__ __forceinline__ RawBuf<BYTES, ALIGN> load_raw(const unsigned char *p)
-{
-    return *reinterpret_cast<const RawBuf<BYTES, ALIGN> *>(__builtin_assume_aligned(p, ALIGN));
-}
-
-template <int BYTES, int ALIGN>
-__device__ __forceinline__ void store_raw(unsigned char *p, const RawBuf<BYTES, ALIGN> &v)
-{
-    *reinterpret_cast<RawBuf<BYTES, ALIGN> *>(__builtin_assume_aligned(p, ALIGN)) = v;
-}
-
 // Store of an output run that is written once and not read back by this
 // launch: non-temporal vector stores (they do not keep the lines in the
 // caches, which leaves room there for the source rows that neighbouring
@@ -189,132 +177,6 @@ __global__ void __launch_bounds__(1024) k_gather(ResizeArgs a)
 }
 
 // ---------------------------------------------------------------------------
-// k_gather_aa (antialiased: filter stretched by the shrink factor)
-// ---------------------------------------------------------------------------
-
-// Taps of output index x for an antialiased filter of radius R (1 bilinear,
-// 2 Keys): sigma = max(1, n_in / n_out), every source i with
-// s - R sigma < i <= s + R sigma inside [0, n_in - 1], from exact integers
-// (s = num / (2 n_out), num = (2x + 1) n_in - n_out). Not in the paper: the
-// usual remedy for aliasing when shrinking.
-__device__ __forceinline__ void aa_range(int32_t x, int32_t n_in, int32_t n_out, int32_t r,
-                                         int32_t &lo, int32_t &hi)
-{
-    const int64_t num = (2 * static_cast<int64_t>(x) + 1) * n_in - n_out;
-    const int64_t den = 2 * static_cast<int64_t>(n_out);
-    const int64_t reach = 2 * static_cast<int64_t>(r) * (n_in > n_out ? n_in : n_out);
-    // floor division of possibly negative numerators
-    auto fdiv = [](int64_t a, int64_t b) { return a >= 0 ? a / b : -((-a + b - 1) / b); };
-    lo = static_cast<int32_t>(max<int64_t>(fdiv(num - reach, den) + 1, 0));
-    hi = static_cast<int32_t>(min<int64_t>(fdiv(num + reach, den), n_in - 1));
-}
-
-// K(d) in factored forms whose factors do not cancel: 1 - u; Keys a = -1/2
-// as (1 - u)(1 + u (1 - 3u/2)) for u <= 1 and -(u - 1)(u - 2)^2 / 2 for
-// 1 < u < 2 (u - 1 and u - 2 are exact there).
-template <int R>
-__device__ __forceinline__ float aa_kernel(float d)
-{
-    const float u = fabsf(d);
-    if constexpr (R == 1) {
-        return u < 1.0f ? 1.0f - u : 0.0f;
-    } else {
-        if (u <= 1.0f)
-            return (1.0f - u) * (1.0f + u * (1.0f - 1.5f * u));
-        if (u < 2.0f) {
-            const float v = u - 2.0f;
-            return (-0.5f * (u - 1.0f)) * (v * v);
-        }
-        return 0.0f;
-    }
-}
-
-// Taps and normalised weights of one output index into an LDS table: the
-// kernel values K((i - s) / sigma) for i = lo .. hi, then each divided by
-// their sum (summed in ascending i).
-template <int R>
-__device__ __forceinline__ void aa_table(int32_t x, int32_t n_in, int32_t n_out, int32_t kmax,
-                                         int32_t *lo_out, int32_t *n_out_taps, float *w)
-{
-    int32_t lo, hi;
-    aa_range(x, n_in, n_out, R, lo, hi);
-    const int32_t n = min(hi - lo + 1, kmax);
-    // (i - s) / sigma = (2 i n_out - num) / (2 max(n_in, n_out)) from exact
-    // integers: one rounding, no cancellation
-    const int64_t num = (2 * static_cast<int64_t>(x) + 1) * n_in - n_out;
-    const float den = static_cast<float>(2 * static_cast<int64_t>(n_in > n_out ? n_in : n_out));
-    float sum = 0.0f;
-    for (int32_t k = 0; k < n; ++k) {
-        const int64_t dn = 2 * static_cast<int64_t>(lo + k) * n_out - num;
-        const float v = aa_kernel<R>(static_cast<float>(dn) / den);
-        w[k] = v;
-        sum += v;
-    }
-    const float inv = 1.0f / sum;
-    for (int32_t k = 0; k < n; ++k)
-        w[k] *= inv;
-    *lo_out = lo;
-    *n_out_taps = n;
-}
-
-// One output pixel per thread in a block_w x block_h tile (the paper's
-// tiling, eq. 6). The workgroup first fills LDS tables of taps and weights
-// for its block_w columns and block_h rows (kx / ky weights each), then every
-// thread sums its window: per source row the taps ascending (multiply, then
-// FMAs), then the rows ascending.
-template <int R, typename T, int C>
-__global__ void __launch_bounds__(1024) k_gather_aa(ResizeArgs a, int32_t kx, int32_t ky)
-{
-    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
-    const int32_t bw = static_cast<int32_t>(blockDim.x), bh = static_cast<int32_t>(blockDim.y);
-    int32_t *xlo = reinterpret_cast<int32_t *>(lds);
-    int32_t *xn = xlo + bw;
-    int32_t *ylo = xn + bw;
-    int32_t *yn = ylo + bh;
-    float *xw = reinterpret_cast<float *>(yn + bh);
-    float *yw = xw + bw * kx;
-    const int32_t tid = threadIdx.y * bw + threadIdx.x;
-    for (int32_t t = tid; t < bw + bh; t += bw * bh) {
-        if (t < bw) {
-            const int32_t x = min(static_cast<int32_t>(blockIdx.x) * bw + t, a.out_w - 1);
-            aa_table<R>(x, a.in_w, a.out_w, kx, xlo + t, xn + t, xw + t * kx);
-        } else {
-            const int32_t u = t - bw;
-            const int32_t y = a.dst_row0 + min(static_cast<int32_t>(blockIdx.y) * bh + u, a.dst_rows - 1);
-            aa_table<R>(y, a.in_h, a.out_h, ky, ylo + u, yn + u, yw + u * ky);
-        }
-    }
-    __syncthreads();
-    const int32_t px = blockIdx.x * bw + threadIdx.x;
-    const int32_t py = blockIdx.y * bh + threadIdx.y;
-    if (px >= a.out_w || py >= a.dst_rows)
-        return;
-    const unsigned char *src = a.src + static_cast<int64_t>(blockIdx.z) * a.src_plane_pitch;
-    const int32_t x0 = xlo[threadIdx.x], nx = xn[threadIdx.x];
-    const int32_t y0 = ylo[threadIdx.y], ny = yn[threadIdx.y];
-    const float *wxr = xw + threadIdx.x * kx;
-    const float *wyr = yw + threadIdx.y * ky;
-    float acc[C];
-    for (int32_t j = 0; j < ny; ++j) {
-        const unsigned char *row = src + static_cast<int64_t>(y0 + j - a.src_row0) * a.src_pitch;
-        float h[C], p[C];
-        Pix<T, C>::load(row, x0, p);
-        fma_first(h, wxr[0], p);
-        for (int32_t i = 1; i < nx; ++i) {
-            Pix<T, C>::load(row, x0 + i, p);
-            fma_next(h, wxr[i], p);
-        }
-        if (j == 0)
-            fma_first(acc, wyr[0], h);
-        else
-            fma_next(acc, wyr[j], h);
-    }
-    unsigned char *dst = a.dst + static_cast<int64_t>(blockIdx.z) * a.dst_plane_pitch +
-                         static_cast<int64_t>(py) * a.dst_pitch;
-    Pix<T, C>::store(dst, px, acc);
-}
-
-// ---------------------------------------------------------------------------
 // k_strip (any scale)
 // ---------------------------------------------------------------------------
 
@@ -332,163 +194,6 @@ __device__ __forceinline__ void copy_pixel(unsigned char *dst, const unsigned ch
         *reinterpret_cast<uint2 *>(dst) = *reinterpret_cast<const uint2 *>(src);
     } else {
         *reinterpret_cast<uint4 *>(dst) = *reinterpret_cast<const uint4 *>(src);
-    }
-}
-
-// The antialiased filter on block_w x block_h tiles of output pixels with
-// the source window staged in LDS (separable). A workgroup takes `tpb`
-// vertically adjacent tiles of one tile column: the column tables (taps and
-// kx weights per output column, the same as k_gather_aa's) are built once,
-// the row tables once per tile. Per tile the source window (rows ylo(first)
-// .. yhi(last), columns xlo(first) .. xhi(last)) is copied to LDS with
-// coalesced loads, the horizontal pass filters every window row for every
-// tile column into an LDS row buffer, and each thread then sums its rows. Per
-// pixel the float32 sequence is exactly k_gather_aa's (taps ascending per
-// row, rows ascending), so the two kernels agree bit for bit. The window is
-// at most win_w x win_h pixels (bounded on the host from the scale).
-constexpr int kAaRegTaps = 12;  // register-held horizontal weights (bicubic to 1/2.75)
-constexpr int32_t kAaTilesPerBlock = 4;  // most tiles a workgroup walks down its column
-constexpr int64_t kAaMinBlocks = 1024;    // workgroups the multi-tile grid keeps
-
-template <int R, typename T, int C>
-__global__ void __launch_bounds__(1024) k_tile_aa(ResizeArgs a, int32_t kx, int32_t ky, int32_t win_w,
-                                                  int32_t win_h, int32_t tpb)
-{
-    constexpr int PB = Pix<T, C>::kBytes;
-    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
-    const int32_t bw = static_cast<int32_t>(blockDim.x), bh = static_cast<int32_t>(blockDim.y);
-    const int32_t nthreads = bw * bh;
-    int32_t *xlo = reinterpret_cast<int32_t *>(lds);
-    int32_t *xn = xlo + bw;
-    int32_t *ylo = xn + bw;
-    int32_t *yn = ylo + bh;
-    float *xw = reinterpret_cast<float *>(yn + bh);
-    float *yw = xw + bw * kx;
-    const int64_t table_bytes = 4 * (2 * static_cast<int64_t>(bw) + 2 * bh +
-                                     static_cast<int64_t>(bw) * kx + static_cast<int64_t>(bh) * ky);
-    unsigned char *win = lds + (table_bytes + 15) / 16 * 16;
-    float *hbuf = reinterpret_cast<float *>(win + (static_cast<int64_t>(win_w) * win_h * PB + 15) / 16 * 16);
-    const int32_t tid = threadIdx.y * bw + threadIdx.x;
-    const unsigned char *src = a.src + static_cast<int64_t>(blockIdx.z) * a.src_plane_pitch;
-    const int32_t n_tiles_y = (a.dst_rows + bh - 1) / bh;
-    const int32_t tile_end = min(static_cast<int32_t>(blockIdx.y + 1) * tpb, n_tiles_y);
-    // Every bound below is uniform over the workgroup, and no thread leaves
-    // the loop early, so every thread reaches every barrier.
-    for (int32_t by = static_cast<int32_t>(blockIdx.y) * tpb; by < tile_end; ++by) {
-        const bool first = by == static_cast<int32_t>(blockIdx.y) * tpb;
-        for (int32_t t = tid + (first ? 0 : bw); t < bw + bh; t += nthreads) {
-            if (t < bw) {
-                const int32_t x = min(static_cast<int32_t>(blockIdx.x) * bw + t, a.out_w - 1);
-                aa_table<R>(x, a.in_w, a.out_w, kx, xlo + t, xn + t, xw + t * kx);
-            } else {
-                const int32_t u = t - bw;
-                const int32_t y = a.dst_row0 + min(by * bh + u, a.dst_rows - 1);
-                aa_table<R>(y, a.in_h, a.out_h, ky, ylo + u, yn + u, yw + u * ky);
-            }
-        }
-        __syncthreads();
-        // the tile's source window (tap ranges are monotone in x and y)
-        const int32_t wx0 = xlo[0];
-        const int32_t ww = min(xlo[bw - 1] + xn[bw - 1] - wx0, win_w);
-        const int32_t wy0 = ylo[0];
-        const int32_t wh = min(ylo[bh - 1] + yn[bh - 1] - wy0, win_h);
-        // NB loads in flight per thread before any LDS store. Element i of the
-        // window is (i / ww, i % ww); a thread's elements step by nthreads,
-        // i.e. by dr rows and dc columns with a carry, so no division per
-        // element.
-        constexpr int NB = 8;
-        const int32_t total = ww * wh;
-        const int32_t dr = nthreads / ww, dc = nthreads - dr * ww;
-        int32_t r = tid / ww, c = tid - (tid / ww) * ww;
-        const unsigned char *wsrc = src + static_cast<int64_t>(wy0 - a.src_row0) * a.src_pitch +
-                                    static_cast<int64_t>(wx0) * PB;
-        for (int32_t base = tid; base < total; base += nthreads * NB) {
-            RawBuf<PB, PB> v[NB];
-            int32_t off[NB];
-#pragma unroll
-            for (int k = 0; k < NB; ++k) {
-                // past the end: reload the window's last element (a valid address)
-                const bool in = base + k * nthreads < total;
-                const int32_t rr = in ? r : wh - 1, cc = in ? c : ww - 1;
-                off[k] = (rr * win_w + cc) * PB;
-                v[k] = load_raw<PB, PB>(wsrc + static_cast<int64_t>(rr) * a.src_pitch + cc * PB);
-                c += dc;
-                r += dr + (c >= ww ? 1 : 0);
-                c -= c >= ww ? ww : 0;
-            }
-#pragma unroll
-            for (int k = 0; k < NB; ++k)
-                if (base + k * nthreads < total)
-                    store_raw<PB, PB>(win + off[k], v[k]);
-        }
-        __syncthreads();
-        // horizontal pass: window row r, tile column hc (threads of one
-        // column take rows ty, ty + bh, ...). A column's weights are the same
-        // on every row, so up to kAaRegTaps of them are held in registers.
-        const int32_t hc = threadIdx.x;
-        const int32_t hx0 = xlo[hc] - wx0, hnx = xn[hc];
-        const float *hwx = xw + hc * kx;
-        if (kx <= kAaRegTaps) {
-            float wr[kAaRegTaps];
-#pragma unroll
-            for (int k = 0; k < kAaRegTaps; ++k)
-                wr[k] = k < hnx ? hwx[k] : 0.0f;
-            for (int32_t rr = threadIdx.y; rr < wh; rr += bh) {
-                const unsigned char *wrow = win + static_cast<int64_t>(rr) * win_w * PB;
-                float h[C], p[C];
-                Pix<T, C>::load(wrow, hx0, p);
-                fma_first(h, wr[0], p);
-#pragma unroll
-                for (int k = 1; k < kAaRegTaps; ++k) {
-                    if (k < hnx) {
-                        Pix<T, C>::load(wrow, hx0 + k, p);
-                        fma_next(h, wr[k], p);
-                    }
-                }
-                float *hp = hbuf + (static_cast<int64_t>(rr) * bw + hc) * C;
-#pragma unroll
-                for (int ch = 0; ch < C; ++ch)
-                    hp[ch] = h[ch];
-            }
-        } else {
-            for (int32_t rr = threadIdx.y; rr < wh; rr += bh) {
-                const unsigned char *wrow = win + static_cast<int64_t>(rr) * win_w * PB;
-                float h[C], p[C];
-                Pix<T, C>::load(wrow, hx0, p);
-                fma_first(h, hwx[0], p);
-                for (int32_t k = 1; k < hnx; ++k) {
-                    Pix<T, C>::load(wrow, hx0 + k, p);
-                    fma_next(h, hwx[k], p);
-                }
-                float *hp = hbuf + (static_cast<int64_t>(rr) * bw + hc) * C;
-#pragma unroll
-                for (int ch = 0; ch < C; ++ch)
-                    hp[ch] = h[ch];
-            }
-        }
-        __syncthreads();
-        const int32_t px = blockIdx.x * bw + threadIdx.x;
-        const int32_t py = by * bh + threadIdx.y;
-        if (px < a.out_w && py < a.dst_rows) {
-            const int32_t r0 = ylo[threadIdx.y] - wy0, ny = yn[threadIdx.y];
-            const float *wyr = yw + threadIdx.y * ky;
-            float acc[C], h[C];
-            for (int32_t j = 0; j < ny; ++j) {
-                const float *hp = hbuf + (static_cast<int64_t>(r0 + j) * bw + threadIdx.x) * C;
-#pragma unroll
-                for (int ch = 0; ch < C; ++ch)
-                    h[ch] = hp[ch];
-                if (j == 0)
-                    fma_first(acc, wyr[0], h);
-                else
-                    fma_next(acc, wyr[j], h);
-            }
-            unsigned char *dst = a.dst + static_cast<int64_t>(blockIdx.z) * a.dst_plane_pitch +
-                                 static_cast<int64_t>(py) * a.dst_pitch;
-            Pix<T, C>::store(dst, px, acc);
-        }
-        // the next tile rewrites the row tables, the window and the row buffer
-        __syncthreads();
     }
 }
 
@@ -2091,60 +1796,11 @@ hipError_t launch_filter(const ResizeArgs &a, int32_t dtype, int32_t channels, c
 
 }  // namespace
 
-namespace {
-template <int R, typename T, int C>
-hipError_t launch_aa_typed(const ResizeArgs &a, const xr_tile &tile, hipStream_t stream)
-{
-    const dim3 block(tile.block_w, tile.block_h, 1);
-    const dim3 grid((a.out_w + tile.block_w - 1) / tile.block_w,
-                    (a.dst_rows + tile.block_h - 1) / tile.block_h, a.planes);
-    if (tile.kernel == XR_KERNEL_GATHER) {
-        const AaPlan plan = aa_plan(a.in_w, a.in_h, a.out_w, a.out_h, R, tile.block_w, tile.block_h);
-        hipLaunchKernelGGL((k_gather_aa<R, T, C>), grid, block, plan.lds_bytes, stream, a, plan.kx, plan.ky);
-    } else {
-        const AaPlan plan = aa_tile_plan(a.in_w, a.in_h, a.out_w, a.out_h, R, tile.block_w, tile.block_h,
-                                         Pix<T, C>::kBytes, C);
-        // tiles per workgroup down a tile column: the column tables are then
-        // built once per tpb tiles, while the grid keeps kAaMinBlocks
-        // workgroups
-        const int64_t cols = static_cast<int64_t>(grid.x) * grid.z;
-        int32_t tpb = 1;
-        while (tpb < kAaTilesPerBlock && cols * ((grid.y + 2 * tpb - 1) / (2 * tpb)) >= kAaMinBlocks)
-            tpb *= 2;
-        const dim3 grid_t(grid.x, (grid.y + tpb - 1) / tpb, grid.z);
-        hipLaunchKernelGGL((k_tile_aa<R, T, C>), grid_t, block, plan.lds_bytes, stream, a, plan.kx, plan.ky,
-                           plan.win_w, plan.win_h, tpb);
-    }
-    return hipGetLastError();
-}
-
-template <int R>
-hipError_t launch_aa(const ResizeArgs &a, int32_t dtype, int32_t channels, const xr_tile &tile,
-                     hipStream_t stream)
-{
-    switch (dtype) {
-    case XR_U8:
-        return channels == 4 ? launch_aa_typed<R, uint8_t, 4>(a, tile, stream)
-                             : launch_aa_typed<R, uint8_t, 1>(a, tile, stream);
-    case XR_F16:
-        return channels == 4 ? launch_aa_typed<R, _Float16, 4>(a, tile, stream)
-                             : launch_aa_typed<R, _Float16, 1>(a, tile, stream);
-    case XR_F32:
-        return channels == 4 ? launch_aa_typed<R, float, 4>(a, tile, stream)
-                             : launch_aa_typed<R, float, 1>(a, tile, stream);
-    default:
-        return hipErrorInvalidValue;
-    }
-}
-}  // namespace
-
 hipError_t launch_forward(const ResizeArgs &a, int32_t filter, int32_t dtype, int32_t channels,
                           const xr_tile &tile, int32_t mode, hipStream_t stream)
 {
-    if (filter == XR_BILINEAR_AA)
-        return launch_aa<1>(a, dtype, channels, tile, stream);
-    if (filter == XR_BICUBIC_AA)
-        return launch_aa<2>(a, dtype, channels, tile, stream);
+    if (filter == XR_BILINEAR_AA || filter == XR_BICUBIC_AA)
+        return launch_antialiased(a, filter, dtype, channels, tile, stream);
     if (filter == XR_BICUBIC)
         return launch_filter<kBicubic>(a, dtype, channels, tile, mode, stream);
     if (filter == XR_NEAREST)

@@ -1,0 +1,466 @@
+// Walk of the filters whose results gather a varying number of samples: the
+// antialiased forward filters and the adjoint at any ratio.
+//
+// A result value is sum_j wy_j (sum_k wx_k v[j][k]) over a contiguous range
+// of samples per axis, columns first, both in ascending order. A wavefront
+// owns 64 result columns and a strip of result rows, and walks the sample
+// rows the strip reads, each once, in order:
+//  * the rows are staged in LDS some 8 KiB ahead (xr_stage.hpp);
+//  * a lane filters its column's samples of RB staged rows at a time, all
+//    their LDS reads first, with the column's weights in registers (past
+//    kGatherRegTaps samples: an LDS table of the workgroup);
+//  * a filtered row is added at once to the result rows it belongs to: at
+//    most kSlots consecutive ones, held in registers at slot
+//    (row mod kSlots), each stored when its last sample row has been added.
+//    So the filtered rows need no buffer, and a sample row is filtered once
+//    per strip instead of once per tile of a few rows.
+// The row side is a table of the wavefront in LDS with one entry per sample
+// row: the weight per slot, and which slots are active, new and complete.
+//
+// What bounds it: instruction issue (bicubic x0.5 of a 4096^2 RGBA uint8 image:
+// 98.7 us with a block's window and filtered rows in LDS, 37.6 us so, 2.2 TB/s;
+// 16.1 M VALU instructions, 21 of the 36 us at the 2-cycle rate; 192 bilinear
+// uint8 planes 375 x 500 -> 224^2: 134.7 to 29.8 us). Measured and left out: two
+// windows a wavefront, the next rows arriving while the staged ones are
+// filtered (34.9 to 36.4 us against 36.4; planes 32 against 30).
+//
+// A policy P supplies the tap ranges and weights:
+//   kSlots      power of two, at least the result rows a sample row reaches
+//   kFirstMul   the first term of a row sum is a product (else a fused
+//               multiply-add onto zero)
+//   the geometry, and per axis the first sample and count of a result index
+//   (range_x, range_y) and its weights (weights_x, weights_y into w(k), and
+//   weights_x into an array, zero past the count)
+#pragma once
+
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include <algorithm>
+#include <type_traits>
+
+#include "xr_device.hpp"
+#include "xr_internal.h"
+#include "xr_stage.hpp"
+
+namespace xr {
+
+// LDS layout and strip of a launch (host side, see gather_shape).
+struct GatherShape {
+    int32_t waves;       // wavefronts per workgroup (strips below one another)
+    int32_t strip;       // result rows per wavefront, at most 64
+    int32_t rows_cap;    // sample rows of a strip, at most
+    int32_t kx;          // column weights per column, at most (a multiple of 4)
+    int32_t big;         // more of them than a walk holds in registers
+    int32_t col_bytes;   // column table of the workgroup (big)
+    int32_t wave_bytes;  // row table and window of a wavefront
+    int32_t win_off, win_bytes;
+    int32_t lds_bytes;   // dynamic LDS of a workgroup
+};
+
+constexpr int32_t kGatherCols = 64;
+constexpr int32_t kGatherWaves = 4;
+constexpr int32_t kGatherRegTaps = 10;
+constexpr int64_t kGatherWindow = 8192;
+
+// Strips are the tallest of 64 .. 4 rows that give kGatherMinWaves wavefronts
+// (12 per compute unit): a strip re-filters the sample rows it shares with the
+// next one, but a wavefront alone on its SIMD issues at most every fourth
+// cycle and waits for each load. Bicubic x0.5 of a 4096^2 RGBA image (2048
+// wavefronts at 32 rows, 4096 at 16): 38.4 and 36.4 us; 192 bilinear planes
+// 375 x 500 -> 224^2 (3072 at 64 rows): 30.4 us, 31.4 at 16 rows.
+//
+// 0: fewer than kGatherLeastWaves wavefronts even at 4 rows, too few to hide
+// that latency; kernels that spread one tile's rows over a workgroup are then
+// faster (44 antialiased resizes of 60 .. 8000 K output pixels: from 0.40x to
+// 0.93x their speed below 700 wavefronts, 1.04x to 5.1x above 1000).
+constexpr int64_t kGatherMinWaves = 3072, kGatherLeastWaves = 1024;
+template <class RowsCap>
+inline int64_t gather_strip(int64_t res_w, int64_t res_rows, int64_t planes, int64_t pitch, RowsCap rows_cap)
+{
+    const auto waves = [&](int64_t strip) {
+        return ((res_w + kGatherCols - 1) / kGatherCols) * ((res_rows + strip - 1) / strip) * planes;
+    };
+    int64_t strip = 64;
+    while (strip > 4 && (waves(strip) < kGatherMinWaves || rows_cap(strip) * pitch >= (int64_t(1) << 31)))
+        strip /= 2;
+    return waves(strip) < kGatherLeastWaves || rows_cap(strip) * pitch >= (int64_t(1) << 31) ? 0 : strip;
+}
+
+// The launch of a walk whose sample rows hold at most win_px samples of
+// px_bytes and whose strips of n result rows read at most rows_cap(n) sample
+// rows; false when a workgroup's LDS would not fit.
+template <class RowsCap>
+inline bool gather_shape(GatherShape &g, int32_t slots, int32_t kx, int32_t win_px, int32_t px_bytes,
+                         int64_t strip, RowsCap rows_cap)
+{
+    if (kx > 1024)
+        return false;
+    g.kx = (kx + 3) / 4 * 4;
+    g.strip = static_cast<int32_t>(strip);
+    g.big = kx > kGatherRegTaps;
+    g.col_bytes = g.big ? kGatherCols * 4 * g.kx : 0;
+    const int64_t row_bytes = (static_cast<int64_t>(win_px) * px_bytes + 30) / 16 * 16;
+    const int64_t cap = rows_cap(strip);
+    g.rows_cap = static_cast<int32_t>(cap);
+    g.win_off = static_cast<int32_t>((cap * 4 * (slots + 1) + 15) / 16 * 16);
+    g.win_bytes = static_cast<int32_t>(row_bytes * std::max<int64_t>(1, std::min(cap, kGatherWindow / row_bytes)));
+    // a column with fewer taps than its neighbours reads as many samples
+    g.wave_bytes = g.win_off + g.win_bytes + (g.kx * px_bytes + 8 + 15) / 16 * 16;
+    const int32_t most = 64 * 1024;
+    for (g.waves = kGatherWaves; g.waves > 1 && g.col_bytes + g.waves * g.wave_bytes > most;)
+        g.waves /= 2;
+    g.lds_bytes = g.col_bytes + g.waves * g.wave_bytes;
+    return g.lds_bytes <= most;
+}
+
+// Bytes as float32 operands without a conversion: byte j of a dword, masked
+// in place, is the bit pattern of the number (byte 2^(8j)) 2^-149 (j < 3; the
+// exponent field holds at most 1), the last one after a shift as j = 0. With
+// the weight scaled by 2^(126 - 8j) the product is the byte's, times 2^-23,
+// and every sum of such products rounds as the unscaled one does (nothing
+// here is small enough to lose bits); the row weights carry the 2^23. On
+// gfx950 the mask takes a 2-cycle issue slot, v_cvt_f32_ubyte a 4-cycle one
+// (measured), and a multiply-add takes 2 with either operand.
+
+// Samples of one staged row that belong to a lane's column: N samples of T, C
+// from LDS, then sample t as C operands and their weights.
+template <typename T, int C, int N>
+struct SampleRun {
+    static constexpr int PB = dev::Pix<T, C>::kBytes;
+    static constexpr bool kBytes = std::is_same_v<T, uint8_t>;
+    unsigned char b[(N * PB + 3) / 4 * 4];
+
+    __device__ __forceinline__ void load(const unsigned char *win, uint32_t at)
+    {
+        dev::lds_run<N * PB, PB>(b, win, at);
+    }
+    __device__ __forceinline__ void terms(int t, float (&v)[C]) const
+    {
+        if constexpr (kBytes && C == 4) {
+            uint32_t d;
+            __builtin_memcpy(&d, b + 4 * t, 4);
+            v[0] = __builtin_bit_cast(float, d & 0xffu);
+            v[1] = __builtin_bit_cast(float, d & 0xff00u);
+            v[2] = __builtin_bit_cast(float, d & 0xff0000u);
+            v[3] = __builtin_bit_cast(float, d >> 24);
+        } else if constexpr (kBytes) {
+            uint32_t d;
+            __builtin_memcpy(&d, b + t / 4 * 4, 4);
+            v[0] = __builtin_bit_cast(float, t % 4 == 3 ? d >> 24 : d & (0xffu << (8 * (t % 4))));
+        } else {
+            dev::Pix<T, C>::load(b, t, v);
+        }
+    }
+};
+
+// Weight of sample t (held as scale<T, C>(t) times the weight) for channel ch.
+template <typename T, int C>
+__device__ __forceinline__ float sample_scale(int t)
+{
+    if (!std::is_same_v<T, uint8_t>)
+        return 1.0f;
+    return C == 4 ? 0x1p110f : t % 4 == 1 ? 0x1p118f : t % 4 == 2 ? 0x1p110f : 0x1p126f;
+}
+template <typename T, int C>
+__device__ __forceinline__ void sample_weights(float w, float (&wt)[C])
+{
+#pragma unroll
+    for (int ch = 0; ch < C; ++ch)
+        wt[ch] = !(std::is_same_v<T, uint8_t> && C == 4) ? w
+                 : ch == 1                                ? w * 0x1p8f
+                 : ch == 2                                ? w
+                                                          : w * 0x1p16f;
+}
+
+// BIG: more than kGatherRegTaps samples per column; the column weights then
+// come from an LDS table of the workgroup instead of registers.
+template <class P, typename T, int C, bool BIG>
+__global__ void __launch_bounds__(256, 4) k_gather_walk(ResizeArgs a, GatherShape g)
+{
+    using namespace dev;
+    constexpr int S = P::kSlots;
+    constexpr int PB = Pix<T, C>::kBytes;
+    constexpr bool kBytes = std::is_same_v<T, uint8_t>;
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+    const int32_t lane = static_cast<int32_t>(threadIdx.x);
+    const int32_t wave = __builtin_amdgcn_readfirstlane(static_cast<int32_t>(threadIdx.y));
+    const int32_t plane = blockIdx.z;
+    const int32_t res_w = P::result_w(a);
+    const int32_t c_first = static_cast<int32_t>(blockIdx.x) * kGatherCols;
+    const bool inside = c_first + lane < res_w;
+
+    float *colw = reinterpret_cast<float *>(lds);  // BIG: [kx][64]
+    unsigned char *mine = lds + g.col_bytes + wave * g.wave_bytes;
+    float *roww = reinterpret_cast<float *>(mine);                        // [rows_cap][S]
+    uint32_t *rowf = reinterpret_cast<uint32_t *>(roww + g.rows_cap * S); // [rows_cap]
+    unsigned char *win = mine + g.win_off;
+
+    // the lane's column: samples [lo, lo + cnt)
+    const int32_t x = min(c_first + lane, res_w - 1);
+    int32_t lo, cnt;
+    P::range_x(a, x, lo, cnt);
+    cnt = min(cnt, g.kx);
+    int32_t kn = g.kx, kmin = 0;  // most and fewest samples of a column of this tile
+    while (kn > 0 && __builtin_amdgcn_ballot_w64(cnt >= kn) == 0)
+        --kn;
+    while (kmin < kn && __builtin_amdgcn_ballot_w64(cnt <= kmin) == 0)
+        ++kmin;
+    if constexpr (BIG) {
+        if (wave == 0) {
+            P::weights_x(a, x, lo, cnt, [&](int32_t k) -> float & { return colw[k * kGatherCols + lane]; });
+            for (int32_t k = 0; k < g.kx; ++k)
+                colw[k * kGatherCols + lane] =
+                    k < cnt ? colw[k * kGatherCols + lane] * sample_scale<T, C>(k) : 0.0f;
+        }
+        __syncthreads();
+    }
+
+    // the strip's result rows y_a .. y_b - 1 and sample rows r_lo .. r_lo + rows - 1
+    const int32_t y_a = static_cast<int32_t>(blockIdx.y * blockDim.y + wave) * g.strip;
+    const int32_t y_b = min(y_a + g.strip, P::result_rows(a));
+    if (y_a >= y_b)
+        return;
+    const int32_t o = min(y_a + lane, y_b - 1);  // (strips of up to 64 rows: a result row per lane)
+    int32_t o_lo, o_n;
+    P::range_y(a, o, o_lo, o_n);
+    const int32_t r_lo = __builtin_amdgcn_readfirstlane(o_lo);
+    const int32_t rows = min(__builtin_amdgcn_readlane(o_lo + o_n, 63) - r_lo, g.rows_cap);
+
+    const int32_t seg0 = min(__builtin_amdgcn_readfirstlane(lo), P::walked_w(a) - 1);
+    const int32_t seg1 = max(__builtin_amdgcn_readlane(lo + cnt - 1, 63), seg0);
+    const uint32_t loff = static_cast<uint32_t>((lo - seg0) * PB);
+    const unsigned char *src = a.src + static_cast<int64_t>(plane) * a.src_plane_pitch +
+                               static_cast<int64_t>(P::stored_row(a, r_lo)) * a.src_pitch +
+                               static_cast<int64_t>(seg0) * PB;
+    RowStage st;
+    st.init(src, static_cast<uint32_t>(a.src_pitch), (seg1 - seg0 + 1) * PB, 0, 0);
+    const uint32_t lp = st.lds_pitch();
+    int32_t rc = min(max(g.win_bytes / static_cast<int32_t>(lp), 1), 64);  // (a lane holds a row's flags)
+    rc = rc > 4 ? rc / 4 * 4 : rc;
+    if (rows > 0)
+        st.request(win, 0, min(rc, rows), lane);  // in flight while the tables are built
+
+    // row table
+    o_lo -= r_lo;
+    o_n = min(o_n, rows - o_lo);
+    for (int32_t i = lane; i < rows * S; i += 64)
+        roww[i] = 0.0f;
+    for (int32_t i = lane; i < rows; i += 64)
+        rowf[i] = 0;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    const bool mine_o = y_a + lane < y_b;
+    if (mine_o) {
+        const int32_t slot = lane & (S - 1);
+        P::weights_y(a, o, o_lo + r_lo, o_n, [&](int32_t k) -> float & { return roww[(o_lo + k) * S + slot]; });
+        for (int32_t k = 0; k < o_n; ++k) {
+            if (kBytes)
+                roww[(o_lo + k) * S + slot] *= 0x1p23f;
+            // active, new (first sample row), complete (last one)
+            atomicOr(&rowf[o_lo + k], ((k == 0 ? 0x101u : 0x1u) << slot) | (k == o_n - 1 ? 0x10000u << slot : 0u));
+        }
+        // a row without samples follows the sample row before its place
+        if (o_n == 0 && o_lo > 0)
+            atomicAdd(&rowf[o_lo - 1], 0x1000000u);
+    }
+    // rows without samples before the first sample row
+    const int32_t lead =
+        __builtin_popcountll(__builtin_amdgcn_ballot_w64(mine_o && o_lo + o_n <= 0));
+
+    unsigned char *const dst = a.dst + static_cast<int64_t>(plane) * a.dst_plane_pitch +
+                               static_cast<int64_t>(y_a) * a.dst_pitch +
+                               static_cast<int64_t>(c_first) * PB;
+    float acc[S][C];
+#pragma unroll
+    for (int s = 0; s < S; ++s)
+#pragma unroll
+        for (int ch = 0; ch < C; ++ch)
+            acc[s][ch] = 0.0f;
+    int32_t y = 0;  // rows of the strip that are stored
+    auto zeros = [&](int32_t m) __attribute__((always_inline)) {
+        for (; m > 0; --m, ++y) {
+            const float z[C] = {};
+            if (inside)
+                Pix<T, C>::store(dst + static_cast<int64_t>(y) * a.dst_pitch, lane, z);
+        }
+    };
+    zeros(lead);
+
+    // add filtered row h of the strip (flags f, weights w) to its result rows
+    // and store those that it completes
+    auto add_row = [&](uint32_t f, const float (&w)[S], const float (&h)[C]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int s = 0; s < S; ++s) {
+            if constexpr (kBytes) {
+                fma_next(acc[s], w[s], h);
+            } else {
+                if (P::kFirstMul && (f >> (8 + s)) & 1u)
+                    fma_first(acc[s], w[s], h);
+                else if ((f >> s) & 1u)
+                    fma_next(acc[s], w[s], h);
+            }
+        }
+        if (f >= 0x10000u) {
+            const int32_t y0 = y;
+#pragma unroll
+            for (int s = 0; s < S; ++s)
+                if ((f >> (16 + s)) & 1u) {
+                    const int32_t yy = y0 + ((s - y0) & (S - 1));
+                    if (inside)
+                        Pix<T, C>::store(dst + static_cast<int64_t>(yy) * a.dst_pitch, lane, acc[s]);
+#pragma unroll
+                    for (int ch = 0; ch < C; ++ch)
+                        acc[s][ch] = 0.0f;
+                    ++y;
+                }
+            zeros(static_cast<int32_t>(f >> 24));
+        }
+    };
+
+    // every sample row of the strip: filter(rows of the chunk from i0 on,
+    // their LDS offsets) gives RB filtered rows
+    auto walk = [&](auto rb_tag, auto filter) __attribute__((always_inline)) {
+        constexpr int RB = decltype(rb_tag)::value;
+        for (int32_t base = 0; base < rows; base += rc) {
+            const int32_t n = min(rc, rows - base);
+            if (base > 0) {
+                RowStage::drain_lds();
+                st.request(win, base, n, lane);
+            }
+            RowStage::wait();
+            const int32_t li = min(lane, n - 1);  // lane i holds row i's flags and place
+            const uint32_t flags = rowf[base + li];
+            const uint32_t place = static_cast<uint32_t>(li) * lp + st.start(base + li);
+            for (int32_t i0 = 0; i0 < n; i0 += RB) {
+                float wr[RB][S];
+                uint32_t at[RB];
+#pragma unroll
+                for (int q = 0; q < RB; ++q) {
+                    const int32_t i = min(i0 + q, n - 1);
+                    at[q] = __builtin_amdgcn_readlane(place, i) + loff;
+                    __builtin_memcpy(wr[q], __builtin_assume_aligned(roww + (base + i) * S, 4 * S), 4 * S);
+                }
+                float h[RB][C];
+                filter(at, h);
+#pragma unroll
+                for (int q = 0; q < RB; ++q)
+                    if (i0 + q < n)
+                        add_row(__builtin_amdgcn_readlane(flags, i0 + q), wr[q], h[q]);
+            }
+        }
+    };
+
+    if constexpr (!BIG) {
+        // up to 2 NP samples per column, their weights in registers
+        auto run = [&](auto np_tag) __attribute__((always_inline)) {
+            constexpr int N = 2 * decltype(np_tag)::value;
+            constexpr int RB = N * PB > 72 ? 1 : N * PB > (C == 4 ? 32 : 48) ? 2 : C == 4 || N * PB > 24 ? 4 : 8;
+            float w[N];
+            P::weights_x(a, x, lo, cnt, w);
+            float wt[N][C];
+#pragma unroll
+            for (int t = 0; t < N; ++t)
+                sample_weights<T, C>(w[t] * sample_scale<T, C>(t), wt[t]);
+            walk(std::integral_constant<int, RB>{},
+                 [&](const uint32_t (&at)[RB], float (&h)[RB][C]) __attribute__((always_inline)) {
+                     SampleRun<T, C, N> run[RB];
+#pragma unroll
+                     for (int q = 0; q < RB; ++q)
+                         run[q].load(win, at[q]);
+                     __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                     for (int q = 0; q < RB; ++q)
+#pragma unroll
+                         for (int ch = 0; ch < C; ++ch)
+                             h[q][ch] = 0.0f;
+#pragma unroll
+                     for (int t = 0; t < N; ++t) {
+                         // (bytes: the weights past a column's samples are zero)
+                         if (kBytes || t < kmin || t < cnt) {
+#pragma unroll
+                             for (int q = 0; q < RB; ++q) {
+                                 float v[C];
+                                 run[q].terms(t, v);
+#pragma unroll
+                                 for (int ch = 0; ch < C; ++ch)
+                                     h[q][ch] = t == 0 ? wt[t][ch] * v[ch] : __builtin_fmaf(wt[t][ch], v[ch], h[q][ch]);
+                             }
+                         }
+                     }
+                 });
+        };
+        switch ((kn + 1) / 2) {
+        case 0:
+        case 1:
+            run(std::integral_constant<int, 1>{});
+            break;
+        case 2:
+            run(std::integral_constant<int, 2>{});
+            break;
+        case 3:
+            run(std::integral_constant<int, 3>{});
+            break;
+        case 4:
+            run(std::integral_constant<int, 4>{});
+            break;
+        default:
+            run(std::integral_constant<int, 5>{});
+            break;
+        }
+    } else {
+        constexpr int RB = PB >= 8 ? 2 : C == 4 ? 4 : 8;
+        walk(std::integral_constant<int, RB>{},
+             [&](const uint32_t (&at)[RB], float (&h)[RB][C]) __attribute__((always_inline)) {
+#pragma unroll
+                 for (int q = 0; q < RB; ++q)
+#pragma unroll
+                     for (int ch = 0; ch < C; ++ch)
+                         h[q][ch] = 0.0f;
+                 auto group = [&](auto first_tag, int32_t k) __attribute__((always_inline)) {
+                     SampleRun<T, C, 4> run[RB];
+                     float wt[4][C];
+#pragma unroll
+                     for (int t = 0; t < 4; ++t)
+                         sample_weights<T, C>(colw[(k + t) * kGatherCols + lane], wt[t]);
+#pragma unroll
+                     for (int q = 0; q < RB; ++q)
+                         run[q].load(win, at[q] + static_cast<uint32_t>(k * PB));
+#pragma unroll
+                     for (int t = 0; t < 4; ++t)
+                         if (kBytes || k + t < kmin || k + t < cnt) {
+#pragma unroll
+                             for (int q = 0; q < RB; ++q) {
+                                 float v[C];
+                                 run[q].terms(t, v);
+#pragma unroll
+                                 for (int ch = 0; ch < C; ++ch)
+                                     h[q][ch] = decltype(first_tag)::value && t == 0
+                                                    ? wt[t][ch] * v[ch]
+                                                    : __builtin_fmaf(wt[t][ch], v[ch], h[q][ch]);
+                             }
+                         }
+                 };
+                 group(std::true_type{}, 0);
+                 for (int32_t k = 4; k < kn; k += 4)
+                     group(std::false_type{}, k);
+             });
+    }
+    zeros(y_b - y_a - y);  // a strip without sample rows
+}
+
+// grid: column tiles x (strips / wavefronts) x planes
+template <class P, typename T, int C>
+inline hipError_t launch_gather_walk(const ResizeArgs &a, const GatherShape &g, int32_t res_w, int32_t res_rows,
+                                     hipStream_t stream)
+{
+    const int32_t rows = g.strip * g.waves;
+    const dim3 grid((res_w + kGatherCols - 1) / kGatherCols, (res_rows + rows - 1) / rows, a.planes);
+    if (g.big)
+        hipLaunchKernelGGL((k_gather_walk<P, T, C, true>), grid, dim3(64, g.waves), g.lds_bytes, stream, a, g);
+    else
+        hipLaunchKernelGGL((k_gather_walk<P, T, C, false>), grid, dim3(64, g.waves), g.lds_bytes, stream, a, g);
+    return hipGetLastError();
+}
+
+}  // namespace xr

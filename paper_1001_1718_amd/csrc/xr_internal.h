@@ -94,6 +94,11 @@ enum AxisMode : int32_t { kGeneral = 0, kUp2 = 1, kDown2 = 2 };
 
 hipError_t launch_forward(const ResizeArgs &a, int32_t filter, int32_t dtype, int32_t channels,
                           const xr_tile &tile, int32_t mode, hipStream_t stream);
+hipError_t launch_antialiased(const ResizeArgs &a, int32_t filter, int32_t dtype, int32_t channels,
+                              const xr_tile &tile, hipStream_t stream);
+// True when that launch of an LDS tile takes the gather walk, which needs no
+// block of its own to fit.
+bool antialiased_walk_supported(const ResizeArgs &a, int32_t filter, int32_t dtype, int32_t channels);
 // The batched launches of a prepared workspace: one per kind with grid[kind] > 0.
 hipError_t launch_batched(const void *ws, int32_t dtype, int32_t block_w, int32_t block_h, const int32_t *grid,
                           hipStream_t stream);
