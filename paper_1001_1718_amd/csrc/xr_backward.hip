@@ -16,6 +16,9 @@
 //  phase 2  vertical adjoint, gather: grad[r][c] = sum over the output rows y
 //           whose taps include r of wy_j(y) * u[y][c], summed in ascending y.
 //
+// Where enough strips fill the GPU the same sums run as a gather walk without
+// the row buffer and its barriers (AdjointWalk below).
+//
 // Every sum has a fixed order, so the result is deterministic (bit for bit
 // the same on every run and for every tiling of the launch). The exact-x2
 // walk below (float32 and float16) is deterministic as well.
@@ -25,6 +28,7 @@
 
 #include "xr_buffer.hpp"
 #include "xr_device.hpp"
+#include "xr_gather_walk.hpp"
 #include "xr_internal.h"
 
 namespace xr {
@@ -204,6 +208,113 @@ __global__ void __launch_bounds__(kBwdThreads) k_bwd_owner(ResizeArgs a, int32_t
         }
     }
 }
+
+// ---------------------------------------------------------------------------
+// Gather walk (xr_gather_walk.hpp)
+// ---------------------------------------------------------------------------
+//
+// The same sums in the same order as k_bwd_owner, walked down the upstream
+// rows: a source column's samples are the outputs that reach it, and an
+// upstream row reaches K consecutive source rows, its (clamped) taps.
+// Against the owner tiles: bicubic x1.5 of 48 float32 planes of 512^2, 95.7 to
+// 48.5 us (3.4 TB/s); bilinear x0.75 of 96 float16 planes 480 x 640, 61.4 to
+// 38.8 us (2.4 TB/s). What bounds it now: instruction issue and the waits of a
+// wavefront for its next rows.
+template <int FILTER>
+struct AdjointWalk {
+    using TP = Taps<FILTER>;
+    static constexpr int K = TP::K;
+    static constexpr int kSlots = K;
+    static constexpr bool kFirstMul = false;
+    __device__ __forceinline__ static int32_t result_w(const ResizeArgs &a) { return a.in_w; }
+    __device__ __forceinline__ static int32_t result_rows(const ResizeArgs &a) { return a.in_h; }
+    __device__ __forceinline__ static int32_t walked_w(const ResizeArgs &a) { return a.out_w; }
+    __device__ __forceinline__ static int32_t stored_row(const ResizeArgs &, int32_t r) { return r; }
+
+    // The outputs whose clamped taps reach source index c, [lo, lo + n): none
+    // (n = 0, between its neighbours' ranges) where c lies between the taps of
+    // adjacent outputs. As first_output and last_output, in unsigned 32 bits
+    // ((2m + 1) n_out < 2^32 for sides up to 32768).
+    __device__ __forceinline__ static void range(int32_t c, int32_t n_in, int32_t n_out, int32_t &lo, int32_t &n)
+    {
+        // outputs x with s(x) >= m: from ceil(((2m + 1) n_out - n_in) / (2 n_in)) on
+        const auto from = [&](int32_t m) {
+            if (m < 0)
+                return 0;
+            const uint32_t p = (2u * static_cast<uint32_t>(m) + 1u) * static_cast<uint32_t>(n_out);
+            const uint32_t q = static_cast<uint32_t>(n_in);
+            return p <= q ? 0 : min(static_cast<int32_t>((p - q + 2u * q - 1u) / (2u * q)), n_out);
+        };
+        lo = c <= 0 ? 0 : from(c - K + 1 - TP::LO);
+        const int32_t end = c >= n_in - 1 ? n_out : from(c - TP::LO + 1);
+        n = max(end - lo, 0);
+    }
+    // Summed weight of the taps of outputs lo + m that land on c, m ascending:
+    // put(m, weight). Taps by one division, then steps of 2 n_in.
+    template <class Put>
+    __device__ __forceinline__ static void each_weight(int32_t c, int32_t n_in, int32_t n_out, int32_t lo, int32_t n,
+                                                       Put put)
+    {
+        const int32_t den = 2 * n_out;
+        const int32_t num = static_cast<int32_t>((2u * static_cast<uint32_t>(lo) + 1u) * static_cast<uint32_t>(n_in) -
+                                                 static_cast<uint32_t>(n_out));
+        int32_t q = num / den;
+        int32_t rem = num - q * den;
+        if (rem < 0) {
+            q -= 1;
+            rem += den;
+        }
+        const int32_t sq = 2 * n_in / den, sr = 2 * n_in - sq * den;
+        const float d = static_cast<float>(den), rcp = __fdiv_rn(1.0f, d);
+        for (int32_t m = 0; m < n; ++m) {
+            float wt[K];
+            weights<FILTER>(div_rcp(static_cast<float>(rem), d, rcp), div_rcp(static_cast<float>(den - rem), d, rcp), wt);
+            float sum = 0.0f;
+#pragma unroll
+            for (int i = 0; i < K; ++i)
+                if (clampi(q + TP::LO + i, 0, n_in - 1) == c)
+                    sum += wt[i];
+            put(m, sum);
+            q += sq;
+            rem += sr;
+            if (rem >= den) {
+                rem -= den;
+                ++q;
+            }
+        }
+    }
+    __device__ __forceinline__ static void range_x(const ResizeArgs &a, int32_t c, int32_t &lo, int32_t &n)
+    {
+        range(c, a.in_w, a.out_w, lo, n);
+    }
+    __device__ __forceinline__ static void range_y(const ResizeArgs &a, int32_t r, int32_t &lo, int32_t &n)
+    {
+        range(r, a.in_h, a.out_h, lo, n);
+    }
+    template <class W>
+    __device__ __forceinline__ static void weights_x(const ResizeArgs &a, int32_t c, int32_t lo, int32_t n, W w)
+    {
+        each_weight(c, a.in_w, a.out_w, lo, n, [&](int32_t m, float v) { w(m) = v; });
+    }
+    template <int N>
+    __device__ __forceinline__ static void weights_x(const ResizeArgs &a, int32_t c, int32_t lo, int32_t n,
+                                                     float (&w)[N])
+    {
+#pragma unroll
+        for (int m = 0; m < N; ++m)
+            w[m] = 0.0f;
+        each_weight(c, a.in_w, a.out_w, lo, n, [&](int32_t m, float v) {
+#pragma unroll
+            for (int k = 0; k < N; ++k)
+                w[k] = k == m ? v : w[k];
+        });
+    }
+    template <class W>
+    __device__ __forceinline__ static void weights_y(const ResizeArgs &a, int32_t r, int32_t lo, int32_t n, W w)
+    {
+        each_weight(r, a.in_h, a.out_h, lo, n, [&](int32_t m, float v) { w(m) = v; });
+    }
+};
 
 // ---------------------------------------------------------------------------
 // Exact x2 upscale on both axes: transposed strip walk in registers
@@ -601,6 +712,25 @@ BwdPlan plan_backward(const ResizeArgs &a)
     }
 }
 
+// Launch of the gather walk: false where too few strips make it the slower
+// one (of 38 adjoints it was 1.08x to 2.3x as fast in the 30 with 1,092 strips
+// or more), or it does not apply (pitches past 4 MiB, windows too large for LDS).
+template <int FILTER, typename T, int C>
+bool bwd_walk_shape(const ResizeArgs &a, const BwdPlan &p, GatherShape &g)
+{
+    constexpr int K = Taps<FILTER>::K;
+    if (a.src_pitch > kStageMaxPitch)
+        return false;
+    // outputs that reach n adjacent source indices: at most (n + K - 1) out / in + 2
+    const auto reach = [](int64_t n, int64_t n_in, int64_t n_out) {
+        return std::min<int64_t>(((n + K - 1) * n_out + n_in - 1) / n_in + 2, n_out);
+    };
+    const auto cap = [&](int64_t strip) { return reach(strip, a.in_h, a.out_h); };
+    const int64_t strip = gather_strip(a.in_w, a.in_h, a.planes, a.src_pitch, cap);
+    return strip > 0 && gather_shape(g, K, p.nmax, static_cast<int32_t>(reach(kGatherCols, a.in_w, a.out_w)),
+                                     static_cast<int32_t>(sizeof(T)) * C, strip, cap);
+}
+
 template <int FILTER, typename T, int C>
 hipError_t launch_bwd_typed(const ResizeArgs &a, hipStream_t stream)
 {
@@ -609,6 +739,9 @@ hipError_t launch_bwd_typed(const ResizeArgs &a, hipStream_t stream)
     const BwdPlan p = plan_backward<FILTER, C>(a);
     if (p.lds == 0)
         return hipErrorInvalidConfiguration;
+    GatherShape g;
+    if (bwd_walk_shape<FILTER, T, C>(a, p, g))
+        return launch_gather_walk<AdjointWalk<FILTER>, T, C>(a, g, a.in_w, a.in_h, stream);
     const dim3 grid((a.in_w + p.tw - 1) / p.tw, (a.in_h + p.th - 1) / p.th, a.planes);
     hipLaunchKernelGGL((k_bwd_owner<FILTER, T, C>), grid, dim3(kBwdThreads), p.lds, stream, a, p.tw, p.th,
                        p.max_rows, p.nmax, p.nmax_y);
