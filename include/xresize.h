@@ -109,10 +109,14 @@ typedef struct {
  *                               block_w * block_h <= 512. An exact x2 upscale
  *                               or x0.5 downscale on both axes runs a variant
  *                               specialised for it.
- *         = XR_KERNEL_STRIP_ANY : the strip kernel without the x2 and x0.5
- *                               variants (the same results; for comparisons)
- *         = XR_KERNEL_STRIP_LDS : the strip walk with each source row staged
- *                               once per workgroup in LDS, taps read from LDS
+ *                               Other scales run the staged walk where its
+ *                               rows fit in LDS (source rows staged there a
+ *                               wavefront at a time, strips of at most 256
+ *                               rows), else the per-tap strip kernel.
+ *         = XR_KERNEL_STRIP_ANY : the per-tap strip kernel at every scale
+ *                               (the same results; for comparisons)
+ *         = XR_KERNEL_STRIP_LDS : the staged walk with its own columns per
+ *                               thread
  *                               (any scale; block_h = 1, block_w a multiple of
  *                               64 up to 512, ppt_x = 4 for 4 channels and 8
  *                               for one). XR_ERR_ARG when one workgroup's row
@@ -200,16 +204,16 @@ int xr_resize(const xr_image *src, const xr_image *dst, int32_t filter, int32_t 
               const xr_tile *tile, void *stream);
 
 /*
- * Batched resize of many images of uneven sizes and scales in ONE persistent
- * launch (the paper's per-image tiling question asked for a whole batch,
+ * Batched resize of many images of uneven sizes and scales in one launch per
+ * job kind (the paper's per-image tiling question asked for a whole batch,
  * section III.B).
  *
  * xr_batch_workspace_bytes(n): bytes of device workspace for n jobs.
  * xr_batch_prepare: validates every job exactly like xr_resize_*, groups
- *   the jobs by kind (filter x channel count; jobs narrower than the
- *   filter's taps or than one thread's run form a fifth kind), splits every
+ *   the jobs by kind (filter x channel count; jobs narrower than one thread's
+ *   run or shrinking too far along x form a fifth kind), splits every
  *   output into tiles of `tile` (NULL = the shape xr_batch_autotune chose for
- *   this dtype, else 256x1 threads with 14-row strips; block_w a multiple of
+ *   this dtype, else 128x2 threads with 8- to 24-row strips; block_w a multiple of
  *   64, block_w * block_h <= 256, ppt_y <= 256; the output columns per
  *   thread are fixed per kind, tile.ppt_x is ignored), orders each kind's
  *   jobs largest-first, and uploads the job table and tile prefix sums to
@@ -217,7 +221,7 @@ int xr_resize(const xr_image *src, const xr_image *dst, int32_t filter, int32_t 
  *   with an asynchronous copy on `stream`. The host copy of `jobs` may be
  *   reused once the call returns. NOT capturable (XR_ERR_CAPTURE).
  *   All jobs must share one dtype.
- * xr_resize_batched: one persistent launch per job kind present, back to
+ * xr_resize_batched: one launch per job kind present, back to
  *   back on `stream`, that together process every tile of every prepared
  *   job. Capturable and replayable; it allocates nothing. The workspace must
  *   not be used by two launches at the same time.

@@ -21,7 +21,7 @@ BUILD = os.path.join(HERE, "_build")
 LIBRARY = os.path.join(HERE, "libxresize.so")
 ARCH = os.environ.get("XR_OFFLOAD_ARCH", "gfx950")
 
-SOURCES = ["xr_api.cpp", "xr_forward.hip", "xr_aa.hip", "xr_backward.hip"]
+SOURCES = ["xr_api.cpp", "xr_forward.hip", "xr_walk.hip", "xr_aa.hip", "xr_backward.hip"]
 
 # -ffp-contract=off: every fused multiply-add is written explicitly, so the
 #   float32 evaluation order (and the result) is fixed by the source.

@@ -310,31 +310,79 @@ std::map<TuneKey, xr_tile> g_tuned;
 //  exact x2     256x1 threads, 4 (RGBA) or 8 (one channel) columns per
 //               thread, strips of 24 rows (the x2 walk rounds a strip up to
 //               a multiple of 8 rows);
-//  exact x0.5   512x1 threads, 2 or 4 columns, strips of 6 rows;
-//  other        128x2 threads, 2 or 4 columns, strips of 30 rows when the
-//               rows grow, 6 when they shrink (a strip then walks several
-//               source rows per output row).
+//  exact x0.5   512x1 threads, 2 or 4 columns, strips of 6 rows; bicubic 256x1
+//               threads, 1 or 4 columns, strips of 4 or 2 rows, banded;
+//  other        the staged walk: 64x4 threads (wavefronts below one another),
+//               its own columns per thread, strips of 16 rows down to 2;
+//               where it does not fit 128x2 threads, 2 or 4 columns, strips
+//               of 30 rows when the rows grow, 6 when they shrink.
 // Strips are shortened (24/30 -> 16 -> 14 -> 8 -> 6 -> 2 -> 1 rows) until the
 // launch has about 8 wavefronts per SIMD (2048 x 4); tiny outputs use 64-wide
 // workgroups.
-xr_tile default_tile(int32_t channels, int32_t in_w, int32_t in_h, int32_t out_w, int32_t rows,
-                     int32_t out_h, int32_t planes)
+// `exact`: the x2 and x0.5 kernels apply to those scales.
+constexpr double kWalkWaves = 220.0;  // per row of a strip
+// Outputs of fewer runs (of 256 columns, 128 of RGBA, in one row) take the
+// per-tap strips instead, which start without tables or staged rows (60
+// resizes: 0.60x to 0.96x their speed below, 1.0x to 4.4x above).
+constexpr int64_t kWalkLeastRuns1 = 1700, kWalkLeastRuns4 = 2100;
+xr_tile default_tile(int32_t filter, int32_t dtype, int32_t channels, int32_t in_w, int32_t in_h, int32_t out_w,
+                     int32_t rows, int32_t out_h, int32_t planes, bool exact)
 {
     const bool c4 = channels == 4;
     xr_tile t{};
     t.kernel = XR_KERNEL_STRIP;
     t.order = 0;
     int first;
-    if (out_w == 2 * in_w && out_h == 2 * in_h) {
+    exact = exact && ((out_w == 2 * in_w && out_h == 2 * in_h) || (2 * out_w == in_w && 2 * out_h == in_h));
+    const auto staged = [&] {
+        t.block_w = 64;
+        t.block_h = 4;
+        t.ppt_x = xr::walk_ppx(channels, elem_size(dtype) * channels);
+        // a strip of h rows re-filters K - 1 source rows of its neighbour's,
+        // but needs as many wavefronts for each row it walks: about one per
+        // compute unit (measured: gray x1.3 of a 2479 x 3507 page best at 16
+        // rows, 3705 wavefronts; float32 RGBA x0.36 of 4000 x 3000 at 4 rows,
+        // 6210; bilinear gray x2 of 512^2 at 4 rows, 1024)
+        const int64_t cols = (static_cast<int64_t>(out_w) + 64 * t.ppt_x - 1) / (64 * t.ppt_x);
+        const int64_t runs = (static_cast<int64_t>(out_w) + (c4 ? 127 : 255)) / (c4 ? 128 : 256);
+        if (runs * rows * planes < (c4 ? kWalkLeastRuns4 : kWalkLeastRuns1)) {
+            t.kernel = XR_KERNEL_STRIP_ANY;
+            t.block_h = 1;
+            t.ppt_x = c4 ? 2 : 4;
+            t.ppt_y = 1;
+            return t;
+        }
+        const double walked = std::max(1.0, static_cast<double>(in_h) / out_h);  // source rows per output row
+        for (t.ppt_y = 16; t.ppt_y > 1; t.ppt_y /= 2)
+            if (static_cast<double>(cols * ((rows + t.ppt_y - 1) / t.ppt_y) * planes) >= kWalkWaves * walked * t.ppt_y)
+                break;
+        return t;
+    };
+    const bool fits = xr::walk_fits(filter, dtype, channels, in_w, out_w);
+    if (!exact && fits)
+        return staged();
+    const bool up2 = exact && out_w == 2 * in_w;
+    if (up2) {
         t.block_w = 256;
         t.block_h = 1;
         t.ppt_x = c4 ? 4 : 8;
         first = 24;  // the x2 walk's strips of 12 row pairs (measured best on large images)
-    } else if (2 * out_w == in_w && 2 * out_h == in_h) {
+    } else if (exact) {
         t.block_w = 512;
         t.block_h = 1;
         t.ppt_x = c4 ? 2 : 4;
         first = 6;
+        if (filter == XR_BICUBIC) {
+            // strips share K - 2 source rows: neighbouring strips on one XCD,
+            // one column and 4 rows (RGBA: 4096^2 float16 35.9 -> 32.3 us, uint8
+            // 19.2 -> 15.1, 2048^2 float16 10.5 -> 8.5, against the shape above,
+            // which ran 2 rows) or 4 columns and 2 rows (4096^2 float32 18.1 ->
+            // 14.9, uint8 9.8 -> 9.4)
+            t.block_w = 256;
+            t.ppt_x = c4 ? 1 : 4;
+            t.order = 1;
+            first = c4 ? 4 : 2;
+        }
     } else {
         t.block_w = 128;
         t.block_h = 2;
@@ -345,18 +393,24 @@ xr_tile default_tile(int32_t channels, int32_t in_w, int32_t in_h, int32_t out_w
         const int64_t wcols = (static_cast<int64_t>(out_w) + 64 * u.ppt_x - 1) / (64 * u.ppt_x);
         return wcols * ((static_cast<int64_t>(rows) + u.ppt_y - 1) / u.ppt_y) * planes;
     };
-    const int64_t target = 8192;
-    const int steps[] = {first, 16, 14, 8, 6, 2, 1};
+    // (the x2 kernel's strips are whole eights of rows; 2048 wide RGBA uint8
+    // outputs: 7.1 us in 2,048 wavefronts of 4 columns, 6.3 us in 4,096 of 2)
+    const int steps[] = {first, 16, 14, 8, 6, 4, 2, 1};
     for (int ppy : steps) {
-        if (ppy > first)
+        if (ppy > first || (up2 && ppy % 8 != 0))
             continue;
         t.ppt_y = ppy;
-        if (waves(t) >= target)
+        if (waves(t) >= (up2 && ppy == 8 ? 4096 : 8192))
             return t;
     }
-    t.ppt_x = c4 ? 2 : 4;
+    // small outputs: one-byte pixels in runs of 4 columns take the staged walk
+    // (the x2 kernel moves whole dwords of source)
+    if (up2 && !c4 && elem_size(dtype) == 1 && fits)
+        return staged();
+    t.ppt_x = c4 ? (exact && !up2 && filter == XR_BICUBIC ? 1 : 2) : 4;
     t.block_w = 64;
     t.block_h = 1;
+    t.order = 0;
     return t;
 }
 
@@ -474,7 +528,7 @@ bool lds_usable(const xr_tile &t, int32_t filter, const xr_image &src, const xr_
                               src_aligned4(src));
 }
 
-xr_tile resolve_tile(const xr_tile *tile, int32_t filter, const xr_image &src, const xr_image &dst)
+xr_tile resolve_tile(const xr_tile *tile, int32_t filter, const xr_image &src, const xr_image &dst, int32_t mapping)
 {
     if (tile && tile->kernel != XR_KERNEL_AUTO)
         return *tile;
@@ -490,8 +544,9 @@ xr_tile resolve_tile(const xr_tile *tile, int32_t filter, const xr_image &src, c
                           : (tt.kernel != XR_KERNEL_STRIP_LDS || lds_usable(tt, filter, src, dst)))
             return tt;
     }
-    return default_tile(src.channels, src.width, src.height, dst.width, dst.rows, dst.height,
-                        dst.planes);
+    const xr_tile strip{XR_KERNEL_STRIP, 64, 1, 1, 1, 0};
+    return default_tile(filter, src.dtype, src.channels, src.width, src.height, dst.width, dst.rows, dst.height,
+                        dst.planes, axis_mode(src, dst, strip, filter, mapping) != xr::kGeneral);
 }
 
 int check_grid(const xr_tile &t, const xr_image &dst)
@@ -510,7 +565,7 @@ int resize_common(const xr_image *src, const xr_image *dst, const xr_tile *tile,
     int rc = check_pair(src, dst, filter, mapping);
     if (rc)
         return rc;
-    xr_tile t = resolve_tile(tile, filter, *src, *dst);
+    xr_tile t = resolve_tile(tile, filter, *src, *dst, mapping);
     if (is_aa(filter)) {
         // strip shapes (and the untuned default) mean the default antialiased
         // tile, whose LDS blocks fit
@@ -546,21 +601,44 @@ int resize_common(const xr_image *src, const xr_image *dst, const xr_tile *tile,
 struct BatchInfo {
     int32_t n_jobs;
     int32_t dtype;
-    int32_t block_w, block_h;
-    int32_t grid[xr::kBatchKinds];
+    xr::BatchLaunch launch;
 };
 std::mutex g_batch_mu;
 std::map<const void *, BatchInfo> g_batches;
 std::map<int32_t, xr_tile> g_batch_tuned;  // dtype -> shape chosen by xr_batch_autotune
 
-// Untuned batched shape: 256-wide workgroups, 14-row strips.
-xr_tile batch_default_tile(int32_t dtype)
+// The shape xr_batch_autotune chose for a type, if any.
+bool batch_tuned_tile(int32_t dtype, xr_tile &t)
 {
     std::lock_guard<std::mutex> lock(g_batch_mu);
     auto it = g_batch_tuned.find(dtype);
-    if (it != g_batch_tuned.end())
-        return it->second;
-    return xr_tile{XR_KERNEL_STRIP, 256, 1, 0, 14, 0};
+    if (it == g_batch_tuned.end())
+        return false;
+    t = it->second;
+    return true;
+}
+
+// Untuned batched shape: 128 x 2 threads and strips as tall as leave the
+// batch enough wavefronts (a strip re-filters the source rows it shares with
+// the next). Measured, uint8 (strips of 8 / 14 / 24 rows; wavefronts at 24):
+// 32 images up to 357^2 35.6 / 42 / 55 us (1,800); 108 up to 844^2 146 / 143 /
+// 148 us (17 thousand); 256 up to 2048^2 at 24 rows 997 us, at 32 1,053
+// (184 thousand).
+xr_tile batch_default_tile(const xr_job *jobs, int32_t n_jobs, int32_t dtype)
+{
+    xr_tile t{XR_KERNEL_STRIP, 128, 2, 0, 24, 0};
+    const auto waves = [&](int64_t strip) {
+        int64_t n = 0;
+        for (int32_t k = 0; k < n_jobs; ++k) {
+            const xr_image &d = jobs[k].dst;
+            const int64_t cols = 64 * xr::batch_ppx(jobs[k].filter, dtype, d.channels);
+            n += (d.width + cols - 1) / cols * ((d.rows + strip - 1) / strip) * d.planes;
+        }
+        return n;
+    };
+    if (waves(24) < 32768)
+        t.ppt_y = waves(14) < 12288 ? 8 : 14;
+    return t;
 }
 
 // The current device's architecture name and compute-unit count (the key of
@@ -689,14 +767,14 @@ int build_batch(const xr_job *jobs, int32_t n_jobs, const xr_tile *tile, unsigne
                 BatchInfo &info, void *stream, const char *caller)
 {
     const int32_t dtype = jobs[0].src.dtype;
-    xr_tile t{};
-    if (tile && tile->kernel != XR_KERNEL_AUTO) {
+    xr_tile t{XR_KERNEL_STRIP, 128, 2, 0, 24, 0};
+    const bool named = tile && tile->kernel != XR_KERNEL_AUTO;
+    if (named) {
         t = *tile;
         if (t.kernel != XR_KERNEL_STRIP)
             return fail(XR_ERR_ARG, "the batched launch takes a strip tile");
-    } else {
-        t = batch_default_tile(dtype);
     }
+    const bool tuned = !named && batch_tuned_tile(dtype, t);
     t.ppt_x = 0;  // fixed per job kind
     if (t.block_w < 64 || t.block_w % 64 != 0 || t.block_h < 1 || t.block_w * t.block_h > 256 ||
         t.ppt_y < 1 || t.ppt_y > xr::kBatchMaxStrip)
@@ -726,15 +804,15 @@ int build_batch(const xr_job *jobs, int32_t n_jobs, const xr_tile *tile, unsigne
     if (cs != hipStreamCaptureStatusNone)
         return fail(XR_ERR_CAPTURE, "%s called on a capturing stream", caller);
 
+    if (!named && !tuned)
+        t = batch_default_tile(jobs, n_jobs, dtype);
     // grouped by kind, largest output first within a kind
     const auto fc_of = [&](const xr_job &j) {
         return (j.filter == XR_BICUBIC ? 2 : 0) + (j.src.channels == 4 ? 1 : 0);
     };
     const auto kind_of = [&](const xr_job &j) {
-        const int32_t taps = j.filter == XR_BICUBIC ? 4 : 2;
-        if (j.src.width < taps || j.dst.width < xr::batch_ppx(j.filter, dtype, j.src.channels))
-            return xr::kBatchNarrow;
-        return fc_of(j);
+        return xr::batch_walk_need(make_args(j.src, j.dst), j.filter, dtype, j.src.channels, 1).ok ? fc_of(j)
+                                                                                                  : xr::kBatchNarrow;
     };
     // (std::sort with the job index as the last key: the same order as a
     // stable sort, and no temporary buffer)
@@ -773,6 +851,9 @@ int build_batch(const xr_job *jobs, int32_t n_jobs, const xr_tile *tile, unsigne
         const int64_t max_rows = (int64_t(1) << 31) / j.src.row_pitch - 6;
         strip = std::min<int64_t>(strip, std::max<int64_t>(1, max_rows * j.dst.height / j.src.height));
         b.strip_h = static_cast<int32_t>(strip);
+        const xr::BatchWalkNeed need = xr::batch_walk_need(b.a, j.filter, dtype, j.src.channels, b.strip_h);
+        hdr->table_bytes[kind] = std::max(hdr->table_bytes[kind], need.table_bytes);
+        hdr->win_bytes[kind] = std::max(hdr->win_bytes[kind], need.win_bytes);
         const int64_t tile_w =
             static_cast<int64_t>(t.block_w) * (kind == xr::kBatchNarrow ? 1 : xr::batch_ppx(j.filter, dtype, j.src.channels));
         const int64_t tile_h = static_cast<int64_t>(t.block_h) * b.strip_h;
@@ -785,27 +866,19 @@ int build_batch(const xr_job *jobs, int32_t n_jobs, const xr_tile *tile, unsigne
         if (hdr->tiles[k] >= (int64_t(1) << 31))
             return fail(XR_ERR_ARG, "batch has %lld tiles of one kind (limit 2^31)",
                         static_cast<long long>(hdr->tiles[k]));
-    int dev = 0, cus = 0;
-    e = hipGetDevice(&dev);
-    if (e == hipSuccess)
-        e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-    if (e != hipSuccess)
-        return fail_hip(e, "device query");
     hdr->n_jobs = n_jobs;
     hdr->dtype = dtype;
     hdr->block_w = t.block_w;
     hdr->block_h = t.block_h;
     hdr->ppt_y = t.ppt_y;
-    info = BatchInfo{n_jobs, dtype, t.block_w, t.block_h, {}};
+    info = BatchInfo{n_jobs, dtype, {t.block_w, t.block_h, {}, {}}};
     for (int32_t k = 0; k < xr::kBatchKinds; ++k) {
         if (hdr->tiles[k] == 0)
             continue;
-        const int32_t per_cu = xr::batched_blocks_per_cu(dtype, k, t.block_w * t.block_h);
-        hdr->grid[k] = static_cast<int32_t>(
-            std::max<int64_t>(1, std::min<int64_t>(static_cast<int64_t>(per_cu) * cus, hdr->tiles[k])));
-        info.grid[k] = hdr->grid[k];
-        hdr->ticket[k] = 0;
-        hdr->done[k] = 0;
+        info.launch.grid[k] = static_cast<int32_t>(hdr->tiles[k]);
+        if (k != xr::kBatchNarrow)
+            info.launch.lds[k] = static_cast<size_t>(t.block_w / 64 * t.block_h) *
+                                 xr::batch_walk_wave_bytes(hdr->table_bytes[k], hdr->win_bytes[k]);
     }
     return XR_OK;
 }
@@ -882,8 +955,7 @@ int xr_resize_batched(const void *dev_ws, int32_t n_jobs, void *stream)
     }
     if (n_jobs != info.n_jobs)
         return fail(XR_ERR_ARG, "n_jobs = %d but the workspace holds %d jobs", n_jobs, info.n_jobs);
-    const hipError_t e = xr::launch_batched(dev_ws, info.dtype, info.block_w, info.block_h, info.grid,
-                                            static_cast<hipStream_t>(stream));
+    const hipError_t e = xr::launch_batched(dev_ws, info.dtype, info.launch, static_cast<hipStream_t>(stream));
     if (e != hipSuccess)
         return fail_hip(e, "batched launch");
     return XR_OK;
@@ -920,7 +992,7 @@ int xr_resize_batched_static(const xr_job *jobs, int32_t n_jobs, const xr_tile *
         e = hipStreamSynchronize(static_cast<hipStream_t>(stream));
     if (e != hipSuccess)
         return fail_hip(e, "uploading the job table");
-    e = xr::launch_batched(ws, info.dtype, info.block_w, info.block_h, info.grid, static_cast<hipStream_t>(stream));
+    e = xr::launch_batched(ws, info.dtype, info.launch, static_cast<hipStream_t>(stream));
     if (e != hipSuccess)
         return fail_hip(e, "batched launch");
     return XR_OK;
@@ -1266,7 +1338,8 @@ int xr_get_tile(int32_t filter, int32_t dtype, int32_t channels, int32_t in_w, i
     std::lock_guard<std::mutex> lock(g_tune_mu);
     auto it = g_tuned.find(tune_key(filter, dtype, channels, in_w, in_h, out_w, out_h, 1));
     *out = it != g_tuned.end() ? it->second
-                               : default_tile(channels, in_w, in_h, out_w, out_h, out_h, 1);
+                               : default_tile(filter, dtype, channels, in_w, in_h, out_w, out_h, out_h, 1,
+                                              filter == XR_BILINEAR || filter == XR_BICUBIC);
     return XR_OK;
 }
 

@@ -7,6 +7,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "xr_device.hpp"
 
 namespace xr {
@@ -116,6 +118,26 @@ constexpr int cgcd(int a, int b) { return b == 0 ? a : cgcd(b, a % b); }
 constexpr int cmin(int a, int b) { return a < b ? a : b; }
 
 using namespace dev;
+
+// Encode N pixels into a byte buffer (uint8 pixels four to a dword).
+template <typename T, int C, int N, int BYTES, int ALIGN>
+__device__ __forceinline__ void encode_run(const float (&v)[N][C], RawBuf<BYTES, ALIGN> &out)
+{
+    if constexpr (std::is_same<T, uint8_t>::value && C == 1 && N % 4 == 0) {
+#pragma unroll
+        for (int g = 0; g < N / 4; ++g) {
+            uint32_t r = u8_insert(v[4 * g][0], 0, 0u);
+            r = u8_insert(v[4 * g + 1][0], 1, r);
+            r = u8_insert(v[4 * g + 2][0], 2, r);
+            r = u8_insert(v[4 * g + 3][0], 3, r);
+            *reinterpret_cast<uint32_t *>(out.b + 4 * g) = r;
+        }
+    } else {
+#pragma unroll
+        for (int c = 0; c < N; ++c)
+            Pix<T, C>::store(out.b, c, v[c]);
+    }
+}
 
 // Output runs of the walks.
 //

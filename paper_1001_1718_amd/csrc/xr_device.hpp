@@ -12,6 +12,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "xr_internal.h"
+
 namespace xr {
 namespace dev {
 
@@ -147,6 +149,62 @@ __device__ __forceinline__ float opaque(float v)
 __device__ __forceinline__ int32_t clampi(int32_t v, int32_t lo, int32_t hi)
 {
     return v < lo ? lo : (v > hi ? hi : v);
+}
+
+// Logical tile (bx, by) of this workgroup within its plane. order 0 keeps the
+// launch order. order 1 relies on the hardware dealing consecutive workgroups
+// to the 8 XCDs in turn and gives XCD k the k-th contiguous band of tiles
+// (a bijection for any tile count), so neighbouring tiles share an L2.
+__device__ __forceinline__ void tile_coords(int32_t order, int32_t &bx, int32_t &by)
+{
+    if (order == 0) {
+        bx = blockIdx.x;
+        by = blockIdx.y;
+        return;
+    }
+    const uint32_t gx = gridDim.x;
+    const uint32_t n = gx * gridDim.y;
+    const uint32_t h = blockIdx.y * gx + blockIdx.x;
+    const uint32_t q = n / 8, r = n % 8;
+    const uint32_t xcd = h % 8, slot = h / 8;
+    const uint32_t logical = xcd * q + min(xcd, r) + slot;
+    bx = static_cast<int32_t>(logical % gx);
+    by = static_cast<int32_t>(logical / gx);
+}
+
+// The batch job of this workgroup's tile (counted over the jobs of `kind`, in
+// rows of the grid) and the tile's place in it; false past the last tile.
+// Every field is uniform.
+__device__ __forceinline__ bool batch_tile(const unsigned char *__restrict__ ws, int32_t kind, BatchJob &job,
+                                           int32_t &plane, int32_t &tx, int32_t &ty)
+{
+    const BatchHeader *hdr = reinterpret_cast<const BatchHeader *>(ws);
+    const BatchJob *jobs = reinterpret_cast<const BatchJob *>(ws + kBatchHeaderBytes);
+    const int64_t tile = static_cast<int64_t>(blockIdx.y) * gridDim.x + blockIdx.x;
+    if (tile >= hdr->tiles[kind])
+        return false;
+    int32_t lo = hdr->job_lo[kind], hi = hdr->job_hi[kind] - 1;  // last job of the kind whose tile_begin <= tile
+    while (lo < hi) {
+        const int32_t mid = (lo + hi + 1) >> 1;
+        if (jobs[mid].tile_begin <= tile)
+            lo = mid;
+        else
+            hi = mid - 1;
+    }
+    static_assert(sizeof(BatchJob) % 4 == 0, "whole dwords");
+    uint32_t w[sizeof(BatchJob) / 4];
+    __builtin_memcpy(w, jobs + __builtin_amdgcn_readfirstlane(lo), sizeof(BatchJob));
+#pragma unroll
+    for (size_t i = 0; i < sizeof(BatchJob) / 4; ++i)
+        w[i] = __builtin_amdgcn_readfirstlane(w[i]);
+    __builtin_memcpy(&job, w, sizeof(BatchJob));
+    const uint32_t local = static_cast<uint32_t>(tile - job.tile_begin);  // tiles of a kind: below 2^31
+    const uint32_t per_plane = static_cast<uint32_t>(job.tiles_x * job.tiles_y);
+    plane = static_cast<int32_t>(local / per_plane);
+    const int32_t rem = static_cast<int32_t>(local - plane * per_plane);
+    ty = rem / job.tiles_x;
+    tx = rem - ty * job.tiles_x;
+    return true;
 }
 
 // ---- storage types ------------------------------------------------------

@@ -20,17 +20,12 @@
 //               everywhere, a contiguous run of 2 ppt_x - 2 + K source
 //               pixels per row, two source rows per output row, with the
 //               buffer-resource loads and stores of k_x2.
-//  k_strip_lds  any scale, each source row staged once per workgroup in LDS.
-//  k_batch_walk persistent launches over the tiles of many jobs, one per job
-//               kind (filter x channels); one window load per column and
-//               row weights from a per-wavefront LDS table.
-//  k_gather_aa, k_tile_aa  the antialiased filters (support stretched when
-//               shrinking): one pixel per thread from memory, or the block's
-//               source window staged in LDS and filtered separably.
+//  k_batch_narrow the batched jobs that the staged walk leaves.
 //
-// The bilinear and bicubic kernels evaluate each output with the same float32
-// operation sequence (xr_device.hpp), so their results are bit-identical; so
-// are the two antialiased kernels.
+// Other ratios run the staged walk (xr_walk.hip), antialiased filters the
+// kernels of xr_aa.hip. The bilinear and bicubic kernels evaluate each output
+// with the same float32 operation sequence (xr_device.hpp), so their results
+// are bit-identical.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -102,27 +97,6 @@ __device__ __forceinline__ void store_stream(unsigned char *p, const RawBuf<BYTE
                                         reinterpret_cast<uint32_t *>(__builtin_assume_aligned(p, 4)) + i);
     } else {
         store_raw<BYTES, ALIGN>(p, v);
-    }
-}
-
-
-// Encode N pixels into a byte buffer (uint8 pixels four to a dword).
-template <typename T, int C, int N, int BYTES, int ALIGN>
-__device__ __forceinline__ void encode_run(const float (&v)[N][C], RawBuf<BYTES, ALIGN> &out)
-{
-    if constexpr (std::is_same<T, uint8_t>::value && C == 1 && N % 4 == 0) {
-#pragma unroll
-        for (int g = 0; g < N / 4; ++g) {
-            uint32_t r = u8_insert(v[4 * g][0], 0, 0u);
-            r = u8_insert(v[4 * g + 1][0], 1, r);
-            r = u8_insert(v[4 * g + 2][0], 2, r);
-            r = u8_insert(v[4 * g + 3][0], 3, r);
-            *reinterpret_cast<uint32_t *>(out.b + 4 * g) = r;
-        }
-    } else {
-#pragma unroll
-        for (int c = 0; c < N; ++c)
-            Pix<T, C>::store(out.b, c, v[c]);
     }
 }
 
@@ -339,27 +313,6 @@ struct StripBody {
     }
 };
 
-// Logical tile (bx, by) of this workgroup within its plane. order 0 keeps the
-// launch order. order 1 relies on the hardware dealing consecutive workgroups
-// to the 8 XCDs in turn and gives XCD k the k-th contiguous band of tiles
-// (a bijection for any tile count), so neighbouring tiles share an L2.
-__device__ __forceinline__ void tile_coords(int32_t order, int32_t &bx, int32_t &by)
-{
-    if (order == 0) {
-        bx = blockIdx.x;
-        by = blockIdx.y;
-        return;
-    }
-    const uint32_t gx = gridDim.x;
-    const uint32_t n = gx * gridDim.y;
-    const uint32_t h = blockIdx.y * gx + blockIdx.x;
-    const uint32_t q = n / 8, r = n % 8;
-    const uint32_t xcd = h % 8, slot = h / 8;
-    const uint32_t logical = xcd * q + min(xcd, r) + slot;
-    bx = static_cast<int32_t>(logical % gx);
-    by = static_cast<int32_t>(logical / gx);
-}
-
 // Row strip of a thread: threadIdx.y selects one of blockDim.y strips stacked
 // vertically in the tile. blockDim.x is a multiple of the wavefront size, so
 // the strip is uniform across a wavefront.
@@ -414,173 +367,6 @@ struct LdsPlan {
              (PB >= 4 || aligned4);
     }
 };
-
-// The workgroup is one row strip (block_h = 1): all its threads read the same
-// source rows. Per source row, every lane loads CH chunks of the row segment
-// (coalesced, clamped into the segment, so the loads are unconditional) and
-// writes them to one of three LDS row buffers; after one barrier per row each
-// thread gathers its PPX * K taps from LDS, filters them into its ring, and
-// emits output rows exactly like k_strip (same weights, same order). Row
-// rho + 1 is written to LDS while row rho is filtered; row rho + 2 is in
-// flight from memory meanwhile. Every thread of the workgroup runs the same
-// loop and barrier sequence (the strip and trip count are uniform; threads
-// past the right edge only skip their stores).
-template <int FILTER, typename T, int C, int PPX, int CH>
-__global__ void __launch_bounds__(512) k_strip_lds(ResizeArgs a, int32_t strip_h, int32_t order,
-                                                   int32_t buf_bytes)
-{
-    using TP = Taps<FILTER>;
-    constexpr int K = TP::K;
-    constexpr int PB = Pix<T, C>::kBytes;
-    constexpr int CB = PB < 4 ? 4 : PB;
-    using Chunk = RawBuf<CB, CB>;
-    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
-
-    int32_t bx, by;
-    tile_coords(order, bx, by);
-    const int32_t bw = static_cast<int32_t>(blockDim.x);
-    const int32_t tid = static_cast<int32_t>(threadIdx.x);
-    const int32_t c_first = bx * bw * PPX;
-    const int32_t r_begin = by * strip_h;
-    if (c_first >= a.out_w || r_begin >= a.dst_rows)  // uniform over the workgroup
-        return;
-    const int32_t r_end = min(r_begin + strip_h, a.dst_rows);
-    const int32_t col0 = c_first + tid * PPX;
-    const int32_t c_last = min(c_first + bw * PPX - 1, a.out_w - 1);
-
-    // the workgroup's segment of source columns [seg0, seg1], staged from the
-    // chunk-aligned byte seg_b0 on
-    int32_t xa, xb;
-    float tq, uq;
-    source_tap<FILTER>(c_first, a.in_w, a.out_w, a.map_off, xa, tq, uq);
-    source_tap<FILTER>(c_last, a.in_w, a.out_w, a.map_off, xb, tq, uq);
-    const int32_t seg0 = clampi(xa + TP::LO, 0, a.in_w - 1);
-    const int32_t seg1 = clampi(xb + TP::LO + K - 1, 0, a.in_w - 1);
-    const int32_t seg_b0 = (seg0 * PB) & ~(CB - 1);
-    const int32_t nch = ((seg1 + 1) * PB - seg_b0 + CB - 1) / CB;
-
-    // this thread's taps, as byte offsets into the staged segment
-    int32_t toff[PPX][K];
-    float wx[PPX][K];
-#pragma unroll
-    for (int c = 0; c < PPX; ++c) {
-        const int32_t x = min(col0 + c, a.out_w - 1);
-        int32_t x0;
-        float t, u;
-        source_tap<FILTER>(x, a.in_w, a.out_w, a.map_off, x0, t, u);
-        weights<FILTER>(t, u, wx[c]);
-#pragma unroll
-        for (int i = 0; i < K; ++i)
-            toff[c][i] = clampi(x0 + TP::LO + i, 0, a.in_w - 1) * PB - seg_b0;
-    }
-    const unsigned char *src = a.src + static_cast<int64_t>(blockIdx.z) * a.src_plane_pitch;
-    unsigned char *dst = a.dst + static_cast<int64_t>(blockIdx.z) * a.dst_plane_pitch;
-    const int32_t ncols = min(PPX, a.out_w - col0);
-    const bool full_run = ncols == PPX && a.aligned16;
-
-    int32_t y = a.dst_row0 + r_begin;  // next output row to emit (logical)
-    const int32_t y_end = a.dst_row0 + r_end;
-    int32_t y0, y0_last;
-    float ty, uy, tl, ul;
-    // one division per strip: the rows' taps use its reciprocal
-    const float rcp_h = __fdiv_rn(1.0f, static_cast<float>(2 * a.out_h));
-    source_tap_rcp<FILTER>(y, a.in_h, a.out_h, a.map_off, rcp_h, y0, ty, uy);
-    source_tap_rcp<FILTER>(y_end - 1, a.in_h, a.out_h, a.map_off, rcp_h, y0_last, tl, ul);
-    float wy[K];
-    weights<FILTER>(ty, uy, wy);
-    int32_t last = y0 + TP::LO + K - 1;  // last tap row of output y
-    const int32_t rho0 = y0 + TP::LO;
-    const int32_t rho1 = y0_last + TP::LO + K - 1;
-
-    Chunk q[CH];
-    // the CH chunks of source row rho (clamped into the band, and to rho1:
-    // requests past the last needed row re-read it) that this lane stages
-    auto fetch = [&](int32_t rho) {
-        const int32_t rr = clampi(min(rho, rho1), a.src_row0, a.src_row0 + a.src_rows - 1) - a.src_row0;
-        const unsigned char *row = src + static_cast<int64_t>(rr) * a.src_pitch + seg_b0;
-#pragma unroll
-        for (int k = 0; k < CH; ++k)
-            q[k] = load_raw<CB, CB>(row + min(tid + k * bw, nch - 1) * CB);
-    };
-    auto stage = [&](int32_t buf) {
-        unsigned char *b = lds + buf * buf_bytes;
-#pragma unroll
-        for (int k = 0; k < CH; ++k) {
-            const int32_t i = tid + k * bw;
-            if (i < nch)
-                store_raw<CB, CB>(b + i * CB, q[k]);
-        }
-    };
-    float ring[K][PPX][C];
-    auto filter_row = [&](int32_t buf, float (&out)[PPX][C]) {
-        const unsigned char *b = lds + buf * buf_bytes;
-#pragma unroll
-        for (int c = 0; c < PPX; ++c) {
-            float p[C];
-            Pix<T, C>::load(b + toff[c][0], 0, p);
-            fma_first(out[c], wx[c][0], p);
-#pragma unroll
-            for (int i = 1; i < K; ++i) {
-                Pix<T, C>::load(b + toff[c][i], 0, p);
-                fma_next(out[c], wx[c][i], p);
-            }
-        }
-    };
-    auto emit_all = [&](auto slot_tag, int32_t rho) {
-        constexpr int I = decltype(slot_tag)::value;
-        while (y < y_end && last == rho) {
-            unsigned char *drow = dst + static_cast<int64_t>(y - a.dst_row0) * a.dst_pitch;
-            float v[PPX][C];
-#pragma unroll
-            for (int c = 0; c < PPX; ++c) {
-                fma_first(v[c], wy[0], ring[(I + 1) % K][c]);
-#pragma unroll
-                for (int j = 1; j < K; ++j)
-                    fma_next(v[c], wy[j], ring[(I + 1 + j) % K][c]);
-            }
-            if (full_run) {
-                RawBuf<PPX * PB, cmin(16, PPX * PB)> out;
-                encode_run<T, C, PPX>(v, out);
-                store_stream<PPX * PB, cmin(16, PPX * PB)>(drow + static_cast<int64_t>(col0) * PB, out);
-            } else {
-#pragma unroll
-                for (int c = 0; c < PPX; ++c)
-                    if (c < ncols)
-                        Pix<T, C>::store(drow, col0 + c, v[c]);
-            }
-            ++y;
-            if (y < y_end) {
-                source_tap_rcp<FILTER>(y, a.in_h, a.out_h, a.map_off, rcp_h, y0, ty, uy);
-                weights<FILTER>(ty, uy, wy);
-                last = y0 + TP::LO + K - 1;
-            }
-        }
-    };
-    // Row rho sits in LDS buffer (rho - rho0) mod 3 and ring slot
-    // (rho - rho0) mod K. Buffer (b + 1) mod 3 was last read two rows ago,
-    // before the previous barrier, so it can be refilled now.
-    auto step = [&](auto slot_tag, int32_t rho) {
-        constexpr int I = decltype(slot_tag)::value;
-        if (rho <= rho1) {  // uniform over the workgroup
-            const int32_t b = (rho - rho0) % 3;
-            stage(b == 2 ? 0 : b + 1);  // row rho + 1
-            fetch(rho + 2);
-            __syncthreads();
-            filter_row(b, ring[I % K]);
-            emit_all(slot_tag, rho);
-        }
-    };
-    fetch(rho0);
-    stage(0);
-    fetch(rho0 + 1);
-    __syncthreads();
-    for (int32_t rho = rho0; rho <= rho1; rho += 4) {
-        step(std::integral_constant<int, 0>{}, rho);
-        step(std::integral_constant<int, 1>{}, rho + 1);
-        step(std::integral_constant<int, 2>{}, rho + 2);
-        step(std::integral_constant<int, 3>{}, rho + 3);
-    }
-}
 
 // ---------------------------------------------------------------------------
 // edge runs of the exact-ratio walks
@@ -1029,561 +815,62 @@ __global__ void __launch_bounds__(512) k_x05(ResizeArgs a, int32_t nr, int32_t s
 }
 
 // ---------------------------------------------------------------------------
-// k_batch_walk: persistent launches over the tiles of many jobs
+// k_batch_narrow: the batched jobs that the staged walk (xr_walk.hip) leaves
 // ---------------------------------------------------------------------------
-//
-// The jobs are grouped by kind (filter x channel count). Each kind has a
-// launch of its own, compiled for it (its own columns per thread and register
-// budget); the launches follow one another on the stream. Within a kind,
-// workgroups take tiles from the kind's ticket counter; its jobs are ordered
-// largest first, so long tiles start early and short ones fill the tail. A
-// tile is (blockDim.x * PPX) columns by (blockDim.y * strip_h) rows of one
-// plane of one job (strip_h per job). The last workgroup of a launch to finish
-// resets its kind's counters, so the launches can be replayed (e.g. from a HIP
-// graph) without host-side clearing. Jobs whose source is narrower than the
-// filter's taps, or whose output is narrower than a run, form a fifth kind
-// that runs the per-tap strip walk.
-//
-// The walk of one thread (SrcWalk) covers PPX adjacent output columns of a
-// strip of output rows:
-//  * columns: a column's K taps are K adjacent source pixels (eqs. 2-5).
-//    Pixels of under 4 bytes are read with one window load of K pixels from
-//    the first tap clamped into the row, the taps then picked out of it with
-//    byte permutes (the identity away from the image edges); wider pixels
-//    with one load per tap at its clamped offset. The last run of a row is
-//    moved left to end at the image edge (its pixels are computed twice, to
-//    the same bits), so every store writes a whole run;
-//  * rows: each source row the strip reads is loaded a few rows ahead and
-//    filtered once into ring slot (row mod K), and every output row is
-//    emitted as soon as its last tap row is filtered, reading its K rows
-//    from slots that are constants of the 4-row unrolled loop; the row taps
-//    advance by a constant quotient and remainder (one division per strip),
-//    and the rows' weights are computed once per strip, one row per lane,
-//    into a table of the wavefront in LDS read back per output row as a
-//    broadcast;
-//  * memory: loads and stores go through buffer resources over the strip's
-//    source rows and output rows.
-// The float32 sequence per output value is the one every kernel uses, so
-// the results are bit-identical to the single-image launches.
 
-// K pixels (TB bytes) of a column's window; 2-byte windows (one-channel uint8
-// bilinear) take one 16-bit load, zero-extended into the window's dword
-template <int TB>
-__device__ __forceinline__ void buf_load_win(unsigned char *dst, __amdgpu_buffer_rsrc_t r, uint32_t off)
-{
-    if constexpr (TB % 4 == 0) {
-        buf_load<TB>(dst, r, off);
-    } else {
-        static_assert(TB == 2, "2-byte windows");
-        const uint32_t v = __builtin_amdgcn_raw_buffer_load_b16(r, off, 0, 0);
-        __builtin_memcpy(dst, &v, 4);
-    }
-}
-
-// The column side of the batched walk: PPX adjacent output columns of one
-// thread, their weights and how their taps are loaded from a source row.
-template <int FILTER, typename T, int C, int PPX>
-struct ColTaps {
-    using TP = Taps<FILTER>;
-    static constexpr int K = TP::K;
-    static constexpr int PB = Pix<T, C>::kBytes;
-    static constexpr int TB = K * PB;                 // tap bytes of a column
-    static constexpr int WB = TB < 4 ? 4 : TB;        // their registers
-    static constexpr int OB = PPX * PB;
-    static constexpr bool kWindow = PB <= 2;
-    static constexpr int NS = kWindow ? (TB + 3) / 4 : 1;
-    static constexpr int NO = kWindow ? 1 : K;        // load offsets per column
-    using Win = RawBuf<WB, 4>;
-    using WRow = BatchWeights<K>;
-
-    uint32_t off[PPX][NO];    // byte offsets within a row: the window, or each tap
-    uint32_t psel[PPX][NS];   // window: permute selectors of the taps
-    float wx[PPX][K];
-    __amdgpu_buffer_rsrc_t srsrc;
-    int32_t row_lo, row_hi;   // logical source rows the source resource starts and ends with
-    uint32_t src_pitch;
-
-    // the taps of source row r (clamped into the resource's rows)
-    __device__ __forceinline__ void load_row(Win (&w)[PPX], int32_t r) const
-    {
-        const int32_t rr = clampi(r, row_lo, row_hi);
-        const uint32_t ro = static_cast<uint32_t>(rr - row_lo) * src_pitch;
-#pragma unroll
-        for (int c = 0; c < PPX; ++c) {
-            if constexpr (kWindow) {
-                buf_load_win<TB>(w[c].b, srsrc, ro + off[c][0]);
-            } else {
-#pragma unroll
-                for (int i = 0; i < K; ++i)
-                    buf_load<PB>(w[c].b + i * PB, srsrc, ro + off[c][i]);
-            }
-        }
-    }
-
-    // window: tap i of column c is pixel clamp(f + i, 0, n_in - 1) - ld of it
-    __device__ __forceinline__ void pick(Win (&w)[PPX]) const
-    {
-        if constexpr (kWindow) {
-#pragma unroll
-            for (int c = 0; c < PPX; ++c) {
-                uint32_t d[2];
-                __builtin_memcpy(d, w[c].b, 4);
-                d[1] = 0;
-                if constexpr (WB >= 8)
-                    __builtin_memcpy(&d[1], w[c].b + 4, 4);
-                uint32_t r[NS];
-#pragma unroll
-                for (int k = 0; k < NS; ++k)
-                    r[k] = __builtin_amdgcn_perm(d[1], d[0], psel[c][k]);
-                __builtin_memcpy(w[c].b, r, 4 * NS);
-            }
-        }
-    }
-
-    // the load offsets (and selectors) of column c, first tap f; the
-    // window needs n_in >= K
-    __device__ __forceinline__ void make_taps(int c, int32_t f, int32_t in_w)
-    {
-        if constexpr (kWindow) {
-            const int32_t ld = max(0, min(f, in_w - K));
-            off[c][0] = static_cast<uint32_t>(ld * PB);
-            uint32_t sel[NS];
-#pragma unroll
-            for (int k = 0; k < NS; ++k)
-                sel[k] = 0x0c0c0c0cu;  // bytes past the taps: zero
-#pragma unroll
-            for (int i = 0; i < K; ++i) {
-                const uint32_t idx = static_cast<uint32_t>(clampi(f + i, 0, in_w - 1) - ld);
-#pragma unroll
-                for (int b = 0; b < PB; ++b) {
-                    const int pos = i * PB + b;  // byte of the picked taps
-                    const uint32_t from = idx * PB + b;
-                    sel[pos / 4] = (sel[pos / 4] & ~(0xffu << (8 * (pos % 4)))) | (from << (8 * (pos % 4)));
-                }
-            }
-#pragma unroll
-            for (int k = 0; k < NS; ++k)
-                psel[c][k] = sel[k];
-        } else {
-#pragma unroll
-            for (int i = 0; i < K; ++i)
-                off[c][i] = static_cast<uint32_t>(clampi(f + i, 0, in_w - 1) * PB);
-        }
-    }
-
-    __device__ __forceinline__ void hfilter(const Win (&w)[PPX], float (&out)[PPX][C]) const
-    {
-#pragma unroll
-        for (int c = 0; c < PPX; ++c) {
-            float p[C];
-            decode<T, C>(w[c].b, 0, p);
-            fma_first(out[c], wx[c][0], p);
-#pragma unroll
-            for (int i = 1; i < K; ++i) {
-                decode<T, C>(w[c].b, i, p);
-                fma_next(out[c], wx[c][i], p);
-            }
-        }
-    }
-
-    // columns c0 .. c0 + PPX - 1 (inside the image)
-    __device__ __forceinline__ void set_columns(const ResizeArgs &a, int32_t c0)
-    {
-#pragma unroll
-        for (int c = 0; c < PPX; ++c) {
-            int32_t x0;
-            float t, u;
-            source_tap<FILTER>(c0 + c, a.in_w, a.out_w, a.map_off, x0, t, u);
-            weights<FILTER>(t, u, wx[c]);
-            make_taps(c, x0 + TP::LO, a.in_w);
-        }
-    }
-
-    // the source resource over logical rows [lo, hi] clamped into the band
-    __device__ __forceinline__ void set_source(const ResizeArgs &a, int32_t plane, int32_t lo, int32_t hi)
-    {
-        const int32_t band_lo = a.src_row0, band_hi = a.src_row0 + a.src_rows - 1;
-        row_lo = clampi(lo, band_lo, band_hi);
-        row_hi = clampi(hi, band_lo, band_hi);
-        src_pitch = static_cast<uint32_t>(a.src_pitch);
-        const unsigned char *sbase = a.src + static_cast<int64_t>(plane) * a.src_plane_pitch +
-                                     static_cast<int64_t>(row_lo - a.src_row0) * a.src_pitch;
-        srsrc = buf_rsrc(sbase, static_cast<uint32_t>(static_cast<int64_t>(row_hi - row_lo + 1) * a.src_pitch));
-    }
-};
-
-// The row side of the batched walk: the strip's row taps (one floor
-// division for its first and last row, then steps of 2 n_in = sq den + sr)
-// and its row weights, computed one row per lane into the wavefront's LDS
-// table.
-template <int FILTER>
-struct RowTaps {
-    using TP = Taps<FILTER>;
-    static constexpr int K = TP::K;
-    using WRow = BatchWeights<K>;
-    int32_t den, sq, sr;
-    int32_t y_first, rows;
-
-    __device__ __forceinline__ void floor_div(const ResizeArgs &a, int32_t yy, int32_t &qq, int32_t &rr) const
-    {
-        const int32_t num = (2 * yy + a.map_off) * a.in_h - a.map_off * a.out_h;
-        qq = num / den;
-        rr = num - qq * den;
-        if (rr < 0) {
-            qq -= 1;
-            rr += den;
-        }
-    }
-
-    __device__ __forceinline__ void advance(int32_t &q, int32_t &r) const
-    {
-        r += sr;
-        q += sq;
-        if (r >= den) {
-            r -= den;
-            ++q;
-        }
-    }
-
-    __device__ __forceinline__ void init(const ResizeArgs &a, int32_t r_begin, int32_t r_end, WRow *table,
-                                         int32_t tid)
-    {
-        y_first = a.dst_row0 + r_begin;
-        rows = r_end - r_begin;
-        den = 2 * a.out_h;
-        sq = (2 * a.in_h) / den;
-        sr = 2 * a.in_h - sq * den;
-        const int32_t lane = tid & 63;
-        const float rcp_h = __fdiv_rn(1.0f, static_cast<float>(den));
-        for (int32_t base = 0; base < rows; base += 64) {
-            const int32_t yy = y_first + min(base + lane, rows - 1);
-            int32_t y0;
-            float t, u;
-            source_tap_rcp<FILTER>(yy, a.in_h, a.out_h, a.map_off, rcp_h, y0, t, u);
-            WRow e;
-            weights<FILTER>(t, u, e.w);
-            if (base + lane < kBatchMaxStrip)
-                table[base + lane] = e;
-        }
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    }
-};
-
-// Cache policy of the batched walk's output stores: non-temporal only. The
-// batch's rows start at arbitrary byte offsets, so a wavefront's run covers
-// partial lines at both ends; measured on the uneven 256-image batch, plain
-// non-temporal stores beat the streaming past-the-L2 policy of the exact
-// walks by 8% (and write-back stores by 12%).
-constexpr int kBatchStore = 2;
-
-// Source-row driven walk (any scale): each source row the strip reads is
-// loaded PD rows ahead, filtered once into ring slot (row mod K), and every
-// output row is emitted as soon as its last tap row is filtered, reading its
-// K rows from slots that are constants of the 4-row unrolled loop.
-template <int FILTER, typename T, int C, int PPX>
-struct SrcWalk : ColTaps<FILTER, T, C, PPX> {
-    using B = ColTaps<FILTER, T, C, PPX>;
-    using typename B::Win;
-    using typename B::WRow;
-    using TP = Taps<FILTER>;
-    static constexpr int K = B::K, PB = B::PB, OB = B::OB, WB = B::WB;
-    static constexpr int PD = PPX * WB <= 32 ? 3 : 1;  // rows loaded ahead
-    static constexpr int Q = PD + 1;                  // divides 4
-
-    float ring[K][PPX][C];
-    Win rawq[Q][PPX];
-    float wy[K];
-    RowTaps<FILTER> rt;
-    const WRow *wt;
-    __amdgpu_buffer_rsrc_t drsrc;
-    uint32_t dst_off, dst_pitch, lane_off;
-    int32_t y, y_end, q, rem, last;
-
-    __device__ __forceinline__ void read_weights()
-    {
-        const WRow e = wt[min(y - rt.y_first, rt.rows - 1)];
-#pragma unroll
-        for (int j = 0; j < K; ++j)
-            wy[j] = e.w[j];
-    }
-
-    template <int I>
-    __device__ __forceinline__ void emit()
-    {
-        float v[PPX][C];
-#pragma unroll
-        for (int c = 0; c < PPX; ++c) {
-            fma_first(v[c], wy[0], ring[(I + 1) % K][c]);
-#pragma unroll
-            for (int j = 1; j < K; ++j)
-                fma_next(v[c], wy[j], ring[(I + 1 + j) % K][c]);
-        }
-        RawBuf<OB, cmin(16, cgcd(OB, 16))> out;
-        encode_run<T, C, PPX>(v, out);
-        buf_store<OB, kBatchStore>(out.b, drsrc, dst_off + lane_off);
-        ++y;
-        dst_off += dst_pitch;
-        rt.advance(q, rem);
-        last = q + TP::LO + K - 1;
-        read_weights();
-    }
-
-    template <int I>
-    __device__ __forceinline__ void step(int32_t rho, int32_t rho1)
-    {
-        this->load_row(rawq[(I + PD) % Q], min(rho + PD, rho1));
-        if (rho <= rho1) {
-            this->pick(rawq[I % Q]);
-            this->hfilter(rawq[I % Q], ring[I % K]);
-            while (y < y_end && last == rho)
-                emit<I>();
-        }
-    }
-
-    __device__ __forceinline__ void run(const ResizeArgs &a, int32_t plane, int32_t col0, int32_t r_begin,
-                                        int32_t r_end, WRow *table, int32_t tid)
-    {
-        const int32_t c0 = min(col0, a.out_w - PPX);
-        lane_off = col0 < a.out_w ? static_cast<uint32_t>(c0 * PB) : 0x80000000u;
-        this->set_columns(a, c0);
-        rt.init(a, r_begin, r_end, table, tid);
-        wt = table;
-        y = rt.y_first;
-        y_end = y + rt.rows;
-        int32_t q_last, r_last;
-        rt.floor_div(a, y, q, rem);
-        rt.floor_div(a, y_end - 1, q_last, r_last);
-        last = q + TP::LO + K - 1;
-        read_weights();
-        const int32_t rho0 = q + TP::LO;
-        const int32_t rho1 = q_last + TP::LO + K - 1;
-        this->set_source(a, plane, rho0, rho1);
-        unsigned char *dbase = a.dst + static_cast<int64_t>(plane) * a.dst_plane_pitch +
-                               static_cast<int64_t>(r_begin) * a.dst_pitch;
-        drsrc = buf_rsrc(dbase, static_cast<uint32_t>(static_cast<int64_t>(rt.rows) * a.dst_pitch));
-        dst_pitch = static_cast<uint32_t>(a.dst_pitch);
-        dst_off = 0;
-#pragma unroll
-        for (int i = 0; i < PD; ++i)
-            this->load_row(rawq[i % Q], min(rho0 + i, rho1));
-        for (int32_t rho = rho0; rho <= rho1; rho += 4) {
-            step<0>(rho, rho1);
-            step<1>(rho + 1, rho1);
-            step<2>(rho + 2, rho1);
-            step<3>(rho + 3, rho1);
-        }
-    }
-};
-
-template <int FILTER, typename T, int C>
-__global__ void __launch_bounds__(256) k_batch_walk(unsigned char *ws, int32_t kind)
-{
-    constexpr int PPX = batch_ppx(FILTER == kBicubic ? XR_BICUBIC : XR_BILINEAR, DType<T>::kCode, C);
-    using W = SrcWalk<FILTER, T, C, PPX>;
-    __shared__ typename W::WRow table[4][kBatchMaxStrip];
-    __shared__ uint32_t s_tile;
-    BatchHeader *hdr = reinterpret_cast<BatchHeader *>(ws);
-    const BatchJob *jobs = reinterpret_cast<const BatchJob *>(ws + kBatchHeaderBytes);
-    const int64_t total = hdr->tiles[kind];
-    const int32_t j_lo = hdr->job_lo[kind], j_hi = hdr->job_hi[kind];
-    const int32_t tid = static_cast<int32_t>(threadIdx.y * blockDim.x + threadIdx.x);
-    for (;;) {
-        if (tid == 0)
-            s_tile = atomicAdd(&hdr->ticket[kind], 1u);
-        __syncthreads();
-        const int64_t tile = static_cast<int64_t>(__builtin_amdgcn_readfirstlane(s_tile));
-        __syncthreads();
-        if (tile >= total)
-            break;
-        int32_t lo = j_lo, hi = j_hi - 1;  // last job of the kind whose tile_begin <= tile
-        while (lo < hi) {
-            const int32_t mid = (lo + hi + 1) >> 1;
-            if (jobs[mid].tile_begin <= tile)
-                lo = mid;
-            else
-                hi = mid - 1;
-        }
-        const BatchJob &job = jobs[lo];
-        const ResizeArgs a = job.a;
-        const int64_t local = tile - job.tile_begin;
-        const int64_t per_plane = static_cast<int64_t>(job.tiles_x) * job.tiles_y;
-        const int32_t plane = static_cast<int32_t>(local / per_plane);
-        const int32_t rem = static_cast<int32_t>(local - plane * per_plane);
-        const int32_t ty = rem / job.tiles_x;
-        const int32_t tx = rem - ty * job.tiles_x;
-        const int32_t col0 = (tx * static_cast<int32_t>(blockDim.x) + static_cast<int32_t>(threadIdx.x)) * PPX;
-        const int32_t strip_h = job.strip_h;
-        const int32_t r_begin =
-            __builtin_amdgcn_readfirstlane((ty * static_cast<int32_t>(blockDim.y) + threadIdx.y) * strip_h);
-        const int32_t wave_col0 = __builtin_amdgcn_readfirstlane(col0);
-        if (wave_col0 < a.out_w && r_begin < a.dst_rows) {
-            W w;
-            w.run(a, plane, col0, r_begin, min(r_begin + strip_h, a.dst_rows), table[tid >> 6], tid);
-        }
-    }
-    if (tid == 0) {
-        __threadfence();
-        if (atomicAdd(&hdr->done[kind], 1u) == gridDim.x - 1) {
-            atomicExch(&hdr->ticket[kind], 0u);
-            atomicExch(&hdr->done[kind], 0u);
-        }
-    }
-}
-
-// Jobs whose source is narrower than the filter's taps or whose output is
-// narrower than the walk's run (any filter and channel count): the per-tap
-// strip walk, one column per thread.
+// Jobs whose output is narrower than the staged walk's run or whose staged
+// rows are too long for it (any filter and channel count): the per-tap strip
+// walk, one column per thread, a workgroup per tile.
 template <typename T>
-__global__ void __launch_bounds__(256) k_batch_narrow(unsigned char *ws)
+__global__ void __launch_bounds__(256) k_batch_narrow(const unsigned char *__restrict__ ws)
 {
-    constexpr int32_t kind = kBatchNarrow;
-    __shared__ uint32_t s_tile;
-    BatchHeader *hdr = reinterpret_cast<BatchHeader *>(ws);
-    const BatchJob *jobs = reinterpret_cast<const BatchJob *>(ws + kBatchHeaderBytes);
-    const int64_t total = hdr->tiles[kind];
-    const int32_t j_lo = hdr->job_lo[kind], j_hi = hdr->job_hi[kind];
-    const int32_t tid = static_cast<int32_t>(threadIdx.y * blockDim.x + threadIdx.x);
-    for (;;) {
-        if (tid == 0)
-            s_tile = atomicAdd(&hdr->ticket[kind], 1u);
-        __syncthreads();
-        const int64_t tile = static_cast<int64_t>(__builtin_amdgcn_readfirstlane(s_tile));
-        __syncthreads();
-        if (tile >= total)
-            break;
-        int32_t lo = j_lo, hi = j_hi - 1;
-        while (lo < hi) {
-            const int32_t mid = (lo + hi + 1) >> 1;
-            if (jobs[mid].tile_begin <= tile)
-                lo = mid;
-            else
-                hi = mid - 1;
-        }
-        const BatchJob &job = jobs[lo];
-        const ResizeArgs a = job.a;
-        const int64_t local = tile - job.tile_begin;
-        const int64_t per_plane = static_cast<int64_t>(job.tiles_x) * job.tiles_y;
-        const int32_t plane = static_cast<int32_t>(local / per_plane);
-        const int32_t rem = static_cast<int32_t>(local - plane * per_plane);
-        const int32_t ty = rem / job.tiles_x;
-        const int32_t tx = rem - ty * job.tiles_x;
-        const int32_t col0 = tx * static_cast<int32_t>(blockDim.x) + static_cast<int32_t>(threadIdx.x);
-        const int32_t r_begin =
-            __builtin_amdgcn_readfirstlane((ty * static_cast<int32_t>(blockDim.y) + threadIdx.y) * job.strip_h);
-        if (col0 < a.out_w && r_begin < a.dst_rows) {
-            const int32_t r_end = min(r_begin + job.strip_h, a.dst_rows);
-            switch (job.kind_fc) {
-            case 0: {
-                StripBody<kBilinear, T, 1, 1> b;
-                b.run(a, plane, col0, r_begin, r_end);
-                break;
-            }
-            case 1: {
-                StripBody<kBilinear, T, 4, 1> b;
-                b.run(a, plane, col0, r_begin, r_end);
-                break;
-            }
-            case 2: {
-                StripBody<kBicubic, T, 1, 1> b;
-                b.run(a, plane, col0, r_begin, r_end);
-                break;
-            }
-            default: {
-                StripBody<kBicubic, T, 4, 1> b;
-                b.run(a, plane, col0, r_begin, r_end);
-                break;
-            }
-            }
-        }
+    int32_t plane, tx, ty;
+    BatchJob job;
+    if (!batch_tile(ws, kBatchNarrow, job, plane, tx, ty))
+        return;
+    const ResizeArgs &a = job.a;
+    const int32_t col0 = tx * static_cast<int32_t>(blockDim.x) + static_cast<int32_t>(threadIdx.x);
+    const int32_t r_begin =
+        __builtin_amdgcn_readfirstlane((ty * static_cast<int32_t>(blockDim.y) + threadIdx.y) * job.strip_h);
+    if (col0 >= a.out_w || r_begin >= a.dst_rows)
+        return;
+    const int32_t r_end = min(r_begin + job.strip_h, a.dst_rows);
+    switch (job.kind_fc) {
+    case 0: {
+        StripBody<kBilinear, T, 1, 1> b;
+        b.run(a, plane, col0, r_begin, r_end);
+        break;
     }
-    if (tid == 0) {
-        __threadfence();
-        if (atomicAdd(&hdr->done[kind], 1u) == gridDim.x - 1) {
-            atomicExch(&hdr->ticket[kind], 0u);
-            atomicExch(&hdr->done[kind], 0u);
-        }
+    case 1: {
+        StripBody<kBilinear, T, 4, 1> b;
+        b.run(a, plane, col0, r_begin, r_end);
+        break;
+    }
+    case 2: {
+        StripBody<kBicubic, T, 1, 1> b;
+        b.run(a, plane, col0, r_begin, r_end);
+        break;
+    }
+    default: {
+        StripBody<kBicubic, T, 4, 1> b;
+        b.run(a, plane, col0, r_begin, r_end);
+        break;
+    }
     }
 }
 
-namespace {
-// kind = 2 * bicubic + four channels; kBatchNarrow last
-template <typename T, int FILTER, int C>
-void launch_kind(unsigned char *p, dim3 block, const int32_t *grid, hipStream_t stream)
+hipError_t launch_batch_narrow(const void *ws, int32_t dtype, dim3 block, int32_t grid, hipStream_t stream)
 {
-    constexpr int kind = (FILTER == kBicubic ? 2 : 0) + (C == 4 ? 1 : 0);
-    if (grid[kind] > 0)
-        hipLaunchKernelGGL((k_batch_walk<FILTER, T, C>), dim3(grid[kind]), block, 0, stream, p, kind);
-}
-
-template <typename T, int FILTER, int C>
-int32_t kind_occupancy(int32_t threads)
-{
-    int n = 0;
-    const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_batch_walk<FILTER, T, C>, threads, 0);
-    return (e == hipSuccess && n > 0) ? n : 1;
-}
-
-template <typename T>
-hipError_t launch_batch_kinds(unsigned char *p, int32_t block_w, int32_t block_h, const int32_t *grid,
-                              hipStream_t stream)
-{
-    const dim3 block(block_w, block_h, 1);
-    launch_kind<T, kBilinear, 1>(p, block, grid, stream);
-    launch_kind<T, kBilinear, 4>(p, block, grid, stream);
-    launch_kind<T, kBicubic, 1>(p, block, grid, stream);
-    launch_kind<T, kBicubic, 4>(p, block, grid, stream);
-    if (grid[kBatchNarrow] > 0)
-        hipLaunchKernelGGL(k_batch_narrow<T>, dim3(grid[kBatchNarrow]), block, 0, stream, p);
+    const unsigned char *p = static_cast<const unsigned char *>(ws);
+    if (dtype == XR_U8)
+        hipLaunchKernelGGL(k_batch_narrow<uint8_t>, batch_grid(grid), block, 0, stream, p);
+    else if (dtype == XR_F16)
+        hipLaunchKernelGGL(k_batch_narrow<_Float16>, batch_grid(grid), block, 0, stream, p);
+    else
+        hipLaunchKernelGGL(k_batch_narrow<float>, batch_grid(grid), block, 0, stream, p);
     return hipGetLastError();
 }
 
-template <typename T>
-int32_t batch_kind_occupancy(int32_t kind, int32_t threads)
-{
-    switch (kind) {
-    case 0:
-        return kind_occupancy<T, kBilinear, 1>(threads);
-    case 1:
-        return kind_occupancy<T, kBilinear, 4>(threads);
-    case 2:
-        return kind_occupancy<T, kBicubic, 1>(threads);
-    case 3:
-        return kind_occupancy<T, kBicubic, 4>(threads);
-    default: {
-        int n = 0;
-        const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_batch_narrow<T>, threads, 0);
-        return (e == hipSuccess && n > 0) ? n : 1;
-    }
-    }
-}
-}  // namespace
-
-hipError_t launch_batched(const void *ws, int32_t dtype, int32_t block_w, int32_t block_h, const int32_t *grid,
-                          hipStream_t stream)
-{
-    unsigned char *p = const_cast<unsigned char *>(static_cast<const unsigned char *>(ws));
-    switch (dtype) {
-    case XR_U8:
-        return launch_batch_kinds<uint8_t>(p, block_w, block_h, grid, stream);
-    case XR_F16:
-        return launch_batch_kinds<_Float16>(p, block_w, block_h, grid, stream);
-    default:
-        return launch_batch_kinds<float>(p, block_w, block_h, grid, stream);
-    }
-}
-
-int32_t batched_blocks_per_cu(int32_t dtype, int32_t kind, int32_t threads)
-{
-    switch (dtype) {
-    case XR_U8:
-        return batch_kind_occupancy<uint8_t>(kind, threads);
-    case XR_F16:
-        return batch_kind_occupancy<_Float16>(kind, threads);
-    default:
-        return batch_kind_occupancy<float>(kind, threads);
-    }
-}
 // ---------------------------------------------------------------------------
 // dispatch
 // ---------------------------------------------------------------------------
@@ -1633,39 +920,6 @@ bool strip_ppx_supported(int32_t dtype, int32_t channels, int32_t ppx)
 }
 
 namespace {
-
-template <int FILTER, typename T, int C>
-hipError_t launch_lds(const ResizeArgs &a, const xr_tile &tile, hipStream_t stream)
-{
-    constexpr int PPX = kLdsPpx[C == 4 ? 1 : 0];
-    using Plan = LdsPlan<FILTER, T, C, PPX>;
-    const Plan plan(a.in_w, a.out_w, tile.block_w, a.aligned4 != 0);
-    if (!plan.ok)
-        return hipErrorInvalidValue;
-    const size_t lds = 3 * static_cast<size_t>(plan.buf_bytes);
-    const int32_t buf_bytes = static_cast<int32_t>(plan.buf_bytes);
-    const int32_t cols_per_block = tile.block_w * PPX;
-    const dim3 block(tile.block_w, 1, 1);
-    const dim3 grid((a.out_w + cols_per_block - 1) / cols_per_block,
-                    (a.dst_rows + tile.ppt_y - 1) / tile.ppt_y, a.planes);
-#define XR_LDS_CASE(N)                                                                        \
-    if (plan.need <= N) {                                                                     \
-        hipLaunchKernelGGL((k_strip_lds<FILTER, T, C, PPX, N>), grid, block, lds, stream, a,  \
-                           tile.ppt_y, tile.order, buf_bytes);                                \
-        return hipGetLastError();                                                             \
-    }
-    XR_LDS_CASE(1)
-    XR_LDS_CASE(2)
-    XR_LDS_CASE(4)
-    if constexpr (Plan::MAX_CH >= 8) {
-        XR_LDS_CASE(8)
-    }
-    if constexpr (Plan::MAX_CH >= 16) {
-        XR_LDS_CASE(16)
-    }
-#undef XR_LDS_CASE
-    return hipErrorInvalidValue;
-}
 
 // The x2 walk needs whole-dword runs: (PPX/2) pixels of a thread a multiple
 // of 4 bytes (one-byte pixels: PPX 8 or 16).
@@ -1725,8 +979,6 @@ hipError_t launch_x05(const ResizeArgs &a, const xr_tile &tile, hipStream_t stre
 template <int FILTER, typename T, int C>
 hipError_t launch_typed(const ResizeArgs &a, const xr_tile &tile, int32_t mode, hipStream_t stream)
 {
-    if (tile.kernel == XR_KERNEL_STRIP_LDS)
-        return launch_lds<FILTER, T, C>(a, tile, stream);
     if (tile.kernel == XR_KERNEL_GATHER) {
         const dim3 block(tile.block_w, tile.block_h, 1);
         const dim3 grid((a.out_w + tile.block_w - 1) / tile.block_w,
@@ -1750,6 +1002,14 @@ hipError_t launch_typed(const ResizeArgs &a, const xr_tile &tile, int32_t mode, 
                 if constexpr ((2 * P * Pix<T, C>::kBytes) % 4 == 0 && P * Pix<T, C>::kBytes <= 64) \
                     return launch_x05<FILTER, T, C, P>(a, tile, stream);                        \
             }                                                                                   \
+        }                                                                                       \
+        if (tile.kernel != XR_KERNEL_STRIP_ANY) {                                               \
+            bool taken = false;                                                                 \
+            const hipError_t e = launch_walk(a, FILTER == kBicubic ? XR_BICUBIC                 \
+                                                : FILTER == kNearest ? XR_NEAREST : XR_BILINEAR, \
+                                             DType<T>::kCode, C, tile, stream, taken);          \
+            if (taken)                                                                          \
+                return e;                                                                       \
         }                                                                                       \
         hipLaunchKernelGGL((k_strip<FILTER, T, C, P>), grid, block, 0, stream, a, tile.ppt_y,   \
                            tile.order);                                                         \

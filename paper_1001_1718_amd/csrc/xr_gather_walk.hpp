@@ -114,65 +114,6 @@ inline bool gather_shape(GatherShape &g, int32_t slots, int32_t kx, int32_t win_
     return g.lds_bytes <= most;
 }
 
-// Bytes as float32 operands without a conversion: byte j of a dword, masked
-// in place, is the bit pattern of the number (byte 2^(8j)) 2^-149 (j < 3; the
-// exponent field holds at most 1), the last one after a shift as j = 0. With
-// the weight scaled by 2^(126 - 8j) the product is the byte's, times 2^-23,
-// and every sum of such products rounds as the unscaled one does (nothing
-// here is small enough to lose bits); the row weights carry the 2^23. On
-// gfx950 the mask takes a 2-cycle issue slot, v_cvt_f32_ubyte a 4-cycle one
-// (measured), and a multiply-add takes 2 with either operand.
-
-// Samples of one staged row that belong to a lane's column: N samples of T, C
-// from LDS, then sample t as C operands and their weights.
-template <typename T, int C, int N>
-struct SampleRun {
-    static constexpr int PB = dev::Pix<T, C>::kBytes;
-    static constexpr bool kBytes = std::is_same_v<T, uint8_t>;
-    unsigned char b[(N * PB + 3) / 4 * 4];
-
-    __device__ __forceinline__ void load(const unsigned char *win, uint32_t at)
-    {
-        dev::lds_run<N * PB, PB>(b, win, at);
-    }
-    __device__ __forceinline__ void terms(int t, float (&v)[C]) const
-    {
-        if constexpr (kBytes && C == 4) {
-            uint32_t d;
-            __builtin_memcpy(&d, b + 4 * t, 4);
-            v[0] = __builtin_bit_cast(float, d & 0xffu);
-            v[1] = __builtin_bit_cast(float, d & 0xff00u);
-            v[2] = __builtin_bit_cast(float, d & 0xff0000u);
-            v[3] = __builtin_bit_cast(float, d >> 24);
-        } else if constexpr (kBytes) {
-            uint32_t d;
-            __builtin_memcpy(&d, b + t / 4 * 4, 4);
-            v[0] = __builtin_bit_cast(float, t % 4 == 3 ? d >> 24 : d & (0xffu << (8 * (t % 4))));
-        } else {
-            dev::Pix<T, C>::load(b, t, v);
-        }
-    }
-};
-
-// Weight of sample t (held as scale<T, C>(t) times the weight) for channel ch.
-template <typename T, int C>
-__device__ __forceinline__ float sample_scale(int t)
-{
-    if (!std::is_same_v<T, uint8_t>)
-        return 1.0f;
-    return C == 4 ? 0x1p110f : t % 4 == 1 ? 0x1p118f : t % 4 == 2 ? 0x1p110f : 0x1p126f;
-}
-template <typename T, int C>
-__device__ __forceinline__ void sample_weights(float w, float (&wt)[C])
-{
-#pragma unroll
-    for (int ch = 0; ch < C; ++ch)
-        wt[ch] = !(std::is_same_v<T, uint8_t> && C == 4) ? w
-                 : ch == 1                                ? w * 0x1p8f
-                 : ch == 2                                ? w
-                                                          : w * 0x1p16f;
-}
-
 // BIG: more than kGatherRegTaps samples per column; the column weights then
 // come from an LDS table of the workgroup instead of registers.
 template <class P, typename T, int C, bool BIG>

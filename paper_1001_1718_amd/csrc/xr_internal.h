@@ -44,8 +44,8 @@ struct BatchJob {
 };
 
 // Launches of the batched resize, one per job kind: kinds 0-3 are
-// 2 * (bicubic) + (four channels); kind 4 holds the jobs with a source
-// narrower than the filter's taps or an output narrower than the walk's run.
+// 2 * (bicubic) + (four channels); kind 4 holds the jobs whose output is
+// narrower than the staged walk's run or whose staged rows are too long.
 constexpr int32_t kBatchKinds = 5;
 constexpr int32_t kBatchNarrow = 4;
 
@@ -60,33 +60,31 @@ struct BatchHeader {
     int32_t pad_;
     int32_t job_lo[kBatchKinds];    // jobs [job_lo, job_hi) are of kind k
     int32_t job_hi[kBatchKinds];
-    int64_t tiles[kBatchKinds];     // tiles of kind k
-    int32_t grid[kBatchKinds];      // workgroups of kind k's launch (0: no launch)
-    uint32_t ticket[kBatchKinds];   // next tile to hand out (self-resetting)
-    uint32_t done[kBatchKinds];     // workgroups that have finished (self-resetting)
+    int64_t tiles[kBatchKinds];     // tiles of kind k, a workgroup each
+    int32_t table_bytes[kBatchKinds];  // LDS of a wavefront of kind k: row weights
+    int32_t win_bytes[kBatchKinds];    // and staged rows
 };
 constexpr size_t kBatchHeaderBytes = 256;
 static_assert(sizeof(BatchHeader) <= kBatchHeaderBytes, "batch header");
 
-// Longest thread strip of the batched walk (rows of its per-wavefront weight
-// table in LDS).
+// Longest thread strip of the batched walk.
 constexpr int32_t kBatchMaxStrip = 256;
 
-// Row weights of one output row in that table.
-template <int K>
-struct alignas(K * 4) BatchWeights {
-    float w[K];
-};
-
-// Output columns per thread of the batched walk, per filter, storage type and
-// channel count: 16-byte runs for bilinear, 8 to 16 for bicubic (whose four
-// tap rows per column would leave fewer waves with 16-byte uint8 runs); the
-// narrow kind takes one column.
+// Output columns per thread of the staged walk, by channels and bytes per
+// pixel: runs of 4 to 16 bytes, as many columns as the ring of filtered rows
+// leaves registers for.
+constexpr int32_t walk_ppx(int32_t channels, int32_t pixel_bytes)
+{
+    return channels == 1 ? 4 : pixel_bytes == 16 ? 1 : 2;
+}
+// In a batch, whose launches hold many tiles at a time, twice as many where a
+// run stays within 16 bytes and registers allow (256 uneven uint8 images: 8
+// columns of one channel and 4 bilinear RGBA ones 1.22 ms, 4 and 2: 1.34 ms).
 constexpr int32_t batch_ppx(int32_t filter, int32_t dtype, int32_t channels)
 {
-    return dtype == XR_U8 ? (channels == 1 ? (filter == XR_BILINEAR ? 16 : 8) : (filter == XR_BILINEAR ? 4 : 2))
-         : dtype == XR_F16 ? (channels == 1 ? 8 : 2)
-                           : (channels == 1 ? 4 : 1);
+    if (dtype == XR_U8)
+        return channels == 1 ? 8 : filter == XR_BILINEAR ? 4 : 2;
+    return walk_ppx(channels, channels * (dtype == XR_F16 ? 2 : 4));
 }
 
 // Shape of an axis that a kernel can specialise on.
@@ -99,11 +97,39 @@ hipError_t launch_antialiased(const ResizeArgs &a, int32_t filter, int32_t dtype
 // True when that launch of an LDS tile takes the gather walk, which needs no
 // block of its own to fit.
 bool antialiased_walk_supported(const ResizeArgs &a, int32_t filter, int32_t dtype, int32_t channels);
+// The staged walk at any ratio (xr_walk.hip); `taken` stays false where it
+// does not apply (staged rows too long for LDS, outputs narrower than a run,
+// runs it is not built for, pitches past 4 MiB).
+hipError_t launch_walk(const ResizeArgs &a, int32_t filter, int32_t dtype, int32_t channels, const xr_tile &tile,
+                       hipStream_t stream, bool &taken);
+// True when the walk with its own columns per thread (walk_ppx) can stage its
+// rows for an in_w -> out_w resize.
+bool walk_fits(int32_t filter, int32_t dtype, int32_t channels, int32_t in_w, int32_t out_w);
+
+// Launches of a prepared batch: workgroups and LDS bytes per kind.
+struct BatchLaunch {
+    int32_t block_w, block_h;
+    int32_t grid[kBatchKinds];
+    size_t lds[kBatchKinds];
+};
+// The grid of `tiles` workgroups, in rows of at most 2^22 (a launch holds
+// fewer than 2^32 threads along x).
+inline dim3 batch_grid(int32_t tiles)
+{
+    const int32_t row = std::min<int32_t>(tiles, 1 << 22);
+    return dim3(static_cast<uint32_t>(row), static_cast<uint32_t>((tiles + static_cast<int64_t>(row) - 1) / row));
+}
+// LDS of a wavefront that walks a job in strips of `strip` rows; ok = false
+// where the staged walk does not apply.
+struct BatchWalkNeed {
+    int32_t table_bytes, win_bytes;
+    bool ok;
+};
+BatchWalkNeed batch_walk_need(const ResizeArgs &a, int32_t filter, int32_t dtype, int32_t channels, int32_t strip);
+int32_t batch_walk_wave_bytes(int32_t table_bytes, int32_t win_bytes);
 // The batched launches of a prepared workspace: one per kind with grid[kind] > 0.
-hipError_t launch_batched(const void *ws, int32_t dtype, int32_t block_w, int32_t block_h, const int32_t *grid,
-                          hipStream_t stream);
-// Workgroups of the batched walk of `kind` that fit on one compute unit.
-int32_t batched_blocks_per_cu(int32_t dtype, int32_t kind, int32_t threads);
+hipError_t launch_batched(const void *ws, int32_t dtype, const BatchLaunch &l, hipStream_t stream);
+hipError_t launch_batch_narrow(const void *ws, int32_t dtype, dim3 block, int32_t grid, hipStream_t stream);
 hipError_t launch_backward(const ResizeArgs &a, int32_t filter, int32_t dtype, int32_t channels,
                            hipStream_t stream);
 // False when the adjoint's smallest LDS tile cannot hold the output rows of

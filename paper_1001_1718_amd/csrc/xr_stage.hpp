@@ -13,6 +13,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "xr_device.hpp"
 
 namespace xr {
@@ -82,6 +84,30 @@ struct RowStage {
         }
     }
 
+    // The same for the rows row_of(i), i < n.
+    template <class RowOf>
+    __device__ __forceinline__ void request_rows(unsigned char *area, int32_t n, int32_t lane, RowOf row_of) const
+    {
+        const int32_t total = n * nch;
+        const int32_t dr = 64 / nch, dc = 64 - dr * nch;
+        int32_t r = lane / nch, c = lane - r * nch;
+        for (int32_t g = 0; g < total; g += 64) {
+            if (g + lane < total) {
+                const uint32_t o = m0 + static_cast<uint32_t>(row_of(r)) * pitch;
+                const int32_t j = min(max(c - front, 0),
+                                      static_cast<int32_t>(((o & 15u) + static_cast<uint32_t>(bytes) - 1u) >> 4));
+                __builtin_amdgcn_global_load_lds((gptr_t)(base + ((o & ~15u) + 16u * static_cast<uint32_t>(j))),
+                                                 (lptr_t)(area + 16 * g), 16, 0, 0);
+            }
+            c += dc;
+            r += dr;
+            if (c >= nch) {
+                c -= nch;
+                ++r;
+            }
+        }
+    }
+
     // every load and store of this wavefront has completed
     __device__ __forceinline__ static void wait()
     {
@@ -120,6 +146,65 @@ __device__ __forceinline__ void lds_run(unsigned char *dst, const unsigned char 
             __builtin_memcpy(dst + 4 * j, &x, 4);
         }
     }
+}
+
+// Bytes as float32 operands without a conversion: byte j of a dword, masked
+// in place, is the bit pattern of the number (byte 2^(8j)) 2^-149 (j < 3; the
+// exponent field holds at most 1), the last one after a shift as j = 0. With
+// the weight scaled by 2^(126 - 8j) the product is the byte's, times 2^-23,
+// and every sum of such products rounds as the unscaled one does (nothing
+// here is small enough to lose bits); the row weights carry the 2^23. On
+// gfx950 the mask takes a 2-cycle issue slot, v_cvt_f32_ubyte a 4-cycle one
+// (measured), and a multiply-add takes 2 with either operand.
+
+// Samples of one staged row that belong to a lane's column: N samples of T, C
+// from LDS, then sample t as C operands and their weights.
+template <typename T, int C, int N>
+struct SampleRun {
+    static constexpr int PB = Pix<T, C>::kBytes;
+    static constexpr bool kBytes = std::is_same_v<T, uint8_t>;
+    unsigned char b[(N * PB + 3) / 4 * 4];
+
+    __device__ __forceinline__ void load(const unsigned char *win, uint32_t at)
+    {
+        lds_run<N * PB, PB>(b, win, at);
+    }
+    __device__ __forceinline__ void terms(int t, float (&v)[C]) const
+    {
+        if constexpr (kBytes && C == 4) {
+            uint32_t d;
+            __builtin_memcpy(&d, b + 4 * t, 4);
+            v[0] = __builtin_bit_cast(float, d & 0xffu);
+            v[1] = __builtin_bit_cast(float, d & 0xff00u);
+            v[2] = __builtin_bit_cast(float, d & 0xff0000u);
+            v[3] = __builtin_bit_cast(float, d >> 24);
+        } else if constexpr (kBytes) {
+            uint32_t d;
+            __builtin_memcpy(&d, b + t / 4 * 4, 4);
+            v[0] = __builtin_bit_cast(float, t % 4 == 3 ? d >> 24 : d & (0xffu << (8 * (t % 4))));
+        } else {
+            Pix<T, C>::load(b, t, v);
+        }
+    }
+};
+
+// Weight of sample t (held as scale<T, C>(t) times the weight) for channel ch.
+template <typename T, int C>
+__device__ __forceinline__ float sample_scale(int t)
+{
+    if (!std::is_same_v<T, uint8_t>)
+        return 1.0f;
+    return C == 4 ? 0x1p110f : t % 4 == 1 ? 0x1p118f : t % 4 == 2 ? 0x1p110f : 0x1p126f;
+}
+template <typename T, int C>
+__device__ __forceinline__ void sample_weights(float w, float (&wt)[C])
+{
+#pragma unroll
+    for (int ch = 0; ch < C; ++ch)
+        wt[ch] = !(std::is_same_v<T, uint8_t> && C == 4) ? w
+                 : ch == 1                                ? w * 0x1p8f
+                 : ch == 2                                ? w
+                                                          : w * 0x1p16f;
 }
 
 }  // namespace dev
