@@ -806,6 +806,17 @@ int build_batch(const xr_job *jobs, int32_t n_jobs, const xr_tile *tile, unsigne
 
     if (!named && !tuned)
         t = batch_default_tile(jobs, n_jobs, dtype);
+    // fewer wavefronts a workgroup where those of the tile pass the LDS limit
+    // (a launch takes the largest table and the largest window of its jobs)
+    for (int32_t k = 0; k < n_jobs; ++k) {
+        const xr_job &j = jobs[k];
+        const xr::BatchWalkNeed n = xr::batch_walk_need(make_args(j.src, j.dst), j.filter, dtype, j.src.channels, t.ppt_y);
+        const int32_t wave = xr::batch_walk_wave_bytes(n.table_bytes, n.win_bytes);
+        while (n.ok && t.block_w / 64 * t.block_h * static_cast<int64_t>(wave) > xr::kStageMaxLds) {
+            int32_t &side = t.block_h > 1 ? t.block_h : t.block_w;
+            side = t.block_h > 1 ? side / 2 : side / 128 * 64;
+        }
+    }
     // grouped by kind, largest output first within a kind
     const auto fc_of = [&](const xr_job &j) {
         return (j.filter == XR_BICUBIC ? 2 : 0) + (j.src.channels == 4 ? 1 : 0);

@@ -129,6 +129,9 @@ BatchWalkNeed batch_walk_need(const ResizeArgs &a, int32_t filter, int32_t dtype
 int32_t batch_walk_wave_bytes(int32_t table_bytes, int32_t win_bytes);
 // The batched launches of a prepared workspace: one per kind with grid[kind] > 0.
 hipError_t launch_batched(const void *ws, int32_t dtype, const BatchLaunch &l, hipStream_t stream);
+// Direct-to-LDS loads take the place of their data from the low 16 bits of M0:
+// workgroups that stage rows stay within 64 KiB of LDS.
+constexpr int64_t kStageMaxLds = 64 * 1024;
 hipError_t launch_batch_narrow(const void *ws, int32_t dtype, dim3 block, int32_t grid, hipStream_t stream);
 hipError_t launch_backward(const ResizeArgs &a, int32_t filter, int32_t dtype, int32_t channels,
                            hipStream_t stream);

@@ -447,19 +447,27 @@ hipError_t launch_walk_ppx(const ResizeArgs &a, const xr_tile &tile, hipStream_t
     const int64_t pitch = std::max(a.src_pitch, a.dst_pitch);
     while (strip > 1 && std::max(src_rows(strip), strip) * pitch >= (int64_t(1) << 30))
         strip /= 2;
-    const int32_t waves = tile.block_w / 64 * tile.block_h;
     const int32_t table = walk_table(K, static_cast<int32_t>(strip));
     const int32_t win = walk_window(row_bytes);
-    const int64_t lds = static_cast<int64_t>(waves) * (table + win + kWalkSlack);
-    const int64_t rows_per_block = strip * tile.block_h;
+    if (pitch > kStageMaxPitch || 4 * row_bytes > kWalkMaxWindow || a.out_w < PPX)
+        return hipSuccess;
+    // fewer wavefronts a workgroup where those of the tile pass the LDS limit
+    // (one fits always: 17 KiB and a table of 5)
+    int32_t block_w = tile.block_w, block_h = tile.block_h;
+    const auto lds = [&] { return static_cast<int64_t>(block_w / 64 * block_h) * (table + win + kWalkSlack); };
+    while (lds() > kStageMaxLds) {
+        int32_t &side = block_h > 1 ? block_h : block_w;
+        side = block_h > 1 ? side / 2 : side / 128 * 64;
+    }
+    const int64_t rows_per_block = strip * block_h;
     const int64_t gy = (a.dst_rows + rows_per_block - 1) / rows_per_block;
-    if (pitch > kStageMaxPitch || 4 * row_bytes > kWalkMaxWindow || lds > 96 * 1024 || a.out_w < PPX || gy > 65535)
+    if (gy > 65535)
         return hipSuccess;
     taken = true;
-    const int32_t cols_per_block = tile.block_w * PPX;
+    const int32_t cols_per_block = block_w * PPX;
     hipLaunchKernelGGL((k_walk<FILTER, T, C, PPX>),
                        dim3((a.out_w + cols_per_block - 1) / cols_per_block, static_cast<uint32_t>(gy), a.planes),
-                       dim3(tile.block_w, tile.block_h), static_cast<size_t>(lds), stream, a,
+                       dim3(block_w, block_h), static_cast<size_t>(lds()), stream, a,
                        static_cast<int32_t>(strip), tile.order, table, win);
     return hipGetLastError();
 }

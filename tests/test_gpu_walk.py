@@ -73,3 +73,21 @@ def test_batch_equals_gather(dtype):
             ref = torch.empty_like(d)
             xr.resize_into(x, ref, mode, tile=GATHER)
             assert _same(d, ref), (tuple(x.shape), tuple(d.shape), mode, t)
+
+
+def test_walk_near_the_lds_limit():
+    # float32 RGBA rows of just under and over 4 KiB per wavefront: workgroups
+    # of the default tile then hold fewer wavefronts, or the walk does not apply
+    for iw, ow in [(720, 184), (735, 184), (1500, 380), (1600, 400), (1700, 400)]:
+        x = _data((41, iw, 4), torch.float32, iw)
+        ref, out = (torch.empty((300, ow, 4), dtype=torch.float32, device=DEV) for _ in range(2))
+        for mode in ("bilinear", "bicubic"):
+            xr.resize_into(x, ref, mode, tile=GATHER)
+            for t in (None, xr.tile(xr.XR_KERNEL_STRIP, 64, 4, 1, 256), xr.tile(xr.XR_KERNEL_STRIP, 256, 1, 1, 9)):
+                out.zero_()
+                xr.resize_into(x, out, mode, tile=t)
+                assert _same(out, ref), (iw, ow, mode, t)
+            for t in (None, xr.tile(xr.XR_KERNEL_STRIP, 64, 4, 0, 256)):
+                out.zero_()
+                xr.Batch([(x, out, mode)], tile=t).run()
+                assert _same(out, ref), (iw, ow, mode, t)
