@@ -253,6 +253,7 @@ template <int R>
 struct AaWalk {
     static constexpr int kSlots = 2 * R;  // |i - s_y| < R sigma, the s_y sigma apart
     static constexpr bool kFirstMul = true;
+    static constexpr bool kRowRegs = true;
     __device__ __forceinline__ static int32_t result_w(const ResizeArgs &a) { return a.out_w; }
     __device__ __forceinline__ static int32_t result_rows(const ResizeArgs &a) { return a.dst_rows; }
     __device__ __forceinline__ static int32_t walked_w(const ResizeArgs &a) { return a.in_w; }
@@ -280,6 +281,12 @@ struct AaWalk {
     {
         aa_weights<R, N>(x, a.in_w, a.out_w, lo, n, w);
     }
+    template <int N>
+    __device__ __forceinline__ static void weights_y(const ResizeArgs &a, int32_t y, int32_t lo, int32_t n,
+                                                     float (&w)[N])
+    {
+        aa_weights<R, N>(a.dst_row0 + y, a.in_h, a.out_h, lo, n, w);
+    }
     template <class W>
     __device__ __forceinline__ static void weights_y(const ResizeArgs &a, int32_t y, int32_t lo, int32_t n, W w)
     {
@@ -297,12 +304,17 @@ bool aa_walk_shape(const ResizeArgs &a, GatherShape &g)
 {
     if (a.in_h < a.out_h || a.src_pitch > kStageMaxPitch)
         return false;
-    const AaPlan p = aa_tile_plan(a.in_w, a.in_h, a.out_w, a.out_h, R, kGatherCols, 1, Pix<T, C>::kBytes, C);
+    const AaPlan p = aa_tile_plan(a.in_w, a.in_h, a.out_w, a.out_h, R, gather_cols(C), 1, Pix<T, C>::kBytes, C);
     const auto cap = [&](int64_t strip) {
         return std::min<int64_t>(((strip - 1) * a.in_h + 2 * R * static_cast<int64_t>(a.in_h)) / a.out_h + 2, a.in_h);
     };
-    const int64_t strip = gather_strip(a.out_w, a.dst_rows, a.planes, a.src_pitch, cap);
-    return strip > 0 && gather_shape(g, AaWalk<R>::kSlots, p.kx, p.win_w, Pix<T, C>::kBytes, strip, cap);
+    // a row of the table form costs as much for a few columns as for a
+    // wavefront's (1024 bilinear planes 274 x 144 -> 27 x 14: 232 us so, 182 in
+    // tiles; 512 bicubic planes 300 x 90 -> 60 x 30: 69 and 105)
+    if (p.kx > kGatherRegTaps && a.out_w < 24)
+        return false;
+    const int64_t strip = gather_strip(C, a.out_w, a.dst_rows, a.planes, a.src_pitch, cap);
+    return strip > 0 && gather_shape(g, C, AaWalk<R>::kSlots, p.kx, p.win_w, Pix<T, C>::kBytes, strip, cap);
 }
 
 template <int R, typename T, int C>

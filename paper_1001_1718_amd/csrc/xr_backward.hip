@@ -226,6 +226,7 @@ struct AdjointWalk {
     static constexpr int K = TP::K;
     static constexpr int kSlots = K;
     static constexpr bool kFirstMul = false;
+    static constexpr bool kRowRegs = false;
     __device__ __forceinline__ static int32_t result_w(const ResizeArgs &a) { return a.in_w; }
     __device__ __forceinline__ static int32_t result_rows(const ResizeArgs &a) { return a.in_h; }
     __device__ __forceinline__ static int32_t walked_w(const ResizeArgs &a) { return a.out_w; }
@@ -726,8 +727,8 @@ bool bwd_walk_shape(const ResizeArgs &a, const BwdPlan &p, GatherShape &g)
         return std::min<int64_t>(((n + K - 1) * n_out + n_in - 1) / n_in + 2, n_out);
     };
     const auto cap = [&](int64_t strip) { return reach(strip, a.in_h, a.out_h); };
-    const int64_t strip = gather_strip(a.in_w, a.in_h, a.planes, a.src_pitch, cap);
-    return strip > 0 && gather_shape(g, K, p.nmax, static_cast<int32_t>(reach(kGatherCols, a.in_w, a.out_w)),
+    const int64_t strip = gather_strip(C, a.in_w, a.in_h, a.planes, a.src_pitch, cap);
+    return strip > 0 && gather_shape(g, C, K, p.nmax, static_cast<int32_t>(reach(gather_cols(C), a.in_w, a.out_w)),
                                      static_cast<int32_t>(sizeof(T)) * C, strip, cap);
 }
 

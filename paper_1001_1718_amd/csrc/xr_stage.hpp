@@ -61,25 +61,27 @@ struct RowStage {
     // granules). All earlier reads of the area must have returned.
     __device__ __forceinline__ void request(unsigned char *area, int32_t first, int32_t n, int32_t lane) const
     {
+        if (pitch % 16 != 0 || front > 0) {  // (rows with free granules have them at both ends)
+            request_rows(area, n, lane, [&](int32_t i) { return first + i; });
+            return;
+        }
+        // rows start at one place of a granule and every granule holds window
+        // bytes: a lane's next granule is one constant step on, or two
         const int32_t total = n * nch;
         const int32_t dr = 64 / nch, dc = 64 - dr * nch;
         const int32_t r = lane / nch;
         int32_t c = lane - r * nch;
-        uint32_t o = m0 + static_cast<uint32_t>(first + r) * pitch;  // offset of the lane's row
-        const bool even = pitch % 16 == 0;                           // every granule holds window bytes
+        uint32_t o = static_cast<uint32_t>(first + r) * pitch + 16u * static_cast<uint32_t>(c);
+        const uint32_t step = static_cast<uint32_t>(dr) * pitch + 16u * static_cast<uint32_t>(dc);
+        const uint32_t wrap = pitch - 16u * static_cast<uint32_t>(nch);
         for (int32_t g = 0; g < total; g += 64) {
-            if (g + lane < total) {
-                int32_t j = c - front;
-                if (!even || front > 0)
-                    j = min(max(j, 0), static_cast<int32_t>(((o & 15u) + static_cast<uint32_t>(bytes) - 1u) >> 4));
-                __builtin_amdgcn_global_load_lds((gptr_t)(base + ((o & ~15u) + 16u * static_cast<uint32_t>(j))),
-                                                 (lptr_t)(area + 16 * g), 16, 0, 0);
-            }
+            if (g + lane < total)
+                __builtin_amdgcn_global_load_lds((gptr_t)(base + o), (lptr_t)(area + 16 * g), 16, 0, 0);
             c += dc;
-            o += static_cast<uint32_t>(dr) * pitch;
+            o += step;
             if (c >= nch) {
                 c -= nch;
-                o += pitch;
+                o += wrap;
             }
         }
     }
