@@ -508,14 +508,25 @@ int check_aa(const xr_tile &t, int32_t filter, const xr_image &src, const xr_ima
 }
 
 // Default antialiased tile: the LDS kernel where its walk applies or with the
-// first block whose window fits, else the gather.
+// first block whose window fits, else the gather. Blocks of 64 x 4 past half a
+// compute unit's LDS share it with no other, so where there are more of them
+// than compute units 16 x 8 ones, of half the window and the row overlap of
+// eight rows, are faster: 96 bilinear float32 planes 135 x 384 -> 16 x 46 (82
+// KiB, 384 blocks) 39.9 and 25.9 us, bicubic RGBA float32 588 x 2316 ->
+// 210 x 827 (87 KiB, 689) 29.2 and 24.9; with 68 blocks of 85 KiB 37.8 and
+// 37.5, with 10 of 89 KiB 17.9 and 21.5. So are they where 64 x 4 does not fit:
+// bicubic 2178 x 1046 -> 337 x 162 float32 32.1 us, 40.6 at 64 x 2; uint8 RGBA
+// 368 x 3192 -> 58 x 507 31.4 and 39.6.
 xr_tile aa_default_tile(int32_t filter, const xr_image &src, const xr_image &dst)
 {
     if (xr::antialiased_walk_supported(make_args(src, dst), filter, src.dtype, src.channels))
         return xr_tile{XR_KERNEL_STRIP_LDS, 64, 4, 1, 1, 0};
-    const int blocks[][2] = {{64, 4}, {64, 2}, {32, 2}, {16, 2}};
+    const int64_t groups = static_cast<int64_t>((dst.width + 63) / 64) * ((dst.rows + 3) / 4) * dst.planes;
+    const int blocks[][2] = {{64, 4}, {16, 8}, {64, 2}, {32, 2}, {16, 2}};
     for (const auto &b : blocks) {
         const xr_tile t{XR_KERNEL_STRIP_LDS, b[0], b[1], 1, 1, 0};
+        if (b[1] == 4 && groups > 256 && aa_lds_bytes(t, filter, src, dst) > 80 * 1024)
+            continue;
         if (aa_lds_bytes(t, filter, src, dst) <= xr::kAaLdsBudget)
             return t;
     }
