@@ -221,7 +221,7 @@ int xr_resize(const xr_image *src, const xr_image *dst, int32_t filter, int32_t 
  *   with an asynchronous copy on `stream`. The host copy of `jobs` may be
  *   reused once the call returns. NOT capturable (XR_ERR_CAPTURE).
  *   All jobs must share one dtype.
- * xr_resize_batched: one launch per job kind present, back to
+ * xr_resize_batched: one launch, or two with jobs of the fifth kind, back to
  *   back on `stream`, that together process every tile of every prepared
  *   job. Capturable and replayable; it allocates nothing. The workspace must
  *   not be used by two launches at the same time.

@@ -652,6 +652,52 @@ xr_tile batch_default_tile(const xr_job *jobs, int32_t n_jobs, int32_t dtype)
     return t;
 }
 
+// LDS of a batch's workgroups: what all wavefronts of the jobs need that hold
+// nine tenths of the output pixels (so that a few jobs of long staged rows do
+// not take it from the others: those run fewer wavefronts a workgroup), at
+// least one wavefront of any job, at most kStageMaxLds; and at least a quarter
+// of a compute unit's, for longer windows at the four workgroups that
+// registers allow, or a third for float outputs past 1 GiB, which memory
+// bounds and where fewer rows in flight read it better. Measured with a
+// quarter and a third: 25 float16 and float32 batches of 5 .. 920 MB output
+// from 0.66 to 1.01 of the quarter's speed with the third, 9 of 1.1 .. 5.8 GB
+// 0.94 to 1.19 (float32 of 4.3 GB: 1236 and 1034 us); uint8, bound by
+// instructions, of any size less (256 images: 885 and 1136 us).
+int32_t batch_lds(const xr_job *jobs, int32_t n_jobs, int32_t dtype, const xr_tile &t)
+{
+    const int64_t waves = t.block_w / 64 * t.block_h;
+    int64_t px = 0, most = 0, out_bytes = 0;  // of jobs that walk
+    const auto visit = [&](auto f) {
+        for (int32_t k = 0; k < n_jobs; ++k) {
+            const xr_job &j = jobs[k];
+            const xr::BatchWalkNeed n =
+                xr::batch_walk_need(make_args(j.src, j.dst), j.filter, dtype, j.src.channels, t.ppt_y);
+            if (n.ok)
+                f(n, static_cast<int64_t>(j.dst.width) * j.dst.rows * j.dst.planes,
+                  j.dst.channels * (dtype == XR_U8 ? 1 : dtype == XR_F16 ? 2 : 4));
+        }
+    };
+    visit([&](const xr::BatchWalkNeed &n, int64_t p, int64_t px_bytes) {
+        px += p;
+        out_bytes += p * px_bytes;
+        most = std::max<int64_t>(most, n.wave_bytes);
+    });
+    int64_t wave = 0;
+    for (int64_t window = 8 * 1024; wave == 0 && px > 0; window += 2 * 1024) {
+        int64_t in = 0, need = 0;
+        visit([&](const xr::BatchWalkNeed &n, int64_t p, int64_t) {
+            if (n.win_bytes <= window) {
+                in += p;
+                need = std::max<int64_t>(need, n.wave_bytes);
+            }
+        });
+        if (in >= px - px / 10)
+            wave = need;
+    }
+    const int64_t least = dtype != XR_U8 && out_bytes > int64_t(1) << 30 ? 53 * 1024 : 40 * 1024;
+    return static_cast<int32_t>(std::max({most, least, std::min(waves * wave, xr::kStageMaxLds)}));
+}
+
 // The current device's architecture name and compute-unit count (the key of
 // persisted launch shapes).
 int device_identity(std::string &arch, int &cus)
@@ -817,17 +863,6 @@ int build_batch(const xr_job *jobs, int32_t n_jobs, const xr_tile *tile, unsigne
 
     if (!named && !tuned)
         t = batch_default_tile(jobs, n_jobs, dtype);
-    // fewer wavefronts a workgroup where those of the tile pass the LDS limit
-    // (a launch takes the largest table and the largest window of its jobs)
-    for (int32_t k = 0; k < n_jobs; ++k) {
-        const xr_job &j = jobs[k];
-        const xr::BatchWalkNeed n = xr::batch_walk_need(make_args(j.src, j.dst), j.filter, dtype, j.src.channels, t.ppt_y);
-        const int32_t wave = xr::batch_walk_wave_bytes(n.table_bytes, n.win_bytes);
-        while (n.ok && t.block_w / 64 * t.block_h * static_cast<int64_t>(wave) > xr::kStageMaxLds) {
-            int32_t &side = t.block_h > 1 ? t.block_h : t.block_w;
-            side = t.block_h > 1 ? side / 2 : side / 128 * 64;
-        }
-    }
     // grouped by kind, largest output first within a kind
     const auto fc_of = [&](const xr_job &j) {
         return (j.filter == XR_BICUBIC ? 2 : 0) + (j.src.channels == 4 ? 1 : 0);
@@ -848,6 +883,7 @@ int build_batch(const xr_job *jobs, int32_t n_jobs, const xr_tile *tile, unsigne
         const int64_t wq = static_cast<int64_t>(jobs[q].dst.width) * jobs[q].dst.rows * jobs[q].dst.planes;
         return wp != wq ? wp > wq : p < q;
     });
+    const int32_t lds_bytes = batch_lds(jobs, n_jobs, dtype, t);
     std::memset(host, 0, xr_batch_workspace_bytes(n_jobs));
     auto *hdr = reinterpret_cast<xr::BatchHeader *>(host);
     auto *tab = reinterpret_cast<xr::BatchJob *>(host + xr::kBatchHeaderBytes);
@@ -873,12 +909,15 @@ int build_batch(const xr_job *jobs, int32_t n_jobs, const xr_tile *tile, unsigne
         const int64_t max_rows = (int64_t(1) << 31) / j.src.row_pitch - 6;
         strip = std::min<int64_t>(strip, std::max<int64_t>(1, max_rows * j.dst.height / j.src.height));
         b.strip_h = static_cast<int32_t>(strip);
+        int32_t waves_w = t.block_w / 64, waves_h = t.block_h;
         const xr::BatchWalkNeed need = xr::batch_walk_need(b.a, j.filter, dtype, j.src.channels, b.strip_h);
-        hdr->table_bytes[kind] = std::max(hdr->table_bytes[kind], need.table_bytes);
-        hdr->win_bytes[kind] = std::max(hdr->win_bytes[kind], need.win_bytes);
+        while (kind != xr::kBatchNarrow && waves_w * waves_h * need.wave_bytes > lds_bytes)
+            (waves_h > 1 ? waves_h : waves_w) /= 2;
+        b.waves_w = static_cast<int16_t>(waves_w);
+        b.waves_h = static_cast<int16_t>(waves_h);
         const int64_t tile_w =
-            static_cast<int64_t>(t.block_w) * (kind == xr::kBatchNarrow ? 1 : xr::batch_ppx(j.filter, dtype, j.src.channels));
-        const int64_t tile_h = static_cast<int64_t>(t.block_h) * b.strip_h;
+            static_cast<int64_t>(waves_w) * 64 * (kind == xr::kBatchNarrow ? 1 : xr::batch_ppx(j.filter, dtype, j.src.channels));
+        const int64_t tile_h = static_cast<int64_t>(waves_h) * b.strip_h;
         b.tiles_x = static_cast<int32_t>((j.dst.width + tile_w - 1) / tile_w);
         b.tiles_y = static_cast<int32_t>((j.dst.rows + tile_h - 1) / tile_h);
         b.tile_begin = hdr->tiles[kind];
@@ -893,15 +932,10 @@ int build_batch(const xr_job *jobs, int32_t n_jobs, const xr_tile *tile, unsigne
     hdr->block_w = t.block_w;
     hdr->block_h = t.block_h;
     hdr->ppt_y = t.ppt_y;
-    info = BatchInfo{n_jobs, dtype, {t.block_w, t.block_h, {}, {}}};
-    for (int32_t k = 0; k < xr::kBatchKinds; ++k) {
-        if (hdr->tiles[k] == 0)
-            continue;
+    hdr->lds_bytes = lds_bytes;
+    info = BatchInfo{n_jobs, dtype, {t.block_w, t.block_h, {}, lds_bytes}};
+    for (int32_t k = 0; k < xr::kBatchKinds; ++k)
         info.launch.grid[k] = static_cast<int32_t>(hdr->tiles[k]);
-        if (k != xr::kBatchNarrow)
-            info.launch.lds[k] = static_cast<size_t>(t.block_w / 64 * t.block_h) *
-                                 xr::batch_walk_wave_bytes(hdr->table_bytes[k], hdr->win_bytes[k]);
-    }
     return XR_OK;
 }
 

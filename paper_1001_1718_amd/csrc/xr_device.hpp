@@ -172,15 +172,20 @@ __device__ __forceinline__ void tile_coords(int32_t order, int32_t &bx, int32_t 
     by = static_cast<int32_t>(logical / gx);
 }
 
-// The batch job of this workgroup's tile (counted over the jobs of `kind`, in
-// rows of the grid) and the tile's place in it; false past the last tile.
-// Every field is uniform.
-__device__ __forceinline__ bool batch_tile(const unsigned char *__restrict__ ws, int32_t kind, BatchJob &job,
-                                           int32_t &plane, int32_t &tx, int32_t &ty)
+// This workgroup's tile of a launch with a workgroup per tile, in rows of the
+// grid.
+__device__ __forceinline__ int64_t batch_block()
+{
+    return static_cast<int64_t>(blockIdx.y) * gridDim.x + blockIdx.x;
+}
+
+// The batch job of a tile (counted over the jobs of `kind`) and the tile's
+// place in it; false past the last tile. Every field is uniform.
+__device__ __forceinline__ bool batch_tile(const unsigned char *__restrict__ ws, int32_t kind, int64_t tile,
+                                           BatchJob &job, int32_t &plane, int32_t &tx, int32_t &ty)
 {
     const BatchHeader *hdr = reinterpret_cast<const BatchHeader *>(ws);
     const BatchJob *jobs = reinterpret_cast<const BatchJob *>(ws + kBatchHeaderBytes);
-    const int64_t tile = static_cast<int64_t>(blockIdx.y) * gridDim.x + blockIdx.x;
     if (tile >= hdr->tiles[kind])
         return false;
     int32_t lo = hdr->job_lo[kind], hi = hdr->job_hi[kind] - 1;  // last job of the kind whose tile_begin <= tile

@@ -826,7 +826,7 @@ __global__ void __launch_bounds__(256) k_batch_narrow(const unsigned char *__res
 {
     int32_t plane, tx, ty;
     BatchJob job;
-    if (!batch_tile(ws, kBatchNarrow, job, plane, tx, ty))
+    if (!batch_tile(ws, kBatchNarrow, batch_block(), job, plane, tx, ty))
         return;
     const ResizeArgs &a = job.a;
     const int32_t col0 = tx * static_cast<int32_t>(blockDim.x) + static_cast<int32_t>(threadIdx.x);

@@ -40,11 +40,12 @@ struct BatchJob {
     int32_t strip_h;         // output rows per thread strip of this job
     int32_t kind;            // launch of the job (kBatchKinds)
     int32_t kind_fc;         // 2 * (bicubic) + (four channels)
-    int32_t pad_;
+    int16_t waves_w;         // wavefronts of a workgroup that walk a tile of
+    int16_t waves_h;         // this job: side by side, below one another
 };
 
-// Launches of the batched resize, one per job kind: kinds 0-3 are
-// 2 * (bicubic) + (four channels); kind 4 holds the jobs whose output is
+// Kinds of batched jobs; those of the kinds 0-3 share one launch. Kinds 0-3
+// are 2 * (bicubic) + (four channels); kind 4 holds the jobs whose output is
 // narrower than the staged walk's run or whose staged rows are too long.
 constexpr int32_t kBatchKinds = 5;
 constexpr int32_t kBatchNarrow = 4;
@@ -57,12 +58,10 @@ struct BatchHeader {
     int32_t block_w;         // threads per workgroup along x
     int32_t block_h;         // thread rows per workgroup
     int32_t ppt_y;           // rows per thread strip (before per-job scaling)
-    int32_t pad_;
+    int32_t lds_bytes;       // LDS of a workgroup of the staged walk
     int32_t job_lo[kBatchKinds];    // jobs [job_lo, job_hi) are of kind k
     int32_t job_hi[kBatchKinds];
     int64_t tiles[kBatchKinds];     // tiles of kind k, a workgroup each
-    int32_t table_bytes[kBatchKinds];  // LDS of a wavefront of kind k: row weights
-    int32_t win_bytes[kBatchKinds];    // and staged rows
 };
 constexpr size_t kBatchHeaderBytes = 256;
 static_assert(sizeof(BatchHeader) <= kBatchHeaderBytes, "batch header");
@@ -106,11 +105,11 @@ hipError_t launch_walk(const ResizeArgs &a, int32_t filter, int32_t dtype, int32
 // rows for an in_w -> out_w resize.
 bool walk_fits(int32_t filter, int32_t dtype, int32_t channels, int32_t in_w, int32_t out_w);
 
-// Launches of a prepared batch: workgroups and LDS bytes per kind.
+// Launches of a prepared batch: workgroups per kind, LDS of those that walk.
 struct BatchLaunch {
     int32_t block_w, block_h;
     int32_t grid[kBatchKinds];
-    size_t lds[kBatchKinds];
+    int32_t lds_bytes;
 };
 // The grid of `tiles` workgroups, in rows of at most 2^22 (a launch holds
 // fewer than 2^32 threads along x).
@@ -122,12 +121,11 @@ inline dim3 batch_grid(int32_t tiles)
 // LDS of a wavefront that walks a job in strips of `strip` rows; ok = false
 // where the staged walk does not apply.
 struct BatchWalkNeed {
-    int32_t table_bytes, win_bytes;
+    int32_t win_bytes, wave_bytes;  // the staged rows; with the row table
     bool ok;
 };
 BatchWalkNeed batch_walk_need(const ResizeArgs &a, int32_t filter, int32_t dtype, int32_t channels, int32_t strip);
-int32_t batch_walk_wave_bytes(int32_t table_bytes, int32_t win_bytes);
-// The batched launches of a prepared workspace: one per kind with grid[kind] > 0.
+// The batched launches of a prepared workspace: the jobs that walk, and the others.
 hipError_t launch_batched(const void *ws, int32_t dtype, const BatchLaunch &l, hipStream_t stream);
 // Direct-to-LDS loads take the place of their data from the low 16 bits of M0:
 // workgroups that stage rows stay within 64 KiB of LDS.

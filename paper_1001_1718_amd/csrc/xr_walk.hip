@@ -28,8 +28,8 @@
 // 800^2 RGBA uint8 image 26.2 -> 21.1 us (4.5 TB/s). Long outputs are bound by
 // memory, small ones by the time to a wavefront's first rows.
 //
-// Batches: the jobs are grouped by kind (filter x channel count), one launch
-// per kind, compiled for it, with a workgroup per tile. The hardware hands the
+// Batches: the jobs are grouped by kind (filter x channel count), and one launch
+// has a workgroup per tile of all of them. The hardware hands the
 // tiles out in order; a kind's jobs are ordered largest first, so long tiles
 // start early and short ones fill the tail. (Persistent workgroups that drew
 // tiles from a counter in memory were bound by it, some 10 ns a tile: 256
@@ -393,31 +393,103 @@ __global__ void __launch_bounds__(512, 4) k_walk(ResizeArgs a, int32_t strip_h, 
           lds + wave * (table_bytes + win_bytes + kWalkSlack), table_bytes, win_bytes, lane);
 }
 
-// One workgroup per tile of the jobs of `kind`: (blockDim.x PPX) columns by
-// (blockDim.y strip_h) rows of one plane of one job.
+// kind = 2 * bicubic + four channels
+constexpr int32_t batch_kind(int filter, int channels) { return (filter == kBicubic ? 2 : 0) + (channels == 4 ? 1 : 0); }
+
+// A workgroup's tile of the jobs of one kind: waves_w x waves_h strips of
+// 64 PPX columns by strip_h rows of one plane of one job. The wavefronts share
+// the workgroup's LDS; a job of long staged rows leaves some of them idle.
 template <int FILTER, typename T, int C>
-__global__ void __launch_bounds__(256, 4) k_batch_walk(const unsigned char *__restrict__ ws, int32_t kind)
+__device__ __forceinline__ void batch_walk_tile(const unsigned char *__restrict__ ws, int64_t tile,
+                                                unsigned char *lds)
 {
+    constexpr int32_t kind = batch_kind(FILTER, C);
     constexpr int PPX = batch_ppx(FILTER == kBicubic ? XR_BICUBIC : XR_BILINEAR,
                                   std::is_same_v<T, uint8_t> ? XR_U8 : std::is_same_v<T, float> ? XR_F32 : XR_F16, C);
-    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
-    const BatchHeader *hdr = reinterpret_cast<const BatchHeader *>(ws);
-    const int32_t table_bytes = hdr->table_bytes[kind], win_bytes = hdr->win_bytes[kind];
     const int32_t tid = static_cast<int32_t>(threadIdx.y * blockDim.x + threadIdx.x);
     const int32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int32_t wx = __builtin_amdgcn_readfirstlane(static_cast<int32_t>(threadIdx.x) >> 6);
-    const int32_t wy = __builtin_amdgcn_readfirstlane(static_cast<int32_t>(threadIdx.y));
     int32_t plane, tx, ty;
     BatchJob job;
-    if (!batch_tile(ws, kind, job, plane, tx, ty))
+    if (!batch_tile(ws, kind, tile, job, plane, tx, ty))
         return;
     const ResizeArgs &a = job.a;
-    const int32_t col0 = (tx * static_cast<int32_t>(blockDim.x) + wx * 64) * PPX;
-    const int32_t r_begin = (ty * static_cast<int32_t>(blockDim.y) + wy) * job.strip_h;
-    if (col0 < a.out_w && r_begin < a.dst_rows) {
+    int32_t wx = wave, wy = 0;
+    while (wx >= job.waves_w) {
+        wx -= job.waves_w;
+        ++wy;
+    }
+    const int32_t col0 = (tx * job.waves_w + wx) * 64 * PPX;
+    const int32_t r_begin = (ty * job.waves_h + wy) * job.strip_h;
+    if (wy < job.waves_h && col0 < a.out_w && r_begin < a.dst_rows) {
+        const int32_t mine = reinterpret_cast<const BatchHeader *>(ws)->lds_bytes / (job.waves_w * job.waves_h) / 16 * 16;
+        const int32_t table_bytes = walk_table(Taps<FILTER>::K, job.strip_h);
         StagedWalk<FILTER, T, C, PPX> w;
         w.run(a, plane, col0, r_begin, min(r_begin + job.strip_h, a.dst_rows),
-              lds + wave * (table_bytes + win_bytes + kWalkSlack), table_bytes, win_bytes, tid & 63);
+              lds + wave * mine, table_bytes, mine - table_bytes - kWalkSlack, tid & 63);
+    }
+}
+
+// Batches of one kind: a workgroup per tile.
+template <int FILTER, typename T, int C>
+__global__ void __launch_bounds__(256, 4) k_batch_walk(const unsigned char *__restrict__ ws)
+{
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+    batch_walk_tile<FILTER, T, C>(ws, batch_block(), lds);
+}
+
+// Two series of tiles in one: of n in all, a of the first, spread evenly.
+struct Interleave {
+    uint64_t step;  // ceil(2^32 a / n)
+    uint32_t a;
+
+    void init(int64_t a_, int64_t n)
+    {
+        a = static_cast<uint32_t>(a_);
+        step = n > 0 ? ((static_cast<uint64_t>(a_) << 32) + n - 1) / n : 0;
+    }
+    // tile `t` (below n < 2^31) is of the first series; t becomes its place in
+    // its own. min(a, floor(t step / 2^32)) of the tiles below t are.
+    __device__ __forceinline__ bool first(uint32_t &t) const
+    {
+        const uint32_t lo = min(a, static_cast<uint32_t>((t * step) >> 32));
+        const uint32_t hi = min(a, static_cast<uint32_t>((t * step + step) >> 32));
+        const bool mine = hi > lo;
+        t = mine ? lo : t - lo;
+        return mine;
+    }
+};
+
+// Batches of several kinds: one launch of all their tiles, the kinds
+// interleaved, so that a batch has one last wave instead of four and the
+// one-channel and bicubic tiles, which instructions bound, share the chip with
+// the bilinear RGBA ones, which memory bounds. Launched kind by kind and so: 16
+// uneven uint8 images up to 256^2 30 and 10.5 us, 64 up to 700^2 83 and 55,
+// 128 up to 2048^2 642 and 587; 64 float32 images up to 700^2 140 and 119; 256
+// uint8 images up to 2048^2 958 to 975 us and 885 or 988 (a process has one of
+// the two, by where its buffers lie).
+// A batch of one kind has its own kernel, of fewer registers.
+struct BatchMix {
+    Interleave four, cubic1, cubic4;  // RGBA of all, bicubic of the one-channel and of the RGBA tiles
+    int32_t tiles;
+};
+template <typename T>
+__global__ void __launch_bounds__(256, 4) k_batch_mix(const unsigned char *__restrict__ ws, BatchMix mix)
+{
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+    const int64_t block = batch_block();
+    if (block >= mix.tiles)
+        return;
+    uint32_t t = static_cast<uint32_t>(block);
+    if (mix.four.first(t)) {
+        if (mix.cubic4.first(t))
+            batch_walk_tile<kBicubic, T, 4>(ws, t, lds);
+        else
+            batch_walk_tile<kBilinear, T, 4>(ws, t, lds);
+    } else {
+        if (mix.cubic1.first(t))
+            batch_walk_tile<kBicubic, T, 1>(ws, t, lds);
+        else
+            batch_walk_tile<kBilinear, T, 1>(ws, t, lds);
     }
 }
 
@@ -511,20 +583,32 @@ hipError_t launch_walk_filter(const ResizeArgs &a, int32_t dtype, int32_t channe
     }
 }
 
-// kind = 2 * bicubic + four channels
 template <typename T, int FILTER, int C>
 struct BatchKind {
-    static constexpr int32_t kKind = (FILTER == kBicubic ? 2 : 0) + (C == 4 ? 1 : 0);
+    static constexpr int32_t kKind = batch_kind(FILTER, C);
     static void launch(const unsigned char *ws, dim3 block, const BatchLaunch &l, hipStream_t stream)
     {
         if (l.grid[kKind] > 0)
-            hipLaunchKernelGGL((k_batch_walk<FILTER, T, C>), batch_grid(l.grid[kKind]), block, l.lds[kKind], stream, ws, kKind);
+            hipLaunchKernelGGL((k_batch_walk<FILTER, T, C>), batch_grid(l.grid[kKind]), block, l.lds_bytes, stream, ws);
     }
 };
 
 template <typename T>
 void launch_kinds(const unsigned char *ws, dim3 block, const BatchLaunch &l, hipStream_t stream)
 {
+    const int64_t one = int64_t(l.grid[0]) + l.grid[2], four = int64_t(l.grid[1]) + l.grid[3];
+    int kinds = 0;
+    for (int32_t k = 0; k < kBatchNarrow; ++k)
+        kinds += l.grid[k] > 0;
+    if (kinds > 1 && one + four < (int64_t(1) << 31)) {
+        BatchMix mix;
+        mix.four.init(four, one + four);
+        mix.cubic1.init(l.grid[2], one);
+        mix.cubic4.init(l.grid[3], four);
+        mix.tiles = static_cast<int32_t>(one + four);
+        hipLaunchKernelGGL(k_batch_mix<T>, batch_grid(mix.tiles), block, l.lds_bytes, stream, ws, mix);
+        return;
+    }
     BatchKind<T, kBilinear, 1>::launch(ws, block, l, stream);
     BatchKind<T, kBilinear, 4>::launch(ws, block, l, stream);
     BatchKind<T, kBicubic, 1>::launch(ws, block, l, stream);
@@ -560,11 +644,9 @@ BatchWalkNeed batch_walk_need(const ResizeArgs &a, int32_t filter, int32_t dtype
     BatchWalkNeed n;
     n.ok = a.out_w >= ppx && 4 * row_bytes <= kWalkMaxWindow && a.src_pitch <= kStageMaxPitch;
     n.win_bytes = walk_window(row_bytes);
-    n.table_bytes = walk_table(taps, strip);
+    n.wave_bytes = (walk_table(taps, strip) + n.win_bytes + kWalkSlack + 15) / 16 * 16;
     return n;
 }
-
-int32_t batch_walk_wave_bytes(int32_t table_bytes, int32_t win_bytes) { return table_bytes + win_bytes + kWalkSlack; }
 
 hipError_t launch_batched(const void *ws, int32_t dtype, const BatchLaunch &l, hipStream_t stream)
 {

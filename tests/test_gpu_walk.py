@@ -91,3 +91,24 @@ def test_walk_near_the_lds_limit():
                 out.zero_()
                 xr.Batch([(x, out, mode)], tile=t).run()
                 assert _same(out, ref), (iw, ow, mode, t)
+
+
+@pytest.mark.parametrize("dtype", [torch.uint8, torch.float16, torch.float32])
+@pytest.mark.parametrize("kinds", [(("bilinear", 1), ("bicubic", 4)), (("bilinear", 4), ("bicubic", 4)),
+                                   (("bicubic", 1),), (("bilinear", 1), ("bilinear", 4), ("bicubic", 1))])
+def test_batch_of_some_kinds(kinds, dtype):
+    """Uneven counts of tiles per kind; jobs of long staged rows among short ones."""
+    pairs = []
+    for n, (mode, channels) in enumerate(kinds):
+        for k in range(1 + 5 * n):
+            ih, iw, oh, ow = (20 + 7 * k, 900 + 31 * k, 33, 270 - k) if k % 4 == 0 else (9 + k, 40 + 9 * k, 31 + k, 77)
+            x = _data((ih, iw, channels), dtype, 900 + 10 * n + k)
+            pairs.append((x, torch.zeros((oh, ow, channels), dtype=dtype, device=DEV), mode))
+    for t in (None, xr.tile(xr.XR_KERNEL_STRIP, 192, 1, 0, 5), xr.tile(xr.XR_KERNEL_STRIP, 64, 3, 0, 256)):
+        for _, d, _ in pairs:
+            d.zero_()
+        xr.Batch(pairs, tile=t).run()
+        for x, d, mode in pairs:
+            ref = torch.empty_like(d)
+            xr.resize_into(x, ref, mode, tile=GATHER)
+            assert _same(d, ref), (tuple(x.shape), tuple(d.shape), mode, t)
