@@ -16,6 +16,7 @@
 
 #include "../../include/xresize.h"
 #include "xr_internal.h"
+#include "xr_plan.hpp"
 
 // Identity of the kernel build (a hash of the kernel sources, set by the build).
 #ifndef XR_BUILD_ID
@@ -899,16 +900,7 @@ int build_batch(const xr_job *jobs, int32_t n_jobs, const xr_tile *tile, unsigne
         b.a = make_args(j.src, j.dst);
         b.kind = kind;
         b.kind_fc = fc_of(j);
-        // a strip walks about ppt_y source rows or ppt_y output rows, whichever
-        // is fewer output rows, so shrinking jobs do not make long tiles
-        int64_t strip = std::max<int64_t>(
-            1, std::min<int64_t>(t.ppt_y, (static_cast<int64_t>(t.ppt_y) * j.dst.height + j.src.height - 1) /
-                                               j.src.height));
-        // the source rows of a strip, (strip - 1) n_in / n_out + K + 1 at most,
-        // stay below 2^31 bytes (32-bit buffer offsets)
-        const int64_t max_rows = (int64_t(1) << 31) / j.src.row_pitch - 6;
-        strip = std::min<int64_t>(strip, std::max<int64_t>(1, max_rows * j.dst.height / j.src.height));
-        b.strip_h = static_cast<int32_t>(strip);
+        b.strip_h = xr::batch_strip(t.ppt_y, j.src.height, j.dst.height, j.src.row_pitch, j.dst.row_pitch);
         int32_t waves_w = t.block_w / 64, waves_h = t.block_h;
         const xr::BatchWalkNeed need = xr::batch_walk_need(b.a, j.filter, dtype, j.src.channels, b.strip_h);
         while (kind != xr::kBatchNarrow && waves_w * waves_h * need.wave_bytes > lds_bytes)

@@ -43,6 +43,7 @@
 #include "xr_buffer.hpp"
 #include "xr_device.hpp"
 #include "xr_internal.h"
+#include "xr_plan.hpp"
 #include "xr_stage.hpp"
 
 namespace xr {
@@ -642,7 +643,9 @@ BatchWalkNeed batch_walk_need(const ResizeArgs &a, int32_t filter, int32_t dtype
     const int32_t ppx = batch_ppx(filter, dtype, channels);
     const int64_t row_bytes = walk_row_bytes(taps, pb, ppx, a.in_w, a.out_w);
     BatchWalkNeed n;
-    n.ok = a.out_w >= ppx && 4 * row_bytes <= kWalkMaxWindow && a.src_pitch <= kStageMaxPitch;
+    // (the walk stores through a resource of its strip: one row has to fit)
+    n.ok = a.out_w >= ppx && 4 * row_bytes <= kWalkMaxWindow && a.src_pitch <= kStageMaxPitch &&
+           a.dst_pitch < kResourceBytes;
     n.win_bytes = walk_window(row_bytes);
     n.wave_bytes = (walk_table(taps, strip) + n.win_bytes + kWalkSlack + 15) / 16 * 16;
     return n;
