@@ -30,6 +30,7 @@
 #include "xr_device.hpp"
 #include "xr_gather_walk.hpp"
 #include "xr_internal.h"
+#include "xr_plan.hpp"
 
 namespace xr {
 using namespace dev;
@@ -651,15 +652,11 @@ __global__ void __launch_bounds__(256) k_bwd_x2(ResizeArgs a, int32_t ns)
 }
 
 template <int FILTER, typename T, int C>
-hipError_t launch_bwd_up2(const ResizeArgs &a, hipStream_t stream)
+hipError_t launch_bwd_up2(const ResizeArgs &a, int32_t ns, hipStream_t stream)
 {
     constexpr int P = (C == 1) ? 4 : 1;
-    // strips of 8 source rows (measured on the 32x3x1024^2 bilinear FP32
-    // adjoint: 8 rows 345 us, 16 rows 360 us, 32 rows 381 us), shortened so
-    // that a strip's rows stay well inside a buffer resource's 2 GiB
-    int32_t ns = 8;
-    while (ns > 4 && (2 * ns + 8) * std::max(a.src_pitch, a.dst_pitch) >= (int64_t(1) << 30))
-        ns -= 4;
+    // strips of ns = 8 source rows (measured on the 32x3x1024^2 bilinear FP32
+    // adjoint: 8 rows 345 us, 16 rows 360 us, 32 rows 381 us), 4 at long pitches
     const int32_t cols_per_block = 256 * P;
     const size_t lds = RunStore<T, C, P>::kExchange ? 256 * RunStore<T, C, P>::OB : 0;
     hipLaunchKernelGGL((k_bwd_x2<FILTER, T, C, P>),
@@ -735,8 +732,9 @@ bool bwd_walk_shape(const ResizeArgs &a, const BwdPlan &p, GatherShape &g)
 template <int FILTER, typename T, int C>
 hipError_t launch_bwd_typed(const ResizeArgs &a, hipStream_t stream)
 {
-    if (a.out_w == 2 * a.in_w && a.out_h == 2 * a.in_h)
-        return launch_bwd_up2<FILTER, T, C>(a, stream);
+    const int32_t ns = bwd_x2_rows(std::max(a.src_pitch, a.dst_pitch));
+    if (a.out_w == 2 * a.in_w && a.out_h == 2 * a.in_h && ns > 0)
+        return launch_bwd_up2<FILTER, T, C>(a, ns, stream);
     const BwdPlan p = plan_backward<FILTER, C>(a);
     if (p.lds == 0)
         return hipErrorInvalidConfiguration;

@@ -34,6 +34,7 @@
 #include "xr_buffer.hpp"
 #include "xr_device.hpp"
 #include "xr_internal.h"
+#include "xr_plan.hpp"
 
 namespace xr {
 using namespace dev;
@@ -932,15 +933,10 @@ constexpr bool x2_ppx_ok()
 }
 
 // Strips of 2 np output rows, np = ppt_y / 2 rounded up to a multiple of 4
-// (at least 4), and shortened until a strip's source and output rows stay
-// well inside a buffer resource's 2 GiB.
+// (at least 4; see x2_pairs).
 template <int FILTER, typename T, int C, int PPX>
-hipError_t launch_x2(const ResizeArgs &a, const xr_tile &tile, hipStream_t stream)
+hipError_t launch_x2(const ResizeArgs &a, const xr_tile &tile, int64_t np, hipStream_t stream)
 {
-    int64_t np = std::max<int64_t>(4, (static_cast<int64_t>(tile.ppt_y) + 7) / 8 * 4);
-    const int64_t pitch = std::max(a.src_pitch, a.dst_pitch);
-    while (np > 4 && (2 * np + 8) * pitch >= (int64_t(1) << 30))
-        np -= 4;
     const int64_t s_first = (static_cast<int64_t>(a.dst_row0) + 1) / (2 * np);
     const int64_t s_last = (static_cast<int64_t>(a.dst_row0) + a.dst_rows) / (2 * np);
     const int64_t strips = s_last - s_first + 1;
@@ -954,15 +950,10 @@ hipError_t launch_x2(const ResizeArgs &a, const xr_tile &tile, hipStream_t strea
     return hipGetLastError();
 }
 
-// Strips of nr output rows, nr = ppt_y rounded up to an even count, shortened
-// until a strip's rows stay well inside a buffer resource's 2 GiB.
+// Strips of nr output rows, nr = ppt_y rounded up to an even count (x05_rows).
 template <int FILTER, typename T, int C, int PPX>
-hipError_t launch_x05(const ResizeArgs &a, const xr_tile &tile, hipStream_t stream)
+hipError_t launch_x05(const ResizeArgs &a, const xr_tile &tile, int64_t nr, hipStream_t stream)
 {
-    int64_t nr = std::max<int64_t>(2, (static_cast<int64_t>(tile.ppt_y) + 1) / 2 * 2);
-    const int64_t pitch = std::max(a.src_pitch, a.dst_pitch);
-    while (nr > 2 && (2 * nr + 8) * pitch >= (int64_t(1) << 30))
-        nr -= 2;
     const int64_t s_first = static_cast<int64_t>(a.dst_row0) / nr;
     const int64_t s_last = (static_cast<int64_t>(a.dst_row0) + a.dst_rows - 1) / nr;
     const int64_t strips = s_last - s_first + 1;
@@ -986,6 +977,7 @@ hipError_t launch_typed(const ResizeArgs &a, const xr_tile &tile, int32_t mode, 
         hipLaunchKernelGGL((k_gather<FILTER, T, C>), grid, block, 0, stream, a);
         return hipGetLastError();
     }
+    const int64_t pitch = std::max(a.src_pitch, a.dst_pitch);
     const int32_t cols_per_block = tile.block_w * tile.ppt_x;
     const int32_t rows_per_block = tile.block_h * tile.ppt_y;
     const dim3 block(tile.block_w, tile.block_h, 1);
@@ -994,13 +986,13 @@ hipError_t launch_typed(const ResizeArgs &a, const xr_tile &tile, int32_t mode, 
 #define XR_STRIP_CASE(P)                                                                        \
     case P:                                                                                     \
         if constexpr (FILTER != kNearest) {                                                     \
-            if (mode == kUp2) {                                                                 \
+            if (mode == kUp2 && x2_pairs(tile.ppt_y, pitch) > 0) {                              \
                 if constexpr (x2_ppx_ok<T, C, P>())                                             \
-                    return launch_x2<FILTER, T, C, P>(a, tile, stream);                         \
+                    return launch_x2<FILTER, T, C, P>(a, tile, x2_pairs(tile.ppt_y, pitch), stream); \
             }                                                                                   \
-            if (mode == kDown2) {                                                               \
+            if (mode == kDown2 && x05_rows(tile.ppt_y, pitch) > 0) {                            \
                 if constexpr ((2 * P * Pix<T, C>::kBytes) % 4 == 0 && P * Pix<T, C>::kBytes <= 64) \
-                    return launch_x05<FILTER, T, C, P>(a, tile, stream);                        \
+                    return launch_x05<FILTER, T, C, P>(a, tile, x05_rows(tile.ppt_y, pitch), stream); \
             }                                                                                   \
         }                                                                                       \
         if (tile.kernel != XR_KERNEL_STRIP_ANY) {                                               \

@@ -22,6 +22,20 @@ int main()
                         bad += by_src < 1 || by_src > ppt || (by_src > 1 && rows * pitch >= (int64_t(1) << 31));
                         total += 2;
                     }
+    // the exact-ratio walks: whole steps, and 2 strip + 8 rows below 2^31 bytes
+    // or no strip at all, which only pitches of 2^27 bytes and more get
+    for (int64_t base = 16; base < (int64_t(1) << 33); base *= 2)
+        for (int64_t pitch : {base, base + base / 2, 2 * base - 4})
+            for (int32_t ppt = 1; ppt <= 4096; ppt = ppt * 3 / 2 + 1) {
+                const auto check = [&](int64_t strip, int64_t step) {
+                    bad += strip % step != 0 || (strip == 0 && pitch < (int64_t(1) << 27)) ||
+                           (strip > 0 && (2 * strip + 8) * pitch >= (int64_t(1) << 31));
+                    ++total;
+                };
+                check(xr::x2_pairs(ppt, pitch), 4);
+                check(xr::x05_rows(ppt, pitch), 2);
+                check(xr::bwd_x2_rows(pitch), 4);
+            }
     printf("checked %lld strips, %lld too long\n", total, bad);
     return bad != 0;
 }
