@@ -318,19 +318,24 @@ bool aa_walk_shape(const ResizeArgs &a, GatherShape &g)
 }
 
 template <int R, typename T, int C>
-hipError_t launch_aa_typed(const ResizeArgs &a, const xr_tile &tile, hipStream_t stream)
+hipError_t launch_aa_typed(const ResizeArgs &a, const xr_tile &tile, hipStream_t stream, Route *only)
 {
     const dim3 block(tile.block_w, tile.block_h, 1);
     const dim3 grid((a.out_w + tile.block_w - 1) / tile.block_w,
                     (a.dst_rows + tile.block_h - 1) / tile.block_h, a.planes);
     if (tile.kernel == XR_KERNEL_GATHER) {
+        if (just_named(only, kRouteAaGather))
+            return hipSuccess;
         const AaPlan plan = aa_plan(a.in_w, a.in_h, a.out_w, a.out_h, R, tile.block_w, tile.block_h);
         hipLaunchKernelGGL((k_gather_aa<R, T, C>), grid, block, plan.lds_bytes, stream, a, plan.kx, plan.ky);
         return hipGetLastError();
     }
     GatherShape g;
     if (aa_walk_shape<R, T, C>(a, g))
-        return launch_gather_walk<AaWalk<R>, T, C>(a, g, a.out_w, a.dst_rows, stream);
+        return just_named(only, kRouteAaWalk) ? hipSuccess
+                                              : launch_gather_walk<AaWalk<R>, T, C>(a, g, a.out_w, a.dst_rows, stream);
+    if (just_named(only, kRouteAaTile))
+        return hipSuccess;
     const AaPlan plan = aa_tile_plan(a.in_w, a.in_h, a.out_w, a.out_h, R, tile.block_w, tile.block_h,
                                      Pix<T, C>::kBytes, C);
     // tiles per workgroup down a tile column: the column tables are then
@@ -348,18 +353,18 @@ hipError_t launch_aa_typed(const ResizeArgs &a, const xr_tile &tile, hipStream_t
 
 template <int R>
 hipError_t launch_aa(const ResizeArgs &a, int32_t dtype, int32_t channels, const xr_tile &tile,
-                     hipStream_t stream)
+                     hipStream_t stream, Route *only)
 {
     switch (dtype) {
     case XR_U8:
-        return channels == 4 ? launch_aa_typed<R, uint8_t, 4>(a, tile, stream)
-                             : launch_aa_typed<R, uint8_t, 1>(a, tile, stream);
+        return channels == 4 ? launch_aa_typed<R, uint8_t, 4>(a, tile, stream, only)
+                             : launch_aa_typed<R, uint8_t, 1>(a, tile, stream, only);
     case XR_F16:
-        return channels == 4 ? launch_aa_typed<R, _Float16, 4>(a, tile, stream)
-                             : launch_aa_typed<R, _Float16, 1>(a, tile, stream);
+        return channels == 4 ? launch_aa_typed<R, _Float16, 4>(a, tile, stream, only)
+                             : launch_aa_typed<R, _Float16, 1>(a, tile, stream, only);
     case XR_F32:
-        return channels == 4 ? launch_aa_typed<R, float, 4>(a, tile, stream)
-                             : launch_aa_typed<R, float, 1>(a, tile, stream);
+        return channels == 4 ? launch_aa_typed<R, float, 4>(a, tile, stream, only)
+                             : launch_aa_typed<R, float, 1>(a, tile, stream, only);
     default:
         return hipErrorInvalidValue;
     }
@@ -385,10 +390,10 @@ bool antialiased_walk_supported(const ResizeArgs &a, int32_t filter, int32_t dty
 }
 
 hipError_t launch_antialiased(const ResizeArgs &a, int32_t filter, int32_t dtype, int32_t channels,
-                              const xr_tile &tile, hipStream_t stream)
+                              const xr_tile &tile, hipStream_t stream, Route *only)
 {
-    return filter == XR_BILINEAR_AA ? launch_aa<1>(a, dtype, channels, tile, stream)
-                                    : launch_aa<2>(a, dtype, channels, tile, stream);
+    return filter == XR_BILINEAR_AA ? launch_aa<1>(a, dtype, channels, tile, stream, only)
+                                    : launch_aa<2>(a, dtype, channels, tile, stream, only);
 }
 
 }  // namespace xr

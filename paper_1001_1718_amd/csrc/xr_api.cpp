@@ -571,8 +571,9 @@ int check_grid(const xr_tile &t, const xr_image &dst)
     return XR_OK;
 }
 
+// Checks a call and runs it; given `only`, names the kernel instead.
 int resize_common(const xr_image *src, const xr_image *dst, const xr_tile *tile, int32_t filter,
-                  int32_t mapping, void *stream)
+                  int32_t mapping, void *stream, xr::Route *only = nullptr)
 {
     int rc = check_pair(src, dst, filter, mapping);
     if (rc)
@@ -602,9 +603,52 @@ int resize_common(const xr_image *src, const xr_image *dst, const xr_tile *tile,
     const xr::ResizeArgs a = make_args(*src, *dst, mapping);
     const hipError_t e = xr::launch_forward(a, filter, src->dtype, src->channels, t,
                                             axis_mode(*src, *dst, t, filter, mapping),
-                                            static_cast<hipStream_t>(stream));
+                                            static_cast<hipStream_t>(stream), only);
     if (e != hipSuccess)
         return fail_hip(e, "resize launch");
+    return XR_OK;
+}
+
+int backward_common(const xr_image *grad_dst, const xr_image *grad_src, int32_t filter, void *stream,
+                    xr::Route *only = nullptr)
+{
+    if (filter != XR_BILINEAR && filter != XR_BICUBIC)
+        return fail(XR_ERR_ARG, "filter = %d is not XR_BILINEAR or XR_BICUBIC", filter);
+    int rc = check_image(grad_dst, "grad_dst");
+    if (rc)
+        return rc;
+    rc = check_image(grad_src, "grad_src");
+    if (rc)
+        return rc;
+    if ((grad_dst->dtype != XR_F32 && grad_dst->dtype != XR_F16) || grad_src->dtype != grad_dst->dtype)
+        return fail(XR_ERR_DTYPE, "the adjoint takes float32 or float16 gradients, both of one type "
+                    "(grad_dst %d, grad_src %d)", grad_dst->dtype, grad_src->dtype);
+    if (grad_dst->channels != grad_src->channels)
+        return fail(XR_ERR_CHANNELS, "grad_dst.channels %d != grad_src.channels %d",
+                    grad_dst->channels, grad_src->channels);
+    if (grad_dst->planes != grad_src->planes)
+        return fail(XR_ERR_SHAPE, "grad_dst.planes %d != grad_src.planes %d", grad_dst->planes,
+                    grad_src->planes);
+    if (grad_dst->row0 != 0 || grad_dst->rows != grad_dst->height || grad_src->row0 != 0 ||
+        grad_src->rows != grad_src->height)
+        return fail(XR_ERR_RANGE, "the adjoint takes whole images (row0 = 0, rows = height)");
+    if (overlaps(*grad_dst, *grad_src))
+        return fail(XR_ERR_ALIAS, "grad_dst and grad_src memory overlap");
+    // forward view: source = grad_src geometry, destination = grad_dst geometry
+    xr::ResizeArgs a = make_args(*grad_src, *grad_dst);
+    a.src = static_cast<const unsigned char *>(grad_dst->data);
+    a.src_pitch = grad_dst->row_pitch;
+    a.src_plane_pitch = grad_dst->planes > 1 ? grad_dst->plane_pitch : 0;
+    a.dst = static_cast<unsigned char *>(grad_src->data);
+    a.dst_pitch = grad_src->row_pitch;
+    a.dst_plane_pitch = grad_src->planes > 1 ? grad_src->plane_pitch : 0;
+    if (!xr::backward_supported(a, filter, grad_src->channels))
+        return fail(XR_ERR_SHAPE, "adjoint: %dx%d -> %dx%d is too strong an upscale for one LDS tile",
+                    grad_src->width, grad_src->height, grad_dst->width, grad_dst->height);
+    const hipError_t e = xr::launch_backward(a, filter, grad_src->dtype, grad_src->channels,
+                                             static_cast<hipStream_t>(stream), only);
+    if (e != hipSuccess)
+        return fail_hip(e, "backward launch");
     return XR_OK;
 }
 
@@ -1139,44 +1183,24 @@ int xr_batch_autotune(const xr_job *jobs, int32_t n_jobs, const xr_tile *candida
 int xr_resize_backward(const xr_image *grad_dst, const xr_image *grad_src, int32_t filter,
                        void *stream)
 {
-    if (filter != XR_BILINEAR && filter != XR_BICUBIC)
-        return fail(XR_ERR_ARG, "filter = %d is not XR_BILINEAR or XR_BICUBIC", filter);
-    int rc = check_image(grad_dst, "grad_dst");
-    if (rc)
-        return rc;
-    rc = check_image(grad_src, "grad_src");
-    if (rc)
-        return rc;
-    if ((grad_dst->dtype != XR_F32 && grad_dst->dtype != XR_F16) || grad_src->dtype != grad_dst->dtype)
-        return fail(XR_ERR_DTYPE, "the adjoint takes float32 or float16 gradients, both of one type "
-                    "(grad_dst %d, grad_src %d)", grad_dst->dtype, grad_src->dtype);
-    if (grad_dst->channels != grad_src->channels)
-        return fail(XR_ERR_CHANNELS, "grad_dst.channels %d != grad_src.channels %d",
-                    grad_dst->channels, grad_src->channels);
-    if (grad_dst->planes != grad_src->planes)
-        return fail(XR_ERR_SHAPE, "grad_dst.planes %d != grad_src.planes %d", grad_dst->planes,
-                    grad_src->planes);
-    if (grad_dst->row0 != 0 || grad_dst->rows != grad_dst->height || grad_src->row0 != 0 ||
-        grad_src->rows != grad_src->height)
-        return fail(XR_ERR_RANGE, "the adjoint takes whole images (row0 = 0, rows = height)");
-    if (overlaps(*grad_dst, *grad_src))
-        return fail(XR_ERR_ALIAS, "grad_dst and grad_src memory overlap");
-    // forward view: source = grad_src geometry, destination = grad_dst geometry
-    xr::ResizeArgs a = make_args(*grad_src, *grad_dst);
-    a.src = static_cast<const unsigned char *>(grad_dst->data);
-    a.src_pitch = grad_dst->row_pitch;
-    a.src_plane_pitch = grad_dst->planes > 1 ? grad_dst->plane_pitch : 0;
-    a.dst = static_cast<unsigned char *>(grad_src->data);
-    a.dst_pitch = grad_src->row_pitch;
-    a.dst_plane_pitch = grad_src->planes > 1 ? grad_src->plane_pitch : 0;
-    if (!xr::backward_supported(a, filter, grad_src->channels))
-        return fail(XR_ERR_SHAPE, "adjoint: %dx%d -> %dx%d is too strong an upscale for one LDS tile",
-                    grad_src->width, grad_src->height, grad_dst->width, grad_dst->height);
-    const hipError_t e = xr::launch_backward(a, filter, grad_src->dtype, grad_src->channels,
-                                             static_cast<hipStream_t>(stream));
-    if (e != hipSuccess)
-        return fail_hip(e, "backward launch");
-    return XR_OK;
+    return backward_common(grad_dst, grad_src, filter, stream);
+}
+
+// Not part of the interface: the kernel (xr::Route) that a call with these
+// arguments runs, or minus its error code. No HIP call.
+int32_t xr_internal_route(const xr_image *src, const xr_image *dst, int32_t filter, int32_t mapping,
+                          const xr_tile *tile)
+{
+    xr::Route r{};
+    const int rc = resize_common(src, dst, tile, filter, mapping, nullptr, &r);
+    return rc ? -rc : static_cast<int32_t>(r);
+}
+
+int32_t xr_internal_route_backward(const xr_image *grad_dst, const xr_image *grad_src, int32_t filter)
+{
+    xr::Route r{};
+    const int rc = backward_common(grad_dst, grad_src, filter, nullptr, &r);
+    return rc ? -rc : static_cast<int32_t>(r);
 }
 
 int32_t xr_tune_candidates(int32_t filter, int32_t dtype, int32_t channels, int32_t in_w,

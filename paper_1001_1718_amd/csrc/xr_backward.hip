@@ -730,17 +730,21 @@ bool bwd_walk_shape(const ResizeArgs &a, const BwdPlan &p, GatherShape &g)
 }
 
 template <int FILTER, typename T, int C>
-hipError_t launch_bwd_typed(const ResizeArgs &a, hipStream_t stream)
+hipError_t launch_bwd_typed(const ResizeArgs &a, hipStream_t stream, Route *only)
 {
     const int32_t ns = bwd_x2_rows(std::max(a.src_pitch, a.dst_pitch));
     if (a.out_w == 2 * a.in_w && a.out_h == 2 * a.in_h && ns > 0)
-        return launch_bwd_up2<FILTER, T, C>(a, ns, stream);
+        return just_named(only, kRouteBwdX2) ? hipSuccess : launch_bwd_up2<FILTER, T, C>(a, ns, stream);
     const BwdPlan p = plan_backward<FILTER, C>(a);
     if (p.lds == 0)
         return hipErrorInvalidConfiguration;
     GatherShape g;
     if (bwd_walk_shape<FILTER, T, C>(a, p, g))
-        return launch_gather_walk<AdjointWalk<FILTER>, T, C>(a, g, a.in_w, a.in_h, stream);
+        return just_named(only, kRouteBwdWalk)
+                   ? hipSuccess
+                   : launch_gather_walk<AdjointWalk<FILTER>, T, C>(a, g, a.in_w, a.in_h, stream);
+    if (just_named(only, kRouteBwdOwner))
+        return hipSuccess;
     const dim3 grid((a.in_w + p.tw - 1) / p.tw, (a.in_h + p.th - 1) / p.th, a.planes);
     hipLaunchKernelGGL((k_bwd_owner<FILTER, T, C>), grid, dim3(kBwdThreads), p.lds, stream, a, p.tw, p.th,
                        p.max_rows, p.nmax, p.nmax_y);
@@ -748,9 +752,10 @@ hipError_t launch_bwd_typed(const ResizeArgs &a, hipStream_t stream)
 }
 
 template <int FILTER, typename T>
-hipError_t launch_bwd_channels(const ResizeArgs &a, int32_t channels, hipStream_t stream)
+hipError_t launch_bwd_channels(const ResizeArgs &a, int32_t channels, hipStream_t stream, Route *only)
 {
-    return channels == 4 ? launch_bwd_typed<FILTER, T, 4>(a, stream) : launch_bwd_typed<FILTER, T, 1>(a, stream);
+    return channels == 4 ? launch_bwd_typed<FILTER, T, 4>(a, stream, only)
+                         : launch_bwd_typed<FILTER, T, 1>(a, stream, only);
 }
 
 }  // namespace
@@ -765,13 +770,13 @@ bool backward_supported(const ResizeArgs &a, int32_t filter, int32_t channels)
 }
 
 hipError_t launch_backward(const ResizeArgs &a, int32_t filter, int32_t dtype, int32_t channels,
-                           hipStream_t stream)
+                           hipStream_t stream, Route *only)
 {
     if (dtype == XR_F16)
-        return filter == XR_BICUBIC ? launch_bwd_channels<kBicubic, _Float16>(a, channels, stream)
-                                    : launch_bwd_channels<kBilinear, _Float16>(a, channels, stream);
-    return filter == XR_BICUBIC ? launch_bwd_channels<kBicubic, float>(a, channels, stream)
-                                : launch_bwd_channels<kBilinear, float>(a, channels, stream);
+        return filter == XR_BICUBIC ? launch_bwd_channels<kBicubic, _Float16>(a, channels, stream, only)
+                                    : launch_bwd_channels<kBilinear, _Float16>(a, channels, stream, only);
+    return filter == XR_BICUBIC ? launch_bwd_channels<kBicubic, float>(a, channels, stream, only)
+                                : launch_bwd_channels<kBilinear, float>(a, channels, stream, only);
 }
 
 }  // namespace xr

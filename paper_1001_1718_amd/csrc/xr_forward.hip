@@ -935,8 +935,10 @@ constexpr bool x2_ppx_ok()
 // Strips of 2 np output rows, np = ppt_y / 2 rounded up to a multiple of 4
 // (at least 4; see x2_pairs).
 template <int FILTER, typename T, int C, int PPX>
-hipError_t launch_x2(const ResizeArgs &a, const xr_tile &tile, int64_t np, hipStream_t stream)
+hipError_t launch_x2(const ResizeArgs &a, const xr_tile &tile, int64_t np, hipStream_t stream, Route *only)
 {
+    if (just_named(only, kRouteX2))
+        return hipSuccess;
     const int64_t s_first = (static_cast<int64_t>(a.dst_row0) + 1) / (2 * np);
     const int64_t s_last = (static_cast<int64_t>(a.dst_row0) + a.dst_rows) / (2 * np);
     const int64_t strips = s_last - s_first + 1;
@@ -952,8 +954,10 @@ hipError_t launch_x2(const ResizeArgs &a, const xr_tile &tile, int64_t np, hipSt
 
 // Strips of nr output rows, nr = ppt_y rounded up to an even count (x05_rows).
 template <int FILTER, typename T, int C, int PPX>
-hipError_t launch_x05(const ResizeArgs &a, const xr_tile &tile, int64_t nr, hipStream_t stream)
+hipError_t launch_x05(const ResizeArgs &a, const xr_tile &tile, int64_t nr, hipStream_t stream, Route *only)
 {
+    if (just_named(only, kRouteX05))
+        return hipSuccess;
     const int64_t s_first = static_cast<int64_t>(a.dst_row0) / nr;
     const int64_t s_last = (static_cast<int64_t>(a.dst_row0) + a.dst_rows - 1) / nr;
     const int64_t strips = s_last - s_first + 1;
@@ -968,9 +972,11 @@ hipError_t launch_x05(const ResizeArgs &a, const xr_tile &tile, int64_t nr, hipS
 }
 
 template <int FILTER, typename T, int C>
-hipError_t launch_typed(const ResizeArgs &a, const xr_tile &tile, int32_t mode, hipStream_t stream)
+hipError_t launch_typed(const ResizeArgs &a, const xr_tile &tile, int32_t mode, hipStream_t stream, Route *only)
 {
     if (tile.kernel == XR_KERNEL_GATHER) {
+        if (just_named(only, kRouteGather))
+            return hipSuccess;
         const dim3 block(tile.block_w, tile.block_h, 1);
         const dim3 grid((a.out_w + tile.block_w - 1) / tile.block_w,
                         (a.dst_rows + tile.block_h - 1) / tile.block_h, a.planes);
@@ -988,21 +994,23 @@ hipError_t launch_typed(const ResizeArgs &a, const xr_tile &tile, int32_t mode, 
         if constexpr (FILTER != kNearest) {                                                     \
             if (mode == kUp2 && x2_pairs(tile.ppt_y, pitch) > 0) {                              \
                 if constexpr (x2_ppx_ok<T, C, P>())                                             \
-                    return launch_x2<FILTER, T, C, P>(a, tile, x2_pairs(tile.ppt_y, pitch), stream); \
+                    return launch_x2<FILTER, T, C, P>(a, tile, x2_pairs(tile.ppt_y, pitch), stream, only); \
             }                                                                                   \
             if (mode == kDown2 && x05_rows(tile.ppt_y, pitch) > 0) {                            \
                 if constexpr ((2 * P * Pix<T, C>::kBytes) % 4 == 0 && P * Pix<T, C>::kBytes <= 64) \
-                    return launch_x05<FILTER, T, C, P>(a, tile, x05_rows(tile.ppt_y, pitch), stream); \
+                    return launch_x05<FILTER, T, C, P>(a, tile, x05_rows(tile.ppt_y, pitch), stream, only); \
             }                                                                                   \
         }                                                                                       \
         if (tile.kernel != XR_KERNEL_STRIP_ANY) {                                               \
             bool taken = false;                                                                 \
             const hipError_t e = launch_walk(a, FILTER == kBicubic ? XR_BICUBIC                 \
                                                 : FILTER == kNearest ? XR_NEAREST : XR_BILINEAR, \
-                                             DType<T>::kCode, C, tile, stream, taken);          \
+                                             DType<T>::kCode, C, tile, stream, taken, only);    \
             if (taken)                                                                          \
                 return e;                                                                       \
         }                                                                                       \
+        if (just_named(only, kRouteStrip))                                                      \
+            return hipSuccess;                                                                  \
         hipLaunchKernelGGL((k_strip<FILTER, T, C, P>), grid, block, 0, stream, a, tile.ppt_y,   \
                            tile.order);                                                         \
         return hipGetLastError();
@@ -1029,18 +1037,18 @@ hipError_t launch_typed(const ResizeArgs &a, const xr_tile &tile, int32_t mode, 
 
 template <int FILTER>
 hipError_t launch_filter(const ResizeArgs &a, int32_t dtype, int32_t channels, const xr_tile &tile,
-                         int32_t mode, hipStream_t stream)
+                         int32_t mode, hipStream_t stream, Route *only)
 {
     switch (dtype) {
     case XR_U8:
-        return channels == 4 ? launch_typed<FILTER, uint8_t, 4>(a, tile, mode, stream)
-                             : launch_typed<FILTER, uint8_t, 1>(a, tile, mode, stream);
+        return channels == 4 ? launch_typed<FILTER, uint8_t, 4>(a, tile, mode, stream, only)
+                             : launch_typed<FILTER, uint8_t, 1>(a, tile, mode, stream, only);
     case XR_F16:
-        return channels == 4 ? launch_typed<FILTER, _Float16, 4>(a, tile, mode, stream)
-                             : launch_typed<FILTER, _Float16, 1>(a, tile, mode, stream);
+        return channels == 4 ? launch_typed<FILTER, _Float16, 4>(a, tile, mode, stream, only)
+                             : launch_typed<FILTER, _Float16, 1>(a, tile, mode, stream, only);
     case XR_F32:
-        return channels == 4 ? launch_typed<FILTER, float, 4>(a, tile, mode, stream)
-                             : launch_typed<FILTER, float, 1>(a, tile, mode, stream);
+        return channels == 4 ? launch_typed<FILTER, float, 4>(a, tile, mode, stream, only)
+                             : launch_typed<FILTER, float, 1>(a, tile, mode, stream, only);
     default:
         return hipErrorInvalidValue;
     }
@@ -1049,15 +1057,15 @@ hipError_t launch_filter(const ResizeArgs &a, int32_t dtype, int32_t channels, c
 }  // namespace
 
 hipError_t launch_forward(const ResizeArgs &a, int32_t filter, int32_t dtype, int32_t channels,
-                          const xr_tile &tile, int32_t mode, hipStream_t stream)
+                          const xr_tile &tile, int32_t mode, hipStream_t stream, Route *only)
 {
     if (filter == XR_BILINEAR_AA || filter == XR_BICUBIC_AA)
-        return launch_antialiased(a, filter, dtype, channels, tile, stream);
+        return launch_antialiased(a, filter, dtype, channels, tile, stream, only);
     if (filter == XR_BICUBIC)
-        return launch_filter<kBicubic>(a, dtype, channels, tile, mode, stream);
+        return launch_filter<kBicubic>(a, dtype, channels, tile, mode, stream, only);
     if (filter == XR_NEAREST)
-        return launch_filter<kNearest>(a, dtype, channels, tile, mode, stream);
-    return launch_filter<kBilinear>(a, dtype, channels, tile, mode, stream);
+        return launch_filter<kNearest>(a, dtype, channels, tile, mode, stream, only);
+    return launch_filter<kBilinear>(a, dtype, channels, tile, mode, stream, only);
 }
 
 }  // namespace xr

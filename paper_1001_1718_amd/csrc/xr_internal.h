@@ -89,10 +89,24 @@ constexpr int32_t batch_ppx(int32_t filter, int32_t dtype, int32_t channels)
 // Shape of an axis that a kernel can specialise on.
 enum AxisMode : int32_t { kGeneral = 0, kUp2 = 1, kDown2 = 2 };
 
+// The kernel that a call runs. The launches below take a Route to fill in: given
+// one they only name the kernel, so tests can ask for it without a GPU.
+enum Route : int32_t {
+    kRouteGather = 1, kRouteStrip, kRouteWalk, kRouteX2, kRouteX05,
+    kRouteAaGather, kRouteAaTile, kRouteAaWalk,
+    kRouteBwdX2, kRouteBwdOwner, kRouteBwdWalk,
+};
+inline bool just_named(Route *only, Route r)
+{
+    if (only)
+        *only = r;
+    return only != nullptr;
+}
+
 hipError_t launch_forward(const ResizeArgs &a, int32_t filter, int32_t dtype, int32_t channels,
-                          const xr_tile &tile, int32_t mode, hipStream_t stream);
+                          const xr_tile &tile, int32_t mode, hipStream_t stream, Route *only = nullptr);
 hipError_t launch_antialiased(const ResizeArgs &a, int32_t filter, int32_t dtype, int32_t channels,
-                              const xr_tile &tile, hipStream_t stream);
+                              const xr_tile &tile, hipStream_t stream, Route *only);
 // True when that launch of an LDS tile takes the gather walk, which needs no
 // block of its own to fit.
 bool antialiased_walk_supported(const ResizeArgs &a, int32_t filter, int32_t dtype, int32_t channels);
@@ -100,7 +114,7 @@ bool antialiased_walk_supported(const ResizeArgs &a, int32_t filter, int32_t dty
 // does not apply (staged rows too long for LDS, outputs narrower than a run,
 // runs it is not built for, pitches past 4 MiB).
 hipError_t launch_walk(const ResizeArgs &a, int32_t filter, int32_t dtype, int32_t channels, const xr_tile &tile,
-                       hipStream_t stream, bool &taken);
+                       hipStream_t stream, bool &taken, Route *only);
 // True when the walk with its own columns per thread (walk_ppx) can stage its
 // rows for an in_w -> out_w resize.
 bool walk_fits(int32_t filter, int32_t dtype, int32_t channels, int32_t in_w, int32_t out_w);
@@ -132,7 +146,7 @@ hipError_t launch_batched(const void *ws, int32_t dtype, const BatchLaunch &l, h
 constexpr int64_t kStageMaxLds = 64 * 1024;
 hipError_t launch_batch_narrow(const void *ws, int32_t dtype, dim3 block, int32_t grid, hipStream_t stream);
 hipError_t launch_backward(const ResizeArgs &a, int32_t filter, int32_t dtype, int32_t channels,
-                           hipStream_t stream);
+                           hipStream_t stream, Route *only = nullptr);
 // False when the adjoint's smallest LDS tile cannot hold the output rows of
 // one source row and the column tables (upscales beyond roughly 190x rows or
 // a few hundred x columns).

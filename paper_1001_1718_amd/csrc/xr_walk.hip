@@ -510,7 +510,7 @@ constexpr bool walk_ppx_ok()
 }
 
 template <int FILTER, typename T, int C, int PPX>
-hipError_t launch_walk_ppx(const ResizeArgs &a, const xr_tile &tile, hipStream_t stream, bool &taken)
+hipError_t launch_walk_ppx(const ResizeArgs &a, const xr_tile &tile, hipStream_t stream, bool &taken, Route *only)
 {
     constexpr int K = Taps<FILTER>::K, PB = Pix<T, C>::kBytes;
     const int64_t row_bytes = walk_row_bytes(K, PB, PPX, a.in_w, a.out_w);
@@ -537,6 +537,8 @@ hipError_t launch_walk_ppx(const ResizeArgs &a, const xr_tile &tile, hipStream_t
     if (gy > 65535)
         return hipSuccess;
     taken = true;
+    if (just_named(only, kRouteWalk))
+        return hipSuccess;
     const int32_t cols_per_block = block_w * PPX;
     hipLaunchKernelGGL((k_walk<FILTER, T, C, PPX>),
                        dim3((a.out_w + cols_per_block - 1) / cols_per_block, static_cast<uint32_t>(gy), a.planes),
@@ -546,14 +548,14 @@ hipError_t launch_walk_ppx(const ResizeArgs &a, const xr_tile &tile, hipStream_t
 }
 
 template <int FILTER, typename T, int C>
-hipError_t launch_walk_typed(const ResizeArgs &a, const xr_tile &tile, hipStream_t stream, bool &taken)
+hipError_t launch_walk_typed(const ResizeArgs &a, const xr_tile &tile, hipStream_t stream, bool &taken, Route *only)
 {
     // the LDS strip shapes name the columns of a workgroup, not of a thread
     const int32_t ppx = tile.kernel == XR_KERNEL_STRIP_LDS ? walk_ppx(C, Pix<T, C>::kBytes) : tile.ppt_x;
 #define XR_WALK_CASE(P)                                                              \
     case P:                                                                          \
         if constexpr (walk_ppx_ok<FILTER, T, C, P>())                                        \
-            return launch_walk_ppx<FILTER, T, C, P>(a, tile, stream, taken);         \
+            return launch_walk_ppx<FILTER, T, C, P>(a, tile, stream, taken, only);   \
         return hipSuccess;
     switch (ppx) {
         XR_WALK_CASE(1)
@@ -569,18 +571,18 @@ hipError_t launch_walk_typed(const ResizeArgs &a, const xr_tile &tile, hipStream
 
 template <int FILTER>
 hipError_t launch_walk_filter(const ResizeArgs &a, int32_t dtype, int32_t channels, const xr_tile &tile,
-                              hipStream_t stream, bool &taken)
+                              hipStream_t stream, bool &taken, Route *only)
 {
     switch (dtype) {
     case XR_U8:
-        return channels == 4 ? launch_walk_typed<FILTER, uint8_t, 4>(a, tile, stream, taken)
-                             : launch_walk_typed<FILTER, uint8_t, 1>(a, tile, stream, taken);
+        return channels == 4 ? launch_walk_typed<FILTER, uint8_t, 4>(a, tile, stream, taken, only)
+                             : launch_walk_typed<FILTER, uint8_t, 1>(a, tile, stream, taken, only);
     case XR_F16:
-        return channels == 4 ? launch_walk_typed<FILTER, _Float16, 4>(a, tile, stream, taken)
-                             : launch_walk_typed<FILTER, _Float16, 1>(a, tile, stream, taken);
+        return channels == 4 ? launch_walk_typed<FILTER, _Float16, 4>(a, tile, stream, taken, only)
+                             : launch_walk_typed<FILTER, _Float16, 1>(a, tile, stream, taken, only);
     default:
-        return channels == 4 ? launch_walk_typed<FILTER, float, 4>(a, tile, stream, taken)
-                             : launch_walk_typed<FILTER, float, 1>(a, tile, stream, taken);
+        return channels == 4 ? launch_walk_typed<FILTER, float, 4>(a, tile, stream, taken, only)
+                             : launch_walk_typed<FILTER, float, 1>(a, tile, stream, taken, only);
     }
 }
 
@@ -619,13 +621,13 @@ void launch_kinds(const unsigned char *ws, dim3 block, const BatchLaunch &l, hip
 }  // namespace
 
 hipError_t launch_walk(const ResizeArgs &a, int32_t filter, int32_t dtype, int32_t channels, const xr_tile &tile,
-                       hipStream_t stream, bool &taken)
+                       hipStream_t stream, bool &taken, Route *only)
 {
     if (filter == XR_BICUBIC)
-        return launch_walk_filter<kBicubic>(a, dtype, channels, tile, stream, taken);
+        return launch_walk_filter<kBicubic>(a, dtype, channels, tile, stream, taken, only);
     if (filter == XR_NEAREST)
-        return launch_walk_filter<kNearest>(a, dtype, channels, tile, stream, taken);
-    return launch_walk_filter<kBilinear>(a, dtype, channels, tile, stream, taken);
+        return launch_walk_filter<kNearest>(a, dtype, channels, tile, stream, taken, only);
+    return launch_walk_filter<kBilinear>(a, dtype, channels, tile, stream, taken, only);
 }
 
 bool walk_fits(int32_t filter, int32_t dtype, int32_t channels, int32_t in_w, int32_t out_w)

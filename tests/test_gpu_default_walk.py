@@ -1,0 +1,106 @@
+"""GPU test of the walks at sizes where the default launch takes them, with the
+route asserted: the staged walk at its default shape (16 rows a strip down to
+one), the antialiased walk's one-column and many-samples forms, the adjoint
+walk with infinities. Every value must equal, bit for bit, the
+one-pixel-per-thread gather's (the adjoint: the oracle's pattern of infinite and
+undefined values, and the float64 sums within the suite's float32 bound
+elsewhere)."""
+
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+if not torch.cuda.is_available():
+    pytest.skip("no GPU", allow_module_level=True)
+
+import paper_1001_1718_amd as xr  # noqa: E402
+from gpu_util import check_f16_sum, check_f32  # noqa: E402
+from oracle import ref_resize as R  # noqa: E402
+from route_util import route, route_backward  # noqa: E402
+
+DEV = "cuda:0"
+GATHER = xr.tile(xr.XR_KERNEL_GATHER, 64, 4)
+AA_GATHER = xr.tile(xr.XR_KERNEL_GATHER, 32, 4)
+CODES = {torch.uint8: xr.XR_U8, torch.float16: xr.XR_F16, torch.float32: xr.XR_F32}
+
+
+def _data(shape, dtype, seed):
+    rng = np.random.default_rng(seed)
+    if dtype == torch.uint8:
+        return torch.from_numpy(rng.integers(0, 256, shape, dtype=np.uint8)).to(DEV)
+    x = torch.from_numpy(rng.standard_normal(shape).astype(np.float32)).to(dtype)
+    x.view(-1)[::4099] = float("inf")
+    return x.to(DEV)
+
+
+def _same(a, b):
+    return bool(((a == b) | ((a != a) & (b != b))).all())
+
+
+# (in_h, in_w, out_h, out_w), planes: growing, shrinking, shrinking past the
+# taps, one column tile more, and the edges' shapes in stacks
+DEFAULT = [((600, 500, 780, 650), 3), ((1500, 2100, 540, 756), 2), ((3000, 800, 430, 300), 5), ((900, 515, 1800, 513), 1),
+           ((1, 1, 5, 4), 500), ((3, 2, 7, 9), 400), ((19, 40, 25, 51), 100), ((90, 33, 13, 31), 200), ((12, 70, 75, 420), 30)]
+
+
+@pytest.mark.parametrize("mode", ["bilinear", "bicubic", "nearest"])
+@pytest.mark.parametrize("channels", [1, 4])
+@pytest.mark.parametrize("dtype", [torch.uint8, torch.float16, torch.float32])
+def test_default_launch_equals_gather(mode, channels, dtype):
+    for k, ((ih, iw, oh, ow), planes) in enumerate(DEFAULT):
+        assert route(mode, CODES[dtype], (ih, iw), (oh, ow), channels, planes) == "walk"
+        x = _data((planes, ih, iw + 3, channels), dtype, 700 + k)[:, :, 1:1 + iw]
+        out = torch.zeros((planes, oh, ow + 5, channels), dtype=dtype, device=DEV)
+        ref = torch.empty((planes, oh, ow, channels), dtype=dtype, device=DEV)
+        for mapping in ("half_pixel", "paper"):
+            xr.resize_into(x, ref, mode, tile=GATHER, mapping=mapping)
+            out.zero_()
+            xr.resize_into(x, out[:, :, 2:2 + ow], mode, mapping=mapping)
+            assert _same(out[:, :, 2:2 + ow], ref), (ih, iw, oh, ow, mapping)
+            assert not bool(out[:, :, :2].any()) and not bool(out[:, :, 2 + ow:].any())
+
+
+# one column; columns of 11 samples and more (24 of them, a tile, a tile and one)
+AA = [(9, 1, 6, 1), (30, 160, 7, 24), (20, 420, 5, 64), (20, 450, 5, 65), (12, 800, 11, 130)]
+
+
+@pytest.mark.parametrize("mode", ["bilinear_aa", "bicubic_aa"])
+@pytest.mark.parametrize("channels", [1, 4])
+@pytest.mark.parametrize("dtype", [torch.uint8, torch.float16, torch.float32])
+def test_antialiased_walk_equals_gather(mode, channels, dtype):
+    for k, (ih, iw, oh, ow) in enumerate(AA):
+        planes = -(-(1 << 18) // (oh * ow))
+        assert route(mode, CODES[dtype], (ih, iw), (oh, ow), channels, planes) == "aa walk"
+        x = _data((planes, ih, iw + 3, channels), dtype, 800 + k)[:, :, 1:1 + iw]
+        got, ref = (torch.empty((planes, oh, ow, channels), dtype=dtype, device=DEV) for _ in range(2))
+        xr.resize_into(x, got, mode)
+        xr.resize_into(x, ref, mode, tile=AA_GATHER)
+        assert _same(got, ref), (ih, iw, oh, ow)
+
+
+@pytest.mark.parametrize("mode", ["bilinear", "bicubic"])
+@pytest.mark.parametrize("channels", [1, 4])
+@pytest.mark.parametrize("dtype", [torch.float16, torch.float32])
+def test_adjoint_walk_with_infinities(mode, channels, dtype):
+    for k, (ih, iw, oh, ow) in enumerate([(40, 30, 60, 45), (40, 60, 30, 45), (60, 70, 9, 11)]):
+        planes = -(-(1 << 18) // (ih * iw))
+        assert route_backward(mode, CODES[dtype], (ih, iw), (oh, ow), channels, planes) == "adjoint walk"
+        g = _data((planes, oh, ow, channels), dtype, 900 + k)
+        got = xr.resize_backward(g, (ih, iw), mode, layout="hwc").float().cpu().numpy()
+        gp = g.float().cpu().numpy()
+        p = next(p for p in range(planes) if np.isinf(gp[p]).any())
+        code = {"bilinear": 0, "bicubic": 1}[mode]
+        with np.errstate(invalid="ignore"):
+            ref = R.adjoint(gp[p:p + 1], ih, iw, code)
+            scale = R.adjoint(gp[p:p + 1], ih, iw, code, absolute=True)
+        # infinity and undefined where a tap of weight zero or of both signs
+        # meets one; the taps are the same, so are the places
+        wild = ~np.isfinite(ref)
+        assert np.array_equal(~np.isfinite(got[p:p + 1]), wild), (ih, iw, oh, ow)
+        sure = wild & ~np.isnan(ref) & ~np.isnan(got[p:p + 1])
+        assert np.array_equal(got[p:p + 1][sure], ref[sure])
+        calm = ~wild
+        check = check_f32 if dtype == torch.float32 else check_f16_sum
+        check(got[p:p + 1][calm], ref[calm], scale[calm], what=f"adjoint walk {ih}x{iw}-{oh}x{ow}")

@@ -1,0 +1,68 @@
+"""Which kernel a call runs, on both sides of every rule of the dispatch (no GPU)."""
+
+import pytest
+
+import paper_1001_1718_amd as xr
+from route_util import SRC, route, route_backward
+
+U8, F16, F32 = xr.XR_U8, xr.XR_F16, xr.XR_F32
+MIB = 1 << 20
+
+FORWARD = [
+    # the exact-ratio kernels; on unaligned rows, under the printed map and for
+    # nearest neighbour the general ones; at very long pitches too
+    ("x2", dict(mode="bicubic", dtype=U8, in_hw=(4096, 4096), out_hw=(8192, 8192), channels=4)),
+    ("walk", dict(mode="bicubic", dtype=U8, in_hw=(4096, 4096), out_hw=(8192, 8192), src_data=SRC + 1)),
+    ("walk", dict(mode="bicubic", dtype=U8, in_hw=(4096, 4096), out_hw=(8192, 8192), channels=4, mapping="paper")),
+    ("walk", dict(mode="nearest", dtype=U8, in_hw=(4096, 4096), out_hw=(8192, 8192), channels=4)),
+    ("x05", dict(mode="bicubic", dtype=F16, in_hw=(4096, 4096), out_hw=(2048, 2048), channels=4)),
+    ("x2", dict(mode="bicubic", dtype=F32, in_hw=(64, 64), out_hw=(128, 128), dst_pitch=120 * MIB)),
+    ("strip", dict(mode="bicubic", dtype=F32, in_hw=(64, 64), out_hw=(128, 128), dst_pitch=128 * MIB)),
+    # small one-channel uint8 images at x2 (the x2 kernel moves dwords of source)
+    ("walk", dict(mode="bilinear", dtype=U8, in_hw=(512, 512), out_hw=(1024, 1024))),
+    # general ratios: the staged walk from 1700 runs of 256 columns (2100 of 128 RGBA pixels) on
+    ("walk", dict(mode="bicubic", dtype=U8, in_hw=(1500, 200), out_hw=(1700, 256))),
+    ("strip", dict(mode="bicubic", dtype=U8, in_hw=(1500, 200), out_hw=(1699, 256))),
+    ("walk", dict(mode="bicubic", dtype=F32, in_hw=(1500, 100), out_hw=(2100, 128), channels=4)),
+    ("strip", dict(mode="bicubic", dtype=F32, in_hw=(1500, 100), out_hw=(2099, 128), channels=4)),
+    ("walk", dict(mode="bicubic", dtype=F32, in_hw=(512, 512), out_hw=(768, 768), planes=48)),
+    ("walk", dict(mode="bicubic", dtype=F32, in_hw=(3000, 4000), out_hw=(1080, 1440), channels=4)),
+    # row pitches past 4 MiB, rows too long for LDS, outputs narrower than a run
+    ("walk", dict(mode="bicubic", dtype=U8, in_hw=(3000, 2000), out_hw=(4000, 2600), dst_pitch=4 * MIB)),
+    ("strip", dict(mode="bicubic", dtype=U8, in_hw=(3000, 2000), out_hw=(4000, 2600), dst_pitch=5 * MIB)),
+    ("strip", dict(mode="bicubic", dtype=F32, in_hw=(3000, 32000), out_hw=(4000, 3200), channels=4)),
+    ("strip", dict(mode="bicubic", dtype=U8, in_hw=(3000, 3), out_hw=(4000, 2))),
+    # named kernels
+    ("gather", dict(mode="bicubic", dtype=U8, in_hw=(512, 512), out_hw=(1024, 1024),
+                    tile=xr.tile(xr.XR_KERNEL_GATHER, 64, 4))),
+    ("strip", dict(mode="bicubic", dtype=U8, in_hw=(512, 512), out_hw=(1024, 1024),
+                   tile=xr.tile(xr.XR_KERNEL_STRIP_ANY, 64, 4, 8, 8))),
+    ("walk", dict(mode="bicubic", dtype=U8, in_hw=(700, 900), out_hw=(1000, 1300),
+                  tile=xr.tile(xr.XR_KERNEL_STRIP, 64, 4, 4, 8))),
+    ("error 11", dict(mode="bicubic", dtype=F32, in_hw=(4, 32768), out_hw=(4, 64),
+                      tile=xr.tile(xr.XR_KERNEL_STRIP_LDS, 512, 1, 8, 4))),
+    # antialiased: the walk from 2^18 results on, where rows shrink or stay; not
+    # for a few columns of many samples
+    ("aa walk", dict(mode="bilinear_aa", dtype=U8, in_hw=(700, 1024), out_hw=(512, 512))),
+    ("aa tile", dict(mode="bilinear_aa", dtype=U8, in_hw=(700, 1024), out_hw=(511, 512))),
+    ("aa walk", dict(mode="bicubic_aa", dtype=U8, in_hw=(512, 300), out_hw=(512, 600))),
+    ("aa tile", dict(mode="bicubic_aa", dtype=U8, in_hw=(511, 300), out_hw=(512, 600))),
+    ("aa walk", dict(mode="bilinear_aa", dtype=U8, in_hw=(60, 200), out_hw=(30, 24), planes=512)),
+    ("aa tile", dict(mode="bilinear_aa", dtype=U8, in_hw=(60, 200), out_hw=(30, 23), planes=512)),
+    ("aa gather", dict(mode="bicubic_aa", dtype=F32, in_hw=(8000, 500), out_hw=(20, 20), channels=4)),
+]
+
+
+@pytest.mark.parametrize("want, call", FORWARD)
+def test_forward_route(want, call):
+    assert route(**call) == want
+
+
+@pytest.mark.parametrize("want, call", [
+    ("adjoint x2", dict(mode="bilinear", dtype=F32, in_hw=(64, 64), out_hw=(128, 128))),
+    ("adjoint walk", dict(mode="bilinear", dtype=F32, in_hw=(512, 512), out_hw=(768, 768))),
+    ("adjoint owner", dict(mode="bilinear", dtype=F32, in_hw=(511, 512), out_hw=(768, 768))),
+    ("adjoint walk", dict(mode="bicubic", dtype=F16, in_hw=(480, 640), out_hw=(360, 480), channels=4)),
+])
+def test_adjoint_route(want, call):
+    assert route_backward(**call) == want
