@@ -322,10 +322,6 @@ std::map<TuneKey, xr_tile> g_tuned;
 // workgroups.
 // `exact`: the x2 and x0.5 kernels apply to those scales.
 constexpr double kWalkWaves = 220.0;  // per row of a strip
-// Outputs of fewer runs (of 256 columns, 128 of RGBA, in one row) take the
-// per-tap strips instead, which start without tables or staged rows (60
-// resizes: 0.60x to 0.96x their speed below, 1.0x to 4.4x above).
-constexpr int64_t kWalkLeastRuns1 = 1700, kWalkLeastRuns4 = 2100;
 xr_tile default_tile(int32_t filter, int32_t dtype, int32_t channels, int32_t in_w, int32_t in_h, int32_t out_w,
                      int32_t rows, int32_t out_h, int32_t planes, bool exact)
 {
@@ -345,8 +341,7 @@ xr_tile default_tile(int32_t filter, int32_t dtype, int32_t channels, int32_t in
         // rows, 3705 wavefronts; float32 RGBA x0.36 of 4000 x 3000 at 4 rows,
         // 6210; bilinear gray x2 of 512^2 at 4 rows, 1024)
         const int64_t cols = (static_cast<int64_t>(out_w) + 64 * t.ppt_x - 1) / (64 * t.ppt_x);
-        const int64_t runs = (static_cast<int64_t>(out_w) + (c4 ? 127 : 255)) / (c4 ? 128 : 256);
-        if (runs * rows * planes < (c4 ? kWalkLeastRuns4 : kWalkLeastRuns1)) {
+        if (!xr::walk_default(channels, out_w, rows, planes)) {
             t.kernel = XR_KERNEL_STRIP_ANY;
             t.block_h = 1;
             t.ppt_x = c4 ? 2 : 4;

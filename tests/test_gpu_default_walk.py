@@ -1,6 +1,6 @@
 """GPU test of the walks at sizes where the default launch takes them, with the
 route asserted: the staged walk at its default shape (16 rows a strip down to
-one), the antialiased walk's one-column and many-samples forms, the adjoint
+one) and at every run it is built for, the antialiased walk's one-column and many-samples forms, the adjoint
 walk with infinities. Every value must equal, bit for bit, the
 one-pixel-per-thread gather's (the adjoint: the oracle's pattern of infinite and
 undefined values, and the float64 sums within the suite's float32 bound
@@ -51,15 +51,19 @@ DEFAULT = [((600, 500, 780, 650), 3), ((1500, 2100, 540, 756), 2), ((3000, 800, 
 def test_default_launch_equals_gather(mode, channels, dtype):
     for k, ((ih, iw, oh, ow), planes) in enumerate(DEFAULT):
         assert route(mode, CODES[dtype], (ih, iw), (oh, ow), channels, planes) == "walk"
+        named = [xr.tile(xr.XR_KERNEL_STRIP, 64, 2, p, h, o) for p in (1, 2, 4, 8, 16) for h, o in ((1, 0), (37, 1))]
+        tiles = [t for t in named if route(mode, CODES[dtype], (ih, iw), (oh, ow), channels, planes, t) == "walk"]
+        assert len(tiles) >= 2
         x = _data((planes, ih, iw + 3, channels), dtype, 700 + k)[:, :, 1:1 + iw]
         out = torch.zeros((planes, oh, ow + 5, channels), dtype=dtype, device=DEV)
         ref = torch.empty((planes, oh, ow, channels), dtype=dtype, device=DEV)
         for mapping in ("half_pixel", "paper"):
             xr.resize_into(x, ref, mode, tile=GATHER, mapping=mapping)
-            out.zero_()
-            xr.resize_into(x, out[:, :, 2:2 + ow], mode, mapping=mapping)
-            assert _same(out[:, :, 2:2 + ow], ref), (ih, iw, oh, ow, mapping)
-            assert not bool(out[:, :, :2].any()) and not bool(out[:, :, 2 + ow:].any())
+            for t in [None] + tiles:
+                out.zero_()
+                xr.resize_into(x, out[:, :, 2:2 + ow], mode, tile=t, mapping=mapping)
+                assert _same(out[:, :, 2:2 + ow], ref), (ih, iw, oh, ow, mapping, t)
+                assert not bool(out[:, :, :2].any()) and not bool(out[:, :, 2 + ow:].any())
 
 
 # one column; columns of 11 samples and more (24 of them, a tile, a tile and one)

@@ -39,6 +39,19 @@ FORWARD = [
                    tile=xr.tile(xr.XR_KERNEL_STRIP_ANY, 64, 4, 8, 8))),
     ("walk", dict(mode="bicubic", dtype=U8, in_hw=(700, 900), out_hw=(1000, 1300),
                   tile=xr.tile(xr.XR_KERNEL_STRIP, 64, 4, 4, 8))),
+    # (on small outputs only where the walk is the faster one)
+    ("strip", dict(mode="bicubic", dtype=F16, in_hw=(600, 800), out_hw=(200, 270), channels=4,
+                   tile=xr.tile(xr.XR_KERNEL_STRIP, 64, 4, 2, 2))),
+    ("walk", dict(mode="bicubic", dtype=F16, in_hw=(600, 800), out_hw=(200, 270), channels=4, planes=4,
+                  tile=xr.tile(xr.XR_KERNEL_STRIP, 64, 4, 2, 2))),
+    ("strip", dict(mode="bicubic", dtype=F32, in_hw=(600, 800), out_hw=(200, 270),
+                   tile=xr.tile(xr.XR_KERNEL_STRIP, 64, 4, 4, 6))),
+    ("walk", dict(mode="bicubic", dtype=F32, in_hw=(600, 800), out_hw=(200, 270),
+                  tile=xr.tile(xr.XR_KERNEL_STRIP, 64, 4, 4, 2))),
+    ("walk", dict(mode="bicubic", dtype=U8, in_hw=(600, 800), out_hw=(200, 270),
+                  tile=xr.tile(xr.XR_KERNEL_STRIP, 64, 4, 4, 6))),
+    ("walk", dict(mode="bicubic", dtype=F32, in_hw=(200, 300), out_hw=(300, 450),
+                  tile=xr.tile(xr.XR_KERNEL_STRIP, 64, 4, 4, 6))),
     ("error 11", dict(mode="bicubic", dtype=F32, in_hw=(4, 32768), out_hw=(4, 64),
                       tile=xr.tile(xr.XR_KERNEL_STRIP_LDS, 512, 1, 8, 4))),
     # antialiased: the walk from 2^18 results on, where rows shrink or stay; not
