@@ -261,7 +261,7 @@ def headline(args, torch, xr, fields):
                     xr.tile(*(int(v) for v in args.tile.split(","))))
     elif not args.no_tune:
         cands = [c for c in xr.tune_candidates("bicubic", xr.XR_U8, ch, in_hw, in_hw, out_hw, out_hw)
-                 if c.kernel in (xr.XR_KERNEL_STRIP, xr.XR_KERNEL_STRIP_LDS)]
+                 if c.kernel == xr.XR_KERNEL_STRIP]
         t0 = time.perf_counter()
         tile, best_ms = xr.autotune(srcs, dsts, "bicubic", candidates=cands, reps=8, groups=3)
         tune = {"candidates": len(cands), "seconds": round(time.perf_counter() - t0, 2),
@@ -639,7 +639,7 @@ def configs(torch, xr, fields, steps: int = 50, warmup: int = 5, cpu: bool = Tru
         cands = None if (mode.endswith("_aa") or all_kinds) else [
             c for c in xr.tune_candidates(mode, xr._DTYPES[src0.dtype], chans, in_hw[1], in_hw[0],
                                           out_hw[1], out_hw[0])
-            if c.kernel in (xr.XR_KERNEL_STRIP, xr.XR_KERNEL_STRIP_LDS)]
+            if c.kernel in (xr.XR_KERNEL_STRIP, xr.XR_KERNEL_STRIP_ANY)]
         tile, _ = xr.autotune(srcs, dsts, mode, layout=layout, candidates=cands, reps=4, groups=3)
 
         def launch(i):
@@ -876,7 +876,7 @@ def paper_sweep(torch, xr, fields, reps: int = 10, groups: int = 3):
                                 reps=reps, groups=groups)
             times[f"gather {bw}x{bh}"] = ms
         strip = [c for c in xr.tune_candidates("bilinear", xr.XR_U8, 4, 800, 800, n, n)
-                 if c.kernel in (xr.XR_KERNEL_STRIP, xr.XR_KERNEL_STRIP_LDS)]
+                 if c.kernel in (xr.XR_KERNEL_STRIP, xr.XR_KERNEL_STRIP_ANY)]
         best_strip, ms = xr.autotune(srcs, dsts, "bilinear", candidates=strip, reps=reps, groups=groups)
         paper = {k: v for k, v in times.items() if tuple(int(x) for x in k.split()[1].split("x")) in PAPER_SHAPES}
         best_paper = min(paper, key=paper.get)

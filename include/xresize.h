@@ -304,12 +304,14 @@ int xr_resize_backward(const xr_image *grad_dst, const xr_image *grad_src, int32
  * may be NULL) and remembers it for later XR_KERNEL_AUTO calls with the same
  * key (filter, dtype, channels, the scale class of each axis: x2, identity,
  * other up, x0.5, other down; and the size class of the output's
- * width x height x planes pixels: up to 2^16, 2^20, 2^24, 2^26, beyond).
+ * width x height x planes pixels: up to 2^16, 2^20, 2^24, 2^26, beyond; outputs
+ * at general ratios too small for the staged walk's default are apart).
  * Overwrites the dsts.
- * candidates = NULL uses the built-in candidate list. Synchronises the
- * stream; NOT capturable.
+ * candidates = NULL uses the built-in candidate list, whose first is the shape
+ * that an untuned call takes: it is kept, and nothing remembered, unless
+ * another is more than 2% faster. Synchronises the stream; NOT capturable.
  * xr_tune_candidates: copies up to `cap` built-in candidates for the given
- * key into `out` and returns how many exist.
+ * key (images of one plane) into `out` and returns how many exist.
  */
 int xr_autotune(const xr_image *srcs, const xr_image *dsts, int32_t n_pairs, int32_t filter,
                 const xr_tile *candidates, int32_t n_candidates, int32_t reps, int32_t groups,

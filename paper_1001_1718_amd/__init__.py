@@ -248,7 +248,8 @@ def autotune(src, dst, mode="bicubic", layout="hwc", candidates=None, reps: int 
 
     ``src`` / ``dst`` are tensors or equally long lists of tensors; with lists
     the launches cycle through the pairs (use enough pairs to exceed the
-    caches). The winner is remembered for later launches with the same key.
+    caches). The winner is remembered for later launches with the same key; of
+    the built-in list only one that beats the untuned shape, which is part of it.
     """
     srcs = list(src) if isinstance(src, (list, tuple)) else [src]
     dsts = list(dst) if isinstance(dst, (list, tuple)) else [dst]

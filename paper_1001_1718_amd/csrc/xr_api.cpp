@@ -297,11 +297,16 @@ int size_class(int32_t out_w, int32_t out_h, int32_t planes)
 
 using TuneKey = std::tuple<int, int, int, int, int, int>;
 
+// Outputs at general ratios that are too small for the staged walk's default
+// are size classes of their own (5 more): the per-tap shapes that are best there
+// are several times slower than the walk just above, and the walk's slower below.
 TuneKey tune_key(int32_t filter, int32_t dtype, int32_t channels, int32_t in_w, int32_t in_h,
                  int32_t out_w, int32_t out_h, int32_t planes)
 {
-    return TuneKey(filter, dtype, channels, scale_class(in_w, out_w), scale_class(in_h, out_h),
-                   size_class(out_w, out_h, planes));
+    const int x = scale_class(in_w, out_w), y = scale_class(in_h, out_h);
+    const bool exact = filter != XR_NEAREST && x == y && (x == 0 || x == 3);
+    const bool small = !exact && !is_aa(filter) && !xr::walk_default(channels, out_w, out_h, std::max(planes, 1));
+    return TuneKey(filter, dtype, channels, x, y, size_class(out_w, out_h, planes) + (small ? 5 : 0));
 }
 
 std::mutex g_tune_mu;
@@ -515,24 +520,33 @@ int check_aa(const xr_tile &t, int32_t filter, const xr_image &src, const xr_ima
 // 368 x 3192 -> 58 x 507 31.4 and 39.6.
 xr_tile aa_default_tile(int32_t filter, const xr_image &src, const xr_image &dst)
 {
-    if (xr::antialiased_walk_supported(make_args(src, dst), filter, src.dtype, src.channels))
-        return xr_tile{XR_KERNEL_STRIP_LDS, 64, 4, 1, 1, 0};
+    // (the walk is the same launch for every block: one that may also be named)
+    const bool walk = xr::antialiased_walk_supported(make_args(src, dst), filter, src.dtype, src.channels);
     const int64_t groups = static_cast<int64_t>((dst.width + 63) / 64) * ((dst.rows + 3) / 4) * dst.planes;
     const int blocks[][2] = {{64, 4}, {16, 8}, {64, 2}, {32, 2}, {16, 2}};
     for (const auto &b : blocks) {
         const xr_tile t{XR_KERNEL_STRIP_LDS, b[0], b[1], 1, 1, 0};
-        if (b[1] == 4 && groups > 256 && aa_lds_bytes(t, filter, src, dst) > 80 * 1024)
+        if (!walk && b[1] == 4 && groups > 256 && aa_lds_bytes(t, filter, src, dst) > 80 * 1024)
             continue;
         if (aa_lds_bytes(t, filter, src, dst) <= xr::kAaLdsBudget)
             return t;
     }
-    return xr_tile{XR_KERNEL_GATHER, 64, 4, 1, 1, 0};
+    return walk ? xr_tile{XR_KERNEL_STRIP_LDS, 64, 4, 1, 1, 0} : xr_tile{XR_KERNEL_GATHER, 64, 4, 1, 1, 0};
 }
 
 bool lds_usable(const xr_tile &t, int32_t filter, const xr_image &src, const xr_image &dst)
 {
     return xr::strip_lds_fits(filter, src.dtype, src.channels, src.width, dst.width, t.block_w,
                               src_aligned4(src));
+}
+
+// The shape of an untuned call (antialiased: a strip shape, which means
+// aa_default_tile).
+xr_tile untuned_tile(int32_t filter, const xr_image &src, const xr_image &dst, int32_t mapping)
+{
+    const xr_tile strip{XR_KERNEL_STRIP, 64, 1, 1, 1, 0};
+    return default_tile(filter, src.dtype, src.channels, src.width, src.height, dst.width, dst.rows, dst.height,
+                        dst.planes, axis_mode(src, dst, strip, filter, mapping) != xr::kGeneral);
 }
 
 xr_tile resolve_tile(const xr_tile *tile, int32_t filter, const xr_image &src, const xr_image &dst, int32_t mapping)
@@ -551,9 +565,7 @@ xr_tile resolve_tile(const xr_tile *tile, int32_t filter, const xr_image &src, c
                           : (tt.kernel != XR_KERNEL_STRIP_LDS || lds_usable(tt, filter, src, dst)))
             return tt;
     }
-    const xr_tile strip{XR_KERNEL_STRIP, 64, 1, 1, 1, 0};
-    return default_tile(filter, src.dtype, src.channels, src.width, src.height, dst.width, dst.rows, dst.height,
-                        dst.planes, axis_mode(src, dst, strip, filter, mapping) != xr::kGeneral);
+    return untuned_tile(filter, src, dst, mapping);
 }
 
 int check_grid(const xr_tile &t, const xr_image &dst)
@@ -736,6 +748,88 @@ int32_t batch_lds(const xr_job *jobs, int32_t n_jobs, int32_t dtype, const xr_ti
     }
     const int64_t least = dtype != XR_U8 && out_bytes > int64_t(1) << 30 ? 53 * 1024 : 40 * 1024;
     return static_cast<int32_t>(std::max({most, least, std::min(waves * wave, xr::kStageMaxLds)}));
+}
+
+// ---- tuning -------------------------------------------------------------
+
+// An image of these sizes at no address, its rows and planes packed.
+xr_image packed_image(int32_t w, int32_t h, int32_t channels, int32_t dtype, int32_t planes)
+{
+    const int64_t pitch = static_cast<int64_t>(w) * channels * elem_size(dtype);
+    return xr_image{nullptr, w, h, channels, dtype, pitch, planes, planes > 1 ? pitch * h : 0, 0, h};
+}
+
+// The shapes that the tuner tries for a resize of src to dst: the one an
+// untuned call takes first, then the paper's block shapes and those of the
+// kernels that apply.
+std::vector<xr_tile> tune_candidates(int32_t filter, const xr_image &src, const xr_image &dst)
+{
+    const int32_t dtype = src.dtype, channels = src.channels;
+    std::vector<xr_tile> c;
+    // W x H threads, one pixel each: the paper's and a few wider ones
+    const int gather[][2] = {{8, 8}, {32, 4}, {32, 16}, {4, 8}, {8, 4}, {16, 16}, {64, 4}, {64, 1},
+                             {128, 2}, {256, 1}};
+    const auto gathers = [&] {
+        for (const auto &g : gather)
+            c.push_back(xr_tile{XR_KERNEL_GATHER, g[0], g[1], 1, 1, 0});
+    };
+    if (is_aa(filter)) {
+        c.push_back(aa_default_tile(filter, src, dst));
+        gathers();
+        // (every LDS block is one launch where the walk applies)
+        const int lds_blocks[][2] = {{16, 16}, {32, 8}, {64, 4}, {128, 2}, {32, 16}, {64, 8}, {128, 4},
+                                     {64, 16}, {256, 4}, {16, 8}, {64, 2}, {32, 2}, {16, 2}};
+        if (!xr::antialiased_walk_supported(make_args(src, dst), filter, dtype, channels))
+            for (const auto &b : lds_blocks)
+                c.push_back(xr_tile{XR_KERNEL_STRIP_LDS, b[0], b[1], 1, 1, 0});
+        return c;
+    }
+    c.push_back(untuned_tile(filter, src, dst, XR_MAP_HALF_PIXEL));
+    gathers();
+    const int ppx_c4[] = {1, 2, 4, 8}, ppx_c1[] = {4, 8, 16, 0};
+    const auto &ppx_list = channels == 4 ? ppx_c4 : ppx_c1;
+    const int blocks[][2] = {{64, 4}, {128, 2}, {256, 1}, {256, 2}, {512, 1}};
+    const auto strips = [&](int32_t kernel, const auto &rows, const auto &wanted, int orders) {
+        for (int ppx : ppx_list)
+            if (xr::strip_ppx_supported(dtype, channels, ppx) && wanted(ppx))
+                for (const auto &b : blocks)
+                    for (int order = 0; order < orders; ++order)
+                        for (int ppy : rows)
+                            c.push_back(xr_tile{kernel, b[0], b[1], ppx, ppy, order});
+    };
+    const bool x2 = dst.width == 2 * src.width && dst.height == 2 * src.height;
+    const bool x05 = 2 * dst.width == src.width && 2 * dst.height == src.height;
+    const auto several = [&](int ppx) { return channels == 1 || ppx > 1; };
+    if ((x2 || x05) && filter != XR_NEAREST) {
+        // the exact x2 walk: strips of 8 m rows (m pairs of rows per 4-row
+        // group of its loop); the exact x0.5 walk: strips of an even number
+        // of rows, and one RGBA column per thread as well (more wavefronts on
+        // its quarter-size output, so taller strips with less halo); both
+        // workgroup orders
+        const int x2_rows[] = {8, 16, 24, 32, 48, 64};
+        const int x05_rows[] = {2, 4, 6, 8, 12, 16, 24, 32};
+        if (x2)
+            strips(XR_KERNEL_STRIP, x2_rows, several, 2);
+        else
+            strips(XR_KERNEL_STRIP, x05_rows, [](int) { return true; }, 2);
+        return c;
+    }
+    // general ratios: the runs that the staged walk is built for, and the
+    // per-tap strips at the others; at all runs where the walk's rows do not
+    // fit, on outputs of up to twice the size that its default begins at, and
+    // for pixels of 8 and 16 bytes, whose per-tap strips are the faster ones
+    // while one pair of images stays in the caches (bicubic x0.36 of a 4000 x
+    // 3000 float32 RGBA photo: 32 us in 128x2 threads of 2 columns and 14 rows,
+    // the walk 41)
+    const int walk_rows[] = {1, 2, 4, 8, 16, 32, 64};
+    const int tap_rows[] = {1, 2, 6, 14, 22, 30, 46, 62};
+    const bool fits = xr::walk_fits(filter, dtype, channels, src.width, dst.width);
+    const bool taps = !fits || channels * elem_size(dtype) >= 8 ||
+                      !xr::walk_default(channels, dst.width, (dst.rows + 1) / 2, dst.planes);
+    const auto walks = [&](int ppx) { return fits && xr::walk_built(filter, dtype, channels, ppx); };
+    strips(XR_KERNEL_STRIP, walk_rows, walks, 2);
+    strips(XR_KERNEL_STRIP_ANY, tap_rows, [&](int ppx) { return several(ppx) && (taps || !walks(ppx)); }, 2);
+    return c;
 }
 
 // The current device's architecture name and compute-unit count (the key of
@@ -1201,78 +1295,10 @@ int32_t xr_internal_route_backward(const xr_image *grad_dst, const xr_image *gra
 int32_t xr_tune_candidates(int32_t filter, int32_t dtype, int32_t channels, int32_t in_w,
                            int32_t in_h, int32_t out_w, int32_t out_h, xr_tile *out, int32_t cap)
 {
-    (void)in_h;
-    (void)out_h;
-    std::vector<xr_tile> c;
-    // the paper's block shapes (W x H threads, one pixel each) and a few wider ones
-    const int gather[][2] = {{8, 8}, {32, 4}, {32, 16}, {4, 8}, {8, 4}, {16, 16}, {64, 4}, {64, 1},
-                             {128, 2}, {256, 1}};
-    for (const auto &g : gather)
-        c.push_back(xr_tile{XR_KERNEL_GATHER, g[0], g[1], 1, 1, 0});
-    if (is_aa(filter)) {  // the antialiased kernels: gather and LDS block shapes, one pixel each
-        const int lds_blocks[][2] = {{16, 16}, {32, 8}, {64, 4}, {128, 2}, {32, 16}, {64, 8},
-                                     {128, 4}, {64, 16}, {256, 4}, {64, 2}, {32, 2}, {16, 2}};
-        for (const auto &b : lds_blocks)
-            c.push_back(xr_tile{XR_KERNEL_STRIP_LDS, b[0], b[1], 1, 1, 0});
-        if (out)
-            for (int32_t k = 0; k < cap && k < static_cast<int32_t>(c.size()); ++k)
-                out[k] = c[k];
-        return static_cast<int32_t>(c.size());
-    }
-    // one RGBA column per thread only for the exact x0.5 walk (more waves on
-    // its quarter-size output, so taller strips with less halo)
-    const int ppx_c4[4] = {2, 4, 8, 1};
-    const int ppx_c1[4] = {4, 8, 16, 0};
-    const int *ppx_list = channels == 4 ? ppx_c4 : ppx_c1;
-    const int blocks[][2] = {{64, 4}, {128, 2}, {256, 1}, {256, 2}, {512, 1}};
-    const bool x2 = out_w == 2 * in_w && out_h == 2 * in_h;
-    const bool x05 = 2 * out_w == in_w && 2 * out_h == in_h;
-    if ((x2 || x05) && filter != XR_NEAREST) {
-        // the exact x2 walk: strips of 8 m rows (m pairs of rows per 4-row
-        // group of its loop); the exact x0.5 walk: strips of an even number
-        // of rows; both workgroup orders
-        const int x2_rows[] = {8, 16, 24, 32, 48, 64};
-        const int x05_rows[] = {2, 4, 6, 8, 12, 16, 24, 32};
-        for (int k = 0; k < (x05 ? 4 : 3); ++k) {
-            const int ppx = ppx_list[k];
-            if (!xr::strip_ppx_supported(dtype, channels, ppx))
-                continue;
-            for (const auto &b : blocks)
-                for (int order = 0; order < 2; ++order) {
-                    if (x2)
-                        for (int ppy : x2_rows)
-                            c.push_back(xr_tile{XR_KERNEL_STRIP, b[0], b[1], ppx, ppy, order});
-                    else
-                        for (int ppy : x05_rows)
-                            c.push_back(xr_tile{XR_KERNEL_STRIP, b[0], b[1], ppx, ppy, order});
-                }
-        }
-        if (out)
-            for (int32_t k = 0; k < cap && k < static_cast<int32_t>(c.size()); ++k)
-                out[k] = c[k];
-        return static_cast<int32_t>(c.size());
-    }
-    // strip heights 8m-2 make the x2 walk's source-row groups come out even;
-    // 1 and 2 rows give small images enough workgroups
-    const int ppy_list[] = {1, 2, 6, 14, 22, 30, 46, 62};
-    for (int k = 0; k < 3; ++k) {
-        const int ppx = ppx_list[k];
-        if (!xr::strip_ppx_supported(dtype, channels, ppx))
-            continue;
-        for (const auto &b : blocks)
-            for (int ppy : ppy_list)
-                for (int order = 0; order < 2; ++order)
-                    c.push_back(xr_tile{XR_KERNEL_STRIP, b[0], b[1], ppx, ppy, order});
-    }
-    // the LDS-staged walk, where one workgroup's row segment fits
-    const int lds_ppx = xr::kLdsPpx[channels == 4 ? 1 : 0];
-    for (int bw : {64, 128, 256, 512}) {
-        if (!xr::strip_lds_fits(filter, dtype, channels, in_w, out_w, bw, true))
-            continue;
-        for (int ppy : ppy_list)
-            for (int order = 0; order < 2; ++order)
-                c.push_back(xr_tile{XR_KERNEL_STRIP_LDS, bw, 1, lds_ppx, ppy, order});
-    }
+    const auto image = [&](int32_t w, int32_t h) {
+        return packed_image(std::max(w, 1), std::max(h, 1), channels, dtype, 1);
+    };
+    const std::vector<xr_tile> c = tune_candidates(filter, image(in_w, in_h), image(out_w, out_h));
     if (out)
         for (int32_t k = 0; k < cap && k < static_cast<int32_t>(c.size()); ++k)
             out[k] = c[k];
@@ -1308,27 +1334,20 @@ int xr_autotune(const xr_image *srcs, const xr_image *dsts, int32_t n_pairs, int
             return fail(XR_ERR_ARG, "n_candidates = %d", n_candidates);
         cand.assign(candidates, candidates + n_candidates);
     } else {
-        const int32_t n = xr_tune_candidates(filter, src->dtype, src->channels, src->width, src->height,
-                                             dst->width, dst->height, nullptr, 0);
-        cand.resize(n);
-        xr_tune_candidates(filter, src->dtype, src->channels, src->width, src->height, dst->width,
-                           dst->height, cand.data(), n);
-        // the built-in list assumes aligned sources and narrow weight tables;
-        // drop the shapes these sources cannot use
-        for (int32_t k = 0; k < n_pairs; ++k)
-            cand.erase(std::remove_if(cand.begin(), cand.end(),
+        cand = tune_candidates(filter, *src, *dst);
+        // antialiased blocks whose window does not fit (the untuned one runs)
+        if (is_aa(filter))
+            cand.erase(std::remove_if(cand.begin() + 1, cand.end(),
                                       [&](const xr_tile &t) {
-                                          if (is_aa(filter))
-                                              return aa_lds_bytes(t, filter, srcs[k], dsts[k]) >
-                                                     xr::kAaLdsBudget;
-                                          return t.kernel == XR_KERNEL_STRIP_LDS &&
-                                                 !lds_usable(t, filter, srcs[k], dsts[k]);
+                                          return aa_lds_bytes(t, filter, *src, *dst) > xr::kAaLdsBudget;
                                       }),
                        cand.end());
     }
     for (size_t k = 0; k < cand.size(); ++k) {
         if (cand[k].kernel == XR_KERNEL_AUTO)
             return fail(XR_ERR_ARG, "candidate %zu is XR_KERNEL_AUTO", k);
+        if (!candidates && k == 0 && cand[k].kernel == XR_KERNEL_STRIP_LDS)
+            continue;  // (the untuned antialiased walk has no window to fit)
         if (is_aa(filter)) {
             for (int32_t j = 0; j < n_pairs && !rc; ++j)
                 rc = check_aa(cand[k], filter, srcs[j], dsts[j]);
@@ -1355,16 +1374,14 @@ int xr_autotune(const xr_image *srcs, const xr_image *dsts, int32_t n_pairs, int
     for (int32_t k = 0; k < n_pairs; ++k)
         args[k] = make_args(srcs[k], dsts[k]);
     int32_t next = 0;
-    const auto launch = [&](const xr_tile &t, int32_t mode) {
-        const xr::ResizeArgs &a = args[next];
+    const auto launch = [&](const xr_tile &t) {
+        const int32_t k = next;
         next = (next + 1) % n_pairs;
-        return xr::launch_forward(a, filter, src->dtype, src->channels, t, mode, s);
+        return xr::launch_forward(args[k], filter, src->dtype, src->channels, t,
+                                  axis_mode(srcs[k], dsts[k], t, filter, XR_MAP_HALF_PIXEL), s);
     };
-    std::vector<int32_t> modes(cand.size());
-    for (size_t k = 0; k < cand.size(); ++k)
-        modes[k] = axis_mode(*src, *dst, cand[k], filter, XR_MAP_HALF_PIXEL);
     std::vector<float> med;
-    e = time_candidates(cand.size(), reps, groups, s, [&](size_t k) { return launch(cand[k], modes[k]); }, med);
+    e = time_candidates(cand.size(), reps, groups, s, [&](size_t k) { return launch(cand[k]); }, med);
     if (e != hipSuccess)
         return fail_hip(e, "timing a candidate");
     float best_t = 0.0f;
@@ -1377,10 +1394,33 @@ int xr_autotune(const xr_image *srcs, const xr_image *dsts, int32_t n_pairs, int
             best_k = k;
         }
     }
+    // A shape is kept for a whole class of sizes in place of the untuned rule,
+    // which looks at each: it has to be faster by more than such medians differ
+    // by themselves (2%), and in a second look at the two in turn as well.
+    constexpr float kTuneGain = 0.98f;
+    if (!candidates && best_k != 0) {
+        if (med[best_k] < kTuneGain * med[0]) {
+            std::vector<float> turn;
+            e = time_candidates(6, reps, groups, s,
+                                [&](size_t k) { return launch(cand[k % 2 ? best_k : 0]); }, turn);
+            if (e != hipSuccess)
+                return fail_hip(e, "timing a candidate");
+            const auto middle = [](float p, float q, float r) { return std::max(std::min(p, q), std::min(std::max(p, q), r)); };
+            med[0] = middle(turn[0], turn[2], turn[4]);
+            med[best_k] = middle(turn[1], turn[3], turn[5]);
+        }
+        if (med[best_k] >= kTuneGain * med[0])
+            best_k = 0;
+        best_t = med[best_k];
+    }
     {
         std::lock_guard<std::mutex> lock(g_tune_mu);
-        g_tuned[tune_key(filter, src->dtype, src->channels, src->width, src->height, dst->width,
-                         dst->height, dst->planes)] = cand[best_k];
+        const TuneKey key = tune_key(filter, src->dtype, src->channels, src->width, src->height, dst->width,
+                                     dst->height, dst->planes);
+        if (candidates || best_k != 0)
+            g_tuned[key] = cand[best_k];
+        else
+            g_tuned.erase(key);
     }
     if (best)
         *best = cand[best_k];

@@ -126,6 +126,8 @@ hipError_t launch_walk(const ResizeArgs &a, int32_t filter, int32_t dtype, int32
 // True when the walk with its own columns per thread (walk_ppx) can stage its
 // rows for an in_w -> out_w resize.
 bool walk_fits(int32_t filter, int32_t dtype, int32_t channels, int32_t in_w, int32_t out_w);
+// True when the walk is built for runs of ppx columns per thread.
+bool walk_built(int32_t filter, int32_t dtype, int32_t channels, int32_t ppx);
 
 // Launches of a prepared batch: workgroups per kind, LDS of those that walk.
 struct BatchLaunch {

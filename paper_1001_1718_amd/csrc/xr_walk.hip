@@ -502,11 +502,9 @@ namespace {
 
 // Output columns per thread that the walk is built for: runs of up to 16
 // bytes, and few enough that the ring of filtered rows stays in registers.
-template <int FILTER, typename T, int C, int PPX>
-constexpr bool walk_ppx_ok()
+constexpr bool walk_ppx_ok(int32_t taps, int32_t channels, int32_t pixel_bytes, int32_t ppx)
 {
-    return PPX * Pix<T, C>::kBytes <= 16 && (C == 4 ? PPX <= 4 : PPX >= 4) &&
-           PPX * C * Taps<FILTER>::K <= 32;
+    return ppx * pixel_bytes <= 16 && (channels == 4 ? ppx <= 4 : ppx >= 4) && ppx * channels * taps <= 32;
 }
 
 template <int FILTER, typename T, int C, int PPX>
@@ -565,7 +563,7 @@ hipError_t launch_walk_typed(const ResizeArgs &a, const xr_tile &tile, hipStream
     const int32_t ppx = tile.kernel == XR_KERNEL_STRIP_LDS ? walk_ppx(C, Pix<T, C>::kBytes) : tile.ppt_x;
 #define XR_WALK_CASE(P)                                                              \
     case P:                                                                          \
-        if constexpr (walk_ppx_ok<FILTER, T, C, P>())                                        \
+        if constexpr (walk_ppx_ok(Taps<FILTER>::K, C, Pix<T, C>::kBytes, P))             \
             return launch_walk_ppx<FILTER, T, C, P>(a, tile, stream, taken, only);   \
         return hipSuccess;
     switch (ppx) {
@@ -647,6 +645,12 @@ bool walk_fits(int32_t filter, int32_t dtype, int32_t channels, int32_t in_w, in
     const int32_t pb = (dtype == XR_U8 ? 1 : dtype == XR_F16 ? 2 : 4) * channels;
     const int32_t ppx = walk_ppx(channels, pb);
     return out_w >= ppx && 4 * walk_row_bytes(taps, pb, ppx, in_w, out_w) <= kWalkMaxWindow;
+}
+
+bool walk_built(int32_t filter, int32_t dtype, int32_t channels, int32_t ppx)
+{
+    return walk_ppx_ok(filter == XR_BICUBIC ? 4 : filter == XR_NEAREST ? 1 : 2, channels,
+                       (dtype == XR_U8 ? 1 : dtype == XR_F16 ? 2 : 4) * channels, ppx);
 }
 
 BatchWalkNeed batch_walk_need(const ResizeArgs &a, int32_t filter, int32_t dtype, int32_t channels, int32_t strip)
