@@ -213,7 +213,7 @@ int xr_resize(const xr_image *src, const xr_image *dst, int32_t filter, int32_t 
  *   the jobs by kind (filter x channel count; jobs narrower than one thread's
  *   run or shrinking too far along x form a fifth kind), splits every
  *   output into tiles of `tile` (NULL = the shape xr_batch_autotune chose for
- *   this dtype, else 128x2 threads with 8- to 24-row strips; block_w a multiple of
+ *   this dtype and size of batch, else 128x2 threads with 8- to 24-row strips; block_w a multiple of
  *   64, block_w * block_h <= 256, ppt_y <= 256; the output columns per
  *   thread are fixed per kind, tile.ppt_x is ignored), orders each kind's
  *   jobs largest-first, and uploads the job table and tile prefix sums to
@@ -258,12 +258,14 @@ int xr_resize_batched_static(const xr_job *jobs, int32_t n_jobs, const xr_tile *
 /*
  * Autotuner of the batched launch (the paper's tile-shape question, sections
  * III.A and IV, asked for a whole batch): prepares `dev_ws` with each
- * candidate shape in turn (NULL = built-in list: 64x4, 128x2 and 256x1
- * threads, strips of 4 to 190 rows; ppt_x is ignored), times `groups` groups
- * of `reps` launches with HIP events on `stream`, and keeps the shape with
- * the smallest median time per launch. On return `dev_ws` is prepared with
- * that shape, *best / *best_ms (either may be NULL) hold it, and later
- * xr_batch_prepare calls with tile = NULL and the same dtype use it.
+ * candidate shape in turn (NULL = built-in list: the untuned shape, and 64x4,
+ * 128x2 and 256x1 threads with strips of 4 to 190 rows; ppt_x is ignored), times
+ * `groups` groups of `reps` launches with HIP events on `stream`, and keeps the
+ * shape with the smallest median time per launch (of the built-in list the
+ * untuned one unless another, timed in turn with it, is 1% faster). On return `dev_ws` is
+ * prepared with that shape, *best / *best_ms (either may be NULL) hold it, and
+ * later xr_batch_prepare calls with tile = NULL, the same dtype and a batch whose
+ * untuned strips are as tall (8, 14 or 24 rows, by its size) use it.
  * Every timed launch writes every dst (the results do not depend on the
  * shape). Synchronises `stream`; NOT capturable (XR_ERR_CAPTURE). Errors as
  * xr_batch_prepare, plus XR_ERR_ARG for reps, groups or candidates < 1.
@@ -309,7 +311,7 @@ int xr_resize_backward(const xr_image *grad_dst, const xr_image *grad_src, int32
  * Overwrites the dsts.
  * candidates = NULL uses the built-in candidate list, whose first is the shape
  * that an untuned call takes: it is kept, and nothing remembered, unless
- * another is more than 2% faster. Synchronises the stream; NOT capturable.
+ * another, timed in turn with it, is 1% faster. Synchronises the stream; NOT capturable.
  * xr_tune_candidates: copies up to `cap` built-in candidates for the given
  * key (images of one plane) into `out` and returns how many exist.
  */

@@ -668,18 +668,9 @@ struct BatchInfo {
 };
 std::mutex g_batch_mu;
 std::map<const void *, BatchInfo> g_batches;
-std::map<int32_t, xr_tile> g_batch_tuned;  // dtype -> shape chosen by xr_batch_autotune
-
-// The shape xr_batch_autotune chose for a type, if any.
-bool batch_tuned_tile(int32_t dtype, xr_tile &t)
-{
-    std::lock_guard<std::mutex> lock(g_batch_mu);
-    auto it = g_batch_tuned.find(dtype);
-    if (it == g_batch_tuned.end())
-        return false;
-    t = it->second;
-    return true;
-}
+// (dtype, rows of the untuned strips, which grow with the batch) -> shape
+// chosen by xr_batch_autotune
+std::map<std::pair<int32_t, int32_t>, xr_tile> g_batch_tuned;
 
 // Untuned batched shape: 128 x 2 threads and strips as tall as leave the
 // batch enough wavefronts (a strip re-filters the source rows it shares with
@@ -751,6 +742,13 @@ int32_t batch_lds(const xr_job *jobs, int32_t n_jobs, int32_t dtype, const xr_ti
 }
 
 // ---- tuning -------------------------------------------------------------
+
+// A shape is kept for a whole class of calls in place of the untuned rule, which
+// looks at each: timed in turn with that rule's shape, the middle of three
+// medians has to be 1% faster (such middles of one shape differ by less: 256
+// images 961 to 964 us, single medians 960 to 967).
+constexpr float kTuneGain = 0.99f;
+float middle_of(float p, float q, float r) { return std::max(std::min(p, q), std::min(std::max(p, q), r)); }
 
 // An image of these sizes at no address, its rows and planes packed.
 xr_image packed_image(int32_t w, int32_t h, int32_t channels, int32_t dtype, int32_t planes)
@@ -951,6 +949,15 @@ hipError_t time_candidates(size_t n, int32_t reps, int32_t groups, hipStream_t s
     return e;
 }
 
+// The shape of a batch without a named tile.
+xr_tile batch_tile(const xr_job *jobs, int32_t n_jobs, int32_t dtype)
+{
+    const xr_tile untuned = batch_default_tile(jobs, n_jobs, dtype);
+    std::lock_guard<std::mutex> lock(g_batch_mu);
+    const auto it = g_batch_tuned.find({dtype, untuned.ppt_y});
+    return it != g_batch_tuned.end() ? it->second : untuned;
+}
+
 // Validates a batch and builds its workspace image (header and job table,
 // xr_batch_workspace_bytes(n_jobs) bytes) in host memory `host`; `order`
 // holds n_jobs indices of scratch. No device memory is touched.
@@ -965,7 +972,6 @@ int build_batch(const xr_job *jobs, int32_t n_jobs, const xr_tile *tile, unsigne
         if (t.kernel != XR_KERNEL_STRIP)
             return fail(XR_ERR_ARG, "the batched launch takes a strip tile");
     }
-    const bool tuned = !named && batch_tuned_tile(dtype, t);
     t.ppt_x = 0;  // fixed per job kind
     if (t.block_w < 64 || t.block_w % 64 != 0 || t.block_h < 1 || t.block_w * t.block_h > 256 ||
         t.ppt_y < 1 || t.ppt_y > xr::kBatchMaxStrip)
@@ -995,8 +1001,8 @@ int build_batch(const xr_job *jobs, int32_t n_jobs, const xr_tile *tile, unsigne
     if (cs != hipStreamCaptureStatusNone)
         return fail(XR_ERR_CAPTURE, "%s called on a capturing stream", caller);
 
-    if (!named && !tuned)
-        t = batch_default_tile(jobs, n_jobs, dtype);
+    if (!named)
+        t = batch_tile(jobs, n_jobs, dtype);
     // grouped by kind, largest output first within a kind
     const auto fc_of = [&](const xr_job &j) {
         return (j.filter == XR_BICUBIC ? 2 : 0) + (j.src.channels == 4 ? 1 : 0);
@@ -1209,6 +1215,10 @@ int xr_batch_autotune(const xr_job *jobs, int32_t n_jobs, const xr_tile *candida
     int rc = xr_batch_prepare(jobs, n_jobs, &cand[0], dev_ws, ws_bytes, stream);
     if (rc)
         return rc;
+    const int32_t dtype = jobs[0].src.dtype;
+    const xr_tile untuned = batch_default_tile(jobs, n_jobs, dtype);
+    if (!candidates)
+        cand.insert(cand.begin(), untuned);
     hipEvent_t ev0, ev1;
     hipError_t e = hipEventCreate(&ev0);
     if (e != hipSuccess)
@@ -1218,14 +1228,11 @@ int xr_batch_autotune(const xr_job *jobs, int32_t n_jobs, const xr_tile *candida
         return fail_hip(e, "hipEventCreate");
     }
     std::vector<float> per_group(groups);
-    float best_t = 0.0f;
-    size_t best_k = 0;
-    bool have = false;
-    for (size_t k = 0; k < cand.size() && rc == XR_OK && e == hipSuccess; ++k) {
+    // the median time of a launch in shape k; rc and e tell of errors
+    const auto median = [&](size_t k) {
         rc = xr_batch_prepare(jobs, n_jobs, &cand[k], dev_ws, ws_bytes, stream);
-        if (rc)
-            break;
-        rc = xr_resize_batched(dev_ws, n_jobs, stream);  // warm-up
+        if (rc == XR_OK)
+            rc = xr_resize_batched(dev_ws, n_jobs, stream);  // warm-up
         for (int32_t g = 0; g < groups && rc == XR_OK && e == hipSuccess; ++g) {
             e = hipEventRecord(ev0, s);
             for (int32_t r = 0; r < reps && rc == XR_OK && e == hipSuccess; ++r)
@@ -1239,14 +1246,28 @@ int xr_batch_autotune(const xr_job *jobs, int32_t n_jobs, const xr_tile *candida
                 e = hipEventElapsedTime(&ms, ev0, ev1);
             per_group[g] = ms / static_cast<float>(reps);
         }
-        if (rc != XR_OK || e != hipSuccess)
-            break;
         std::sort(per_group.begin(), per_group.end());
-        const float med = per_group[groups / 2];
-        if (!have || med < best_t) {
+        return per_group[groups / 2];
+    };
+    float best_t = 0.0f;
+    size_t best_k = 0;
+    for (size_t k = 0; k < cand.size() && rc == XR_OK && e == hipSuccess; ++k) {
+        const float med = median(k);
+        if (k == 0 || med < best_t) {
             best_t = med;
             best_k = k;
-            have = true;
+        }
+    }
+    // in place of the untuned shape only what beats it in turn
+    if (!candidates && best_k != 0 && rc == XR_OK && e == hipSuccess) {
+        float turn[6] = {};
+        for (int i = 0; i < 6 && rc == XR_OK && e == hipSuccess; ++i)
+            turn[i] = median(i % 2 ? best_k : 0);
+        const float first_t = middle_of(turn[0], turn[2], turn[4]);
+        best_t = middle_of(turn[1], turn[3], turn[5]);
+        if (best_t >= kTuneGain * first_t) {
+            best_k = 0;
+            best_t = first_t;
         }
     }
     (void)hipEventDestroy(ev0);
@@ -1260,7 +1281,10 @@ int xr_batch_autotune(const xr_job *jobs, int32_t n_jobs, const xr_tile *candida
         return rc;
     {
         std::lock_guard<std::mutex> lock(g_batch_mu);
-        g_batch_tuned[jobs[0].src.dtype] = cand[best_k];
+        if (candidates || best_k != 0)
+            g_batch_tuned[{dtype, untuned.ppt_y}] = cand[best_k];
+        else
+            g_batch_tuned.erase({dtype, untuned.ppt_y});
     }
     if (best)
         *best = cand[best_k];
@@ -1394,21 +1418,14 @@ int xr_autotune(const xr_image *srcs, const xr_image *dsts, int32_t n_pairs, int
             best_k = k;
         }
     }
-    // A shape is kept for a whole class of sizes in place of the untuned rule,
-    // which looks at each: it has to be faster by more than such medians differ
-    // by themselves (2%), and in a second look at the two in turn as well.
-    constexpr float kTuneGain = 0.98f;
+    // in place of the untuned shape only what beats it in turn
     if (!candidates && best_k != 0) {
-        if (med[best_k] < kTuneGain * med[0]) {
-            std::vector<float> turn;
-            e = time_candidates(6, reps, groups, s,
-                                [&](size_t k) { return launch(cand[k % 2 ? best_k : 0]); }, turn);
-            if (e != hipSuccess)
-                return fail_hip(e, "timing a candidate");
-            const auto middle = [](float p, float q, float r) { return std::max(std::min(p, q), std::min(std::max(p, q), r)); };
-            med[0] = middle(turn[0], turn[2], turn[4]);
-            med[best_k] = middle(turn[1], turn[3], turn[5]);
-        }
+        std::vector<float> turn;
+        e = time_candidates(6, reps, groups, s, [&](size_t k) { return launch(cand[k % 2 ? best_k : 0]); }, turn);
+        if (e != hipSuccess)
+            return fail_hip(e, "timing a candidate");
+        med[0] = middle_of(turn[0], turn[2], turn[4]);
+        med[best_k] = middle_of(turn[1], turn[3], turn[5]);
         if (med[best_k] >= kTuneGain * med[0])
             best_k = 0;
         best_t = med[best_k];

@@ -1,6 +1,6 @@
 """GPU test of the tuner's built-in list: whatever it keeps (the untuned shape or
 a stored one), later calls give the same bits, and the shape that it reports is
-the one they resolve to."""
+the one they resolve to; a shape tuned on one size of batch is not another's."""
 
 import pytest
 
@@ -40,3 +40,28 @@ def test_autotune_keeps_results(mode, dtype, channels, in_hw, out_hw):
         assert torch.equal(xr.resize(x, out_hw, mode, tile=best), before)
     finally:
         xr.set_tile(*key, xr.tile(xr.XR_KERNEL_AUTO))
+
+
+def _shape(batch):
+    """block_w, block_h and strip rows that a batch was prepared with."""
+    at = batch.ws_ptr - batch.workspace.data_ptr()
+    return batch.workspace[at:at + 24].cpu().view(torch.int32)[2:5].tolist()
+
+
+def test_batch_shapes_are_kept_per_size_of_batch():
+    def pairs(side):  # float32 RGBA: a wavefront covers 64 columns
+        x = torch.rand((64, 64, 4), device=DEV)
+        return [(x, torch.empty((side, side, 4), device=DEV), "bilinear")]
+
+    small, large = pairs(300), pairs(8192)  # 65 and 43,776 wavefronts at 24 rows
+    untuned = _shape(xr.Batch(large))
+    b = xr.Batch(small)
+    ref = xr.resize(small[0][0], (300, 300))
+    b.autotune(candidates=[xr.tile(xr.XR_KERNEL_STRIP, 64, 3, 0, 5)], reps=1, groups=1)
+    assert _shape(xr.Batch(small)) == [64, 3, 5] and _shape(xr.Batch(large)) == untuned == [128, 2, 24]
+    best, _ = b.autotune(reps=2, groups=3)
+    again = xr.Batch(small)
+    assert _shape(again) == [best.block_w, best.block_h, best.ppt_y]
+    small[0][1].zero_()
+    again.run()
+    assert torch.equal(small[0][1], ref)
