@@ -112,18 +112,21 @@ typedef struct {
  *                               Other scales run the staged walk where its
  *                               rows fit in LDS (source rows staged there a
  *                               wavefront at a time, strips of at most 256
- *                               rows), else the per-tap strip kernel.
+ *                               rows) and the output is large enough for it,
+ *                               else the per-tap strip kernel.
  *         = XR_KERNEL_STRIP_ANY : the per-tap strip kernel at every scale
  *                               (the same results; for comparisons)
  *         = XR_KERNEL_STRIP_LDS : the staged walk with its own columns per
- *                               thread
- *                               (any scale; block_h = 1, block_w a multiple of
- *                               64 up to 512, ppt_x = 4 for 4 channels and 8
- *                               for one). XR_ERR_ARG when one workgroup's row
- *                               segment does not fit its LDS budget (strong
- *                               downscales with wide workgroups). With the
- *                               antialiased filters of xr_resize: the
- *                               LDS-tiled separable kernel (see there)
+ *                               thread (any scale; block_h = 1, block_w a
+ *                               multiple of 64 up to 512, ppt_x = 4 for 4
+ *                               channels and 8 for one). XR_ERR_ARG when the
+ *                               source row segment of block_w * ppt_x columns
+ *                               passes 64 bytes a thread or a third of 64 KiB
+ *                               (strong downscales with wide workgroups), or
+ *                               pixels of under 4 bytes lie in rows that are
+ *                               not whole 4-byte words. With the antialiased
+ *                               filters of xr_resize: the LDS-tiled separable
+ *                               kernel (see there)
  *  order  = 0 : tiles are processed in launch order (row-major)
  *         = 1 : the launch is split into 8 contiguous bands of tiles, one per
  *               XCD (the hardware deals workgroups to the 8 XCDs in turn), so
@@ -353,9 +356,13 @@ int xr_tune_load(const char *path, int32_t *n_loaded);
  *   [row0, row0 + rows) read (pixel-centre map; XR_BILINEAR or XR_BICUBIC).
  * xr_needed_rows_map: the same for any filter of xr_resize and either map.
  * xr_thread_of_pixel: eq. 6 inverted for a tile shape: the workgroup
- *   (block_x, block_y) and the thread (thread_x, thread_y) that compute output
- *   pixel (px, py), plus the pixel's index within that thread's ppt_x x ppt_y
- *   group (sub_x, sub_y).
+ *   (block_x, block_y) and the thread (thread_x, thread_y) to which the shape's
+ *   division of the image gives output pixel (px, py), plus the pixel's index
+ *   within that thread's ppt_x x ppt_y group (sub_x, sub_y). XR_KERNEL_GATHER and
+ *   XR_KERNEL_STRIP_ANY launches compute it there in launch order (order = 0);
+ *   the kernels of exact ratios, the staged walk and the antialiased walk
+ *   divide the image into strips of their own (XR_KERNEL_STRIP_LDS also into
+ *   columns).
  */
 int xr_source_taps(int32_t n_in, int32_t n_out, int32_t x, int32_t *x0, int64_t *t_num,
                    int64_t *t_den);

@@ -212,7 +212,7 @@ int check_pair(const xr_image *src, const xr_image *dst, int32_t filter,
 }
 
 // The source base and pitches are 4-byte aligned and a row is a whole number
-// of 4-byte words (the LDS strip kernel then stages small pixels as words).
+// of 4-byte words (what XR_KERNEL_STRIP_LDS asks of small pixels).
 bool src_aligned4(const xr_image &src)
 {
     const int64_t row_bytes = static_cast<int64_t>(src.width) * src.channels * elem_size(src.dtype);
@@ -242,7 +242,6 @@ xr::ResizeArgs make_args(const xr_image &src, const xr_image &dst, int32_t mappi
         return reinterpret_cast<uintptr_t>(p) % 16 == 0 && v1 % 16 == 0 && v2 % 16 == 0;
     };
     a.aligned16 = al(src.data, a.src_pitch, a.src_plane_pitch) && al(dst.data, a.dst_pitch, a.dst_plane_pitch);
-    a.aligned4 = src_aligned4(src);
     a.map_off = mapping == XR_MAP_HALF_PIXEL ? 1 : 0;
     return a;
 }
@@ -415,6 +414,9 @@ xr_tile default_tile(int32_t filter, int32_t dtype, int32_t channels, int32_t in
     return t;
 }
 
+// ppt_x of an XR_KERNEL_STRIP_LDS tile: {one channel, four}
+constexpr int32_t kLdsPpx[2] = {8, 4};
+
 int check_tile(const xr_tile &t, int32_t dtype, int32_t channels)
 {
     if (t.kernel == XR_KERNEL_GATHER) {
@@ -446,7 +448,7 @@ int check_tile(const xr_tile &t, int32_t dtype, int32_t channels)
                         t.block_w, t.block_h);
         if (t.order != 0 && t.order != 1)
             return fail(XR_ERR_ARG, "tile.order = %d (must be 0 or 1)", t.order);
-        const int32_t ppx = xr::kLdsPpx[channels == 4 ? 1 : 0];
+        const int32_t ppx = kLdsPpx[channels == 4 ? 1 : 0];
         if (t.ppt_x != ppx)
             return fail(XR_ERR_ARG, "LDS strip ppt_x = %d (must be %d for %d channels)", t.ppt_x, ppx,
                         channels);
@@ -458,15 +460,29 @@ int check_tile(const xr_tile &t, int32_t dtype, int32_t channels)
     return fail(XR_ERR_ARG, "tile.kernel = %d unknown", t.kernel);
 }
 
-// The LDS-staged strip kernel stages one workgroup's source row segment; it
-// must fit the kernel's LDS and register budget for this scale.
-// `aligned4` is unknown (taken as true) where only sizes are given.
+// The calls that XR_KERNEL_STRIP_LDS is documented to take: a workgroup's
+// bw ppt_x columns read at most floor((cols - 1) in_w / out_w) + K + 1 source
+// pixels of a row (x0(c2) - x0(c1) <= floor((c2 - c1) in_w / out_w) + 1, eqs.
+// 1-4), in chunks of a pixel or 4-byte words, of which a lane holds up to 64
+// bytes and three rows 64 KiB. (The walk that runs them stages rows a wavefront
+// at a time and has no such limit; the refusals are the interface's.) `aligned4`
+// is unknown (taken as true) where only sizes are given.
+bool lds_usable(const xr_tile &t, int32_t filter, int32_t dtype, int32_t channels, int32_t in_w, int32_t out_w,
+                bool aligned4)
+{
+    const int64_t px = static_cast<int64_t>(elem_size(dtype)) * channels, chunk = std::max<int64_t>(px, 4);
+    const int64_t cols = std::min<int64_t>(static_cast<int64_t>(t.block_w) * kLdsPpx[channels == 4 ? 1 : 0], out_w);
+    const int64_t seg = (cols - 1) * in_w / out_w + taps_of(filter) + 1;
+    const int64_t chunks = (seg * px + (chunk - px) + chunk - 1) / chunk;
+    return (chunks + t.block_w - 1) / t.block_w <= 64 / chunk && 3 * ((chunks * chunk + 15) / 16 * 16) <= 64 * 1024 &&
+           (px >= 4 || aligned4);
+}
 int check_lds(const xr_tile &t, int32_t filter, int32_t dtype, int32_t channels, int32_t in_w,
               int32_t out_w, bool aligned4 = true)
 {
     if (t.kernel != XR_KERNEL_STRIP_LDS)
         return XR_OK;
-    if (!xr::strip_lds_fits(filter, dtype, channels, in_w, out_w, t.block_w, aligned4))
+    if (!lds_usable(t, filter, dtype, channels, in_w, out_w, aligned4))
         return fail(XR_ERR_ARG,
                     "LDS strip: a %d-thread workgroup's row segment for %d -> %d columns does not fit "
                     "(or one-channel source rows are not 4-byte aligned words); use a narrower "
@@ -534,12 +550,6 @@ xr_tile aa_default_tile(int32_t filter, const xr_image &src, const xr_image &dst
     return walk ? xr_tile{XR_KERNEL_STRIP_LDS, 64, 4, 1, 1, 0} : xr_tile{XR_KERNEL_GATHER, 64, 4, 1, 1, 0};
 }
 
-bool lds_usable(const xr_tile &t, int32_t filter, const xr_image &src, const xr_image &dst)
-{
-    return xr::strip_lds_fits(filter, src.dtype, src.channels, src.width, dst.width, t.block_w,
-                              src_aligned4(src));
-}
-
 // The shape of an untuned call (antialiased: a strip shape, which means
 // aa_default_tile).
 xr_tile untuned_tile(int32_t filter, const xr_image &src, const xr_image &dst, int32_t mapping)
@@ -562,7 +572,8 @@ xr_tile resolve_tile(const xr_tile *tile, int32_t filter, const xr_image &src, c
     if (it != g_tuned.end()) {
         const xr_tile &tt = it->second;
         if (is_aa(filter) ? aa_lds_bytes(tt, filter, src, dst) <= xr::kAaLdsBudget
-                          : (tt.kernel != XR_KERNEL_STRIP_LDS || lds_usable(tt, filter, src, dst)))
+                          : (tt.kernel != XR_KERNEL_STRIP_LDS ||
+                             lds_usable(tt, filter, src.dtype, src.channels, src.width, dst.width, src_aligned4(src))))
             return tt;
     }
     return untuned_tile(filter, src, dst, mapping);

@@ -337,39 +337,6 @@ __global__ void __launch_bounds__(512) k_strip(ResizeArgs a, int32_t strip_h, in
 }
 
 // ---------------------------------------------------------------------------
-// k_strip_lds (any scale, each source row staged once per workgroup in LDS)
-// ---------------------------------------------------------------------------
-
-// Staging plan of the LDS strip walk. A lane moves CB-byte chunks: whole
-// pixels of 4 bytes or more, else aligned 4-byte words (which needs a 4-byte
-// aligned source with rows of a whole number of words). One workgroup of bw
-// threads covers cols = min(bw * PPX, out_w) output columns and reads a
-// segment of at most seg_max = floor((cols - 1) * in_w / out_w) + K + 1
-// source pixels,
-// since x0(c2) - x0(c1) <= floor((c2 - c1) * in_w / out_w) + 1 (eqs. 1-4);
-// with the word alignment slack that is at most `chunks` chunks, `need`
-// chunks per lane, in an LDS row buffer of `buf_bytes`.
-template <int FILTER, typename T, int C, int PPX>
-struct LdsPlan {
-    static constexpr int K = Taps<FILTER>::K;
-    static constexpr int PB = Pix<T, C>::kBytes;
-    static constexpr int CB = PB < 4 ? 4 : PB;
-    static constexpr int MAX_CH = 64 / CB;  // registers for one row's chunks
-    int64_t chunks, need, buf_bytes;
-    bool ok;
-    LdsPlan(int32_t in_w, int32_t out_w, int32_t bw, bool aligned4)
-    {
-        const int64_t cols = std::min<int64_t>(static_cast<int64_t>(bw) * PPX, out_w);
-        const int64_t seg = (cols - 1) * in_w / out_w + K + 1;
-        chunks = (seg * PB + (CB - PB) + CB - 1) / CB;
-        need = (chunks + bw - 1) / bw;
-        buf_bytes = (chunks * CB + 15) / 16 * 16;
-        ok = need <= MAX_CH && 3 * buf_bytes <= static_cast<int64_t>(kLdsBudget) &&
-             (PB >= 4 || aligned4);
-    }
-};
-
-// ---------------------------------------------------------------------------
 // edge runs of the exact-ratio walks
 // ---------------------------------------------------------------------------
 //
@@ -875,42 +842,6 @@ hipError_t launch_batch_narrow(const void *ws, int32_t dtype, dim3 block, int32_
 // ---------------------------------------------------------------------------
 // dispatch
 // ---------------------------------------------------------------------------
-
-namespace {
-template <int FILTER, typename T, int C>
-bool lds_fits(int32_t in_w, int32_t out_w, int32_t block_w, bool aligned4)
-{
-    return LdsPlan<FILTER, T, C, kLdsPpx[C == 4 ? 1 : 0]>(in_w, out_w, block_w, aligned4).ok;
-}
-template <int FILTER>
-bool lds_fits_filter(int32_t dtype, int32_t channels, int32_t in_w, int32_t out_w, int32_t block_w,
-                     bool aligned4)
-{
-    switch (dtype) {
-    case XR_U8:
-        return channels == 4 ? lds_fits<FILTER, uint8_t, 4>(in_w, out_w, block_w, aligned4)
-                             : lds_fits<FILTER, uint8_t, 1>(in_w, out_w, block_w, aligned4);
-    case XR_F16:
-        return channels == 4 ? lds_fits<FILTER, _Float16, 4>(in_w, out_w, block_w, aligned4)
-                             : lds_fits<FILTER, _Float16, 1>(in_w, out_w, block_w, aligned4);
-    case XR_F32:
-        return channels == 4 ? lds_fits<FILTER, float, 4>(in_w, out_w, block_w, aligned4)
-                             : lds_fits<FILTER, float, 1>(in_w, out_w, block_w, aligned4);
-    default:
-        return false;
-    }
-}
-}  // namespace
-
-bool strip_lds_fits(int32_t filter, int32_t dtype, int32_t channels, int32_t in_w, int32_t out_w,
-                    int32_t block_w, bool aligned4)
-{
-    if (filter == XR_BICUBIC)
-        return lds_fits_filter<kBicubic>(dtype, channels, in_w, out_w, block_w, aligned4);
-    if (filter == XR_NEAREST)
-        return lds_fits_filter<kNearest>(dtype, channels, in_w, out_w, block_w, aligned4);
-    return lds_fits_filter<kBilinear>(dtype, channels, in_w, out_w, block_w, aligned4);
-}
 
 bool strip_ppx_supported(int32_t dtype, int32_t channels, int32_t ppx)
 {

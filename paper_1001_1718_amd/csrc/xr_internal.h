@@ -26,8 +26,6 @@ struct ResizeArgs {
     int32_t dst_rows;        // number of output rows to compute
     int32_t planes;
     int32_t aligned16;       // src, dst and pitches are 16-byte aligned
-    int32_t aligned4;        // src and its pitches are 4-byte aligned and a
-                             // source row is a whole number of 4-byte words
     int32_t map_off;         // 1: pixel-centre map; 0: the map eq. 1 prints
 };
 
@@ -209,15 +207,5 @@ inline AaPlan aa_tile_plan(int32_t in_w, int32_t in_h, int32_t out_w, int32_t ou
 
 // Pixels per thread along x that the strip kernel is instantiated for.
 bool strip_ppx_supported(int32_t dtype, int32_t channels, int32_t ppx);
-// Columns per thread of the LDS-staged strip kernel: {one channel, four}.
-constexpr int32_t kLdsPpx[2] = {8, 4};
-// Dynamic LDS of the LDS-staged strip kernel (three row buffers) is kept
-// within this many bytes per workgroup.
-constexpr size_t kLdsBudget = 64 * 1024;
-// True when a workgroup of block_w threads of the LDS-staged strip kernel can
-// stage its source row segment for an in_w -> out_w resize (`aligned4` as in
-// ResizeArgs; pixels of fewer than 4 bytes are staged as 4-byte words).
-bool strip_lds_fits(int32_t filter, int32_t dtype, int32_t channels, int32_t in_w, int32_t out_w,
-                    int32_t block_w, bool aligned4);
 
 }  // namespace xr

@@ -79,3 +79,26 @@ def test_forward_route(want, call):
 ])
 def test_adjoint_route(want, call):
     assert route_backward(**call) == want
+
+
+def test_lds_tiles_are_taken_as_documented():
+    """XR_KERNEL_STRIP_LDS: the row segment of a workgroup's bw ppt_x columns, in
+    chunks of 4 bytes or a pixel, needs at most 64 bytes a lane and 64 KiB for
+    three rows; pixels under 4 bytes lie in rows of whole words."""
+    taken = refused = 0
+    for mode, taps in (("nearest", 1), ("bilinear", 2), ("bicubic", 4)):
+        for dtype, size in ((U8, 1), (F16, 2), (F32, 4)):
+            for channels, ppx in ((1, 8), (4, 4)):
+                for bw in (64, 192, 512):
+                    for in_w, out_w in ((37, 74), (36, 75), (300, 40), (4096, 300), (32768, 64), (640, 5600), (8192, 1100)):
+                        px = size * channels
+                        chunk = max(px, 4)
+                        seg = (min(bw * ppx, out_w) - 1) * in_w // out_w + taps + 1
+                        chunks = -(-(seg * px + chunk - px) // chunk)
+                        fits = (-(-chunks // bw) <= 64 // chunk and 3 * (-(-chunks * chunk // 16) * 16) <= 65536 and
+                                (px >= 4 or in_w * px % 4 == 0))
+                        got = route(mode, dtype, (50, in_w), (70, out_w), channels,
+                                    tile=xr.tile(xr.XR_KERNEL_STRIP_LDS, bw, 1, ppx, 6))
+                        assert fits == (got != "error 11")
+                        taken, refused = taken + fits, refused + (not fits)
+    assert taken > 100 and refused > 100
