@@ -23,7 +23,7 @@ Printed JSON line (one):
               all host cores (the value) and on one thread, with the host's
               CPU model; the batched comparison and every extra row carry the
               oracle's rate on a sample of the same workload
-  batched     256 uneven uint8 images: one launch per job kind replayed from a
+  batched     256 uneven uint8 images: one launch of every tile replayed from a
               HIP graph vs 256 per-image launches (eager and graph-captured),
               images/s, outputs bitwise identical across the three
   hbm_reference  plain torch fill and copy of 256 MiB: the bandwidth this
@@ -61,7 +61,7 @@ HBM_PEAK_GBS = 8000.0
 FP32_PEAK_TFLOPS = 78.6  # non-packed FP32 FMA: 256 CUs x 64 lanes x 2 flops x 2.4 GHz
 ROTATE_BYTES = 1 << 30
 KERNEL_SOURCES = ["xr_forward.hip", "xr_walk.hip", "xr_aa.hip", "xr_backward.hip", "xr_device.hpp", "xr_buffer.hpp", "xr_aa.hpp",
-                  "xr_stage.hpp", "xr_gather_walk.hpp", "xr_internal.h"]
+                  "xr_stage.hpp", "xr_gather_walk.hpp", "xr_plan.hpp", "xr_internal.h"]
 HEADLINE_PROFILE = "c2_bicubic_x2_u8_rgba.md"
 # untimed launches before the per-launch statistics (see time_launches)
 PREROLL_LAUNCHES = 500
@@ -544,8 +544,8 @@ def batched(torch, xr, fields, reps: int = 20, cpu: bool = True):
     eq_multi = all(torch.equal(d, r) for (_, d, _), r in zip(pairs, ref))
     res["per_image_graph"] = len(pairs) / timed(g_multi.replay, 4)
 
-    # (i) one launch per job kind over every tile, shape from the batch
-    # autotuner, captured in a graph
+    # (i) one launch over every tile, shape from the batch autotuner, captured
+    # in a graph
     for _, d, _ in pairs:
         d.zero_()
     b = xr.Batch(pairs)

@@ -186,9 +186,10 @@ int xr_resize_bicubic(const xr_image *src, const xr_image *dst, const xr_tile *t
  *            enough workgroups, one takes up to 4 tiles down its column. Where
  *            rows shrink or stay and the output fills the GPU, XR_KERNEL_STRIP_LDS
  *            runs a walk instead that stages rows per wavefront and picks its
- *            own strips. All give identical bits. Strip kinds (and XR_KERNEL_AUTO before tuning) take the
- *            walk, else the first LDS block of 64x4, 64x2, 32x2, 16x2 that fits, else a 64x4
- *            gather. XR_ERR_ARG when the workgroup's LDS exceeds 96 KiB: the
+ *            own strips. All give identical bits. Strip kinds (and XR_KERNEL_AUTO
+ *            before tuning) take the walk, else the first LDS block of 64x4 (where
+ *            more of them than compute units pass half their LDS, not that one),
+ *            16x8, 64x2, 32x2, 16x2 that fits, else a 64x4 gather. XR_ERR_ARG when the workgroup's LDS exceeds 96 KiB: the
  *            weight tables, 4 (2 bw + 2 bh + bw kx + bh ky) bytes with
  *            k = floor(2 R sigma) + 1, plus for LDS blocks the source window
  *            (W x H pixels, W = floor(((bw - 1) N_in + 2 R max(N_in, N_out)) / N_out) + 2
@@ -207,9 +208,8 @@ int xr_resize(const xr_image *src, const xr_image *dst, int32_t filter, int32_t 
               const xr_tile *tile, void *stream);
 
 /*
- * Batched resize of many images of uneven sizes and scales in one launch per
- * job kind (the paper's per-image tiling question asked for a whole batch,
- * section III.B).
+ * Batched resize of many images of uneven sizes and scales in one launch (the
+ * paper's per-image tiling question asked for a whole batch, section III.B).
  *
  * xr_batch_workspace_bytes(n): bytes of device workspace for n jobs.
  * xr_batch_prepare: validates every job exactly like xr_resize_*, groups

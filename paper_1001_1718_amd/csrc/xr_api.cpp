@@ -715,8 +715,9 @@ xr_tile batch_default_tile(const xr_job *jobs, int32_t n_jobs, int32_t dtype)
 // bounds and where fewer rows in flight read it better. Measured with a
 // quarter and a third: 25 float16 and float32 batches of 5 .. 920 MB output
 // from 0.66 to 1.01 of the quarter's speed with the third, 9 of 1.1 .. 5.8 GB
-// 0.94 to 1.19 (float32 of 4.3 GB: 1236 and 1034 us); uint8, bound by
-// instructions, of any size less (256 images: 885 and 1136 us).
+// 0.94 to 1.19 (quarter and third: 256 float32 images up to 2048^2 2729 and 2640
+// us, 128 float16 ones 917 and 785); uint8, bound by instructions, of any size less
+// (256 images up to 2048^2 954 and 1133 us, 64 up to 700^2 58 and 80).
 int32_t batch_lds(const xr_job *jobs, int32_t n_jobs, int32_t dtype, const xr_tile &t)
 {
     const int64_t waves = t.block_w / 64 * t.block_h;
@@ -1182,8 +1183,7 @@ int xr_resize_batched_static(const xr_job *jobs, int32_t n_jobs, const xr_tile *
     rc = scratch_address(dev, &ws);
     if (rc)
         return rc;
-    // the upload writes the whole header, so the tickets start at zero; the
-    // staging buffer is reused by the next call, hence the synchronisation
+    // the staging buffer is reused by the next call, hence the synchronisation
     e = hipMemcpyAsync(ws, g_static_stage, xr_batch_workspace_bytes(n_jobs), hipMemcpyHostToDevice,
                        static_cast<hipStream_t>(stream));
     if (e == hipSuccess)

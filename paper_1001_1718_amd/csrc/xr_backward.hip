@@ -218,8 +218,8 @@ __global__ void __launch_bounds__(kBwdThreads) k_bwd_owner(ResizeArgs a, int32_t
 // rows: a source column's samples are the outputs that reach it, and an
 // upstream row reaches K consecutive source rows, its (clamped) taps.
 // Against the owner tiles: bicubic x1.5 of 48 float32 planes of 512^2, 95.7 to
-// 48.5 us (3.4 TB/s); bilinear x0.75 of 96 float16 planes 480 x 640, 61.4 to
-// 38.8 us (2.4 TB/s). What bounds it now: instruction issue and the waits of a
+// 41.6 us (3.9 TB/s); bilinear x0.75 of 96 float16 planes 480 x 640, 61.4 to
+// 33.2 us (2.8 TB/s). What bounds it now: instruction issue and the waits of a
 // wavefront for its next rows.
 template <int FILTER>
 struct AdjointWalk {

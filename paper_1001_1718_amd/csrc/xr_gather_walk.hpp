@@ -21,8 +21,8 @@
 // 99.3 us with a block's window and filtered rows in LDS, 35.4 us so, 2.4 TB/s;
 // of a wavefront's time a tenth goes into its tables; 192 bilinear uint8 planes
 // 375 x 500 -> 224^2: 135.0 to 24.5 us, 29.8 with one column per lane; the
-// bicubic x1.5 adjoint of 48 float32 planes 512^2: 96.1 to 43.3 us, 46.7 with
-// one column). Measured and left out: two windows a wavefront, the next rows
+// bicubic x1.5 adjoint of 48 float32 planes 512^2: 96.1 to 43.3 us, 46.7
+// with one column; 41.6 in a trace of warm steps). Measured and left out: two windows a wavefront, the next rows
 // arriving while the staged ones are filtered (34.9 to 36.4 us against 36.4,
 // planes 32 against 30).
 //

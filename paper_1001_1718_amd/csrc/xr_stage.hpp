@@ -3,10 +3,10 @@
 // A walk's wavefront owns an area of LDS and copies the next rows of its
 // source window there with direct loads from memory (16 bytes a lane, no
 // registers and no branch per load), waits for them once, and filters every
-// staged row from LDS. Nothing else it does waits for memory: loads and
-// stores share one counter on gfx950, so a walk that loads row by row between
-// its stores has to wait for those stores as well. Wavefronts are
-// independent (no workgroup barrier), and the rows in flight are bounded by
+// staged row from LDS. Loads and stores share one counter on gfx950: a walk that
+// loads row by row between its stores waits for those stores at every row; this
+// one waits for a chunk's stores once, with the next chunk's rows, and where one
+// chunk holds a strip, never. Wavefronts are independent (no workgroup barrier), and the rows in flight are bounded by
 // LDS, not by registers.
 #pragma once
 

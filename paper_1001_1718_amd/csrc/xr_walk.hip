@@ -23,7 +23,7 @@
 // Against the walks it replaced (taps loaded from memory per row between the
 // stores of the rows before, whose completion every such load then waits for):
 // bicubic x1.3 of a 2479 x 3507 gray uint8 page 58.7 -> 13.0 us, bicubic x1.5 of
-// 48 float32 planes of 512^2 196 -> 31 us (5.2 TB/s), bicubic x0.36 of a
+// 48 float32 planes of 512^2 196 -> 36 us (4.5 TB/s), bicubic x0.36 of a
 // 4000 x 3000 float32 RGBA photo 64.8 -> 44.7 us (4.8 TB/s), bilinear x6 of an
 // 800^2 RGBA uint8 image 26.2 -> 21.1 us (4.5 TB/s). Long outputs are bound by
 // memory, small ones by the time to a wavefront's first rows.
@@ -123,9 +123,9 @@ struct AxisSteps {
 
 // Cache policy of the walk's output stores: non-temporal only. Rows may start
 // at any byte offset, so a wavefront's run covers partial lines at both ends;
-// measured on the uneven 256-image batch, plain non-temporal stores beat the
-// streaming past-the-L2 policy of the exact walks by 8% (and write-back stores
-// by 12%).
+// measured on uneven batches (plain non-temporal, streaming past the L2 as in the
+// exact walks, write-back): 256 uint8 images up to 2048^2 987, 1003 and 913 us,
+// 128 float16 ones 805, 915 and 883, 64 float32 ones up to 1500^2 497, 480 and 468.
 constexpr int kWalkStore = 2;
 
 template <int FILTER, typename T, int C, int PPX>
@@ -463,11 +463,13 @@ struct Interleave {
 // Batches of several kinds: one launch of all their tiles, the kinds
 // interleaved, so that a batch has one last wave instead of four and the
 // one-channel and bicubic tiles, which instructions bound, share the chip with
-// the bilinear RGBA ones, which memory bounds. Launched kind by kind and so: 16
-// uneven uint8 images up to 256^2 30 and 10.5 us, 64 up to 700^2 83 and 55,
-// 128 up to 2048^2 642 and 587; 64 float32 images up to 700^2 140 and 119; 256
-// uint8 images up to 2048^2 958 to 975 us and 885 or 988 (a process has one of
-// the two, by where its buffers lie).
+// the bilinear RGBA ones, which memory bounds. Launched kind by kind and so, in
+// processes in turn: 16 uneven uint8 images up to 256^2 29.3 and 11.2 us, 64 up to
+// 700^2 75 and 57, 128 up to 1200^2 240 and 201, 128 up to 2048^2 493 and 424, 256
+// up to 2048^2 984 to 995 and 955; float16 64 up to 1000^2 135 and 124, 128 up to
+// 2048^2 913 and 790; float32 64 up to 1500^2 502 and 496, 256 up to 2048^2 2853
+// and 2640. (The 256 uint8 images take 940 to 990 us by box and process, for a
+// cause not found: kind by kind 980 to 1010.)
 // A batch of one kind has its own kernel, of fewer registers.
 struct BatchMix {
     Interleave four, cubic1, cubic4;  // RGBA of all, bicubic of the one-channel and of the RGBA tiles
