@@ -304,7 +304,7 @@ TuneKey tune_key(int32_t filter, int32_t dtype, int32_t channels, int32_t in_w, 
 {
     const int x = scale_class(in_w, out_w), y = scale_class(in_h, out_h);
     const bool exact = filter != XR_NEAREST && x == y && (x == 0 || x == 3);
-    const bool small = !exact && !is_aa(filter) && !xr::walk_default(channels, out_w, out_h, std::max(planes, 1));
+    const bool small = !exact && !is_aa(filter) && !xr::walk_default(filter, dtype, channels, in_w, out_w, out_h, std::max(planes, 1));
     return TuneKey(filter, dtype, channels, x, y, size_class(out_w, out_h, planes) + (small ? 5 : 0));
 }
 
@@ -339,13 +339,18 @@ xr_tile default_tile(int32_t filter, int32_t dtype, int32_t channels, int32_t in
         t.block_w = 64;
         t.block_h = 4;
         t.ppt_x = xr::walk_ppx(channels, elem_size(dtype) * channels);
+        // (two float16 RGBA columns of a strongly shrinking row need so much LDS
+        // that few wavefronts fit: bicubic x0.27 of 2860 x 2600 20.0 us, 15.9 with
+        // one, bilinear 12.6 and 10.2; x0.45 20.3 and 18.5, 17.3 and 15.7)
+        if (c4 && dtype == XR_F16 && in_w / 2 >= out_w)
+            t.ppt_x = 1;
         // a strip of h rows re-filters K - 1 source rows of its neighbour's,
         // but needs as many wavefronts for each row it walks: about one per
         // compute unit (measured: gray x1.3 of a 2479 x 3507 page best at 16
         // rows, 3705 wavefronts; float32 RGBA x0.36 of 4000 x 3000 at 4 rows,
         // 6210; bilinear gray x2 of 512^2 at 4 rows, 1024)
         const int64_t cols = (static_cast<int64_t>(out_w) + 64 * t.ppt_x - 1) / (64 * t.ppt_x);
-        if (!xr::walk_default(channels, out_w, rows, planes)) {
+        if (!xr::walk_default(filter, dtype, channels, in_w, out_w, rows, planes)) {
             t.kernel = XR_KERNEL_STRIP_ANY;
             t.block_h = 1;
             t.ppt_x = c4 ? 2 : 4;
@@ -353,15 +358,27 @@ xr_tile default_tile(int32_t filter, int32_t dtype, int32_t channels, int32_t in
             return t;
         }
         const double walked = std::max(1.0, static_cast<double>(in_h) / out_h);  // source rows per output row
-        for (t.ppt_y = 16; t.ppt_y > 1; t.ppt_y /= 2)
+        // (float16 RGBA of one and two taps, whose strips share one row or none, in 8
+        // rows at most: 56 growing resizes 1.00x to 1.31x the speed of 16. The other
+        // types have no such line: gray float16 and RGBA uint8 bilinear at 8 rows 0.76x
+        // to 1.34x, by the output's pitch; bicubic 0.76x to 0.94x at 4)
+        const int top = c4 && dtype == XR_F16 && filter != XR_BICUBIC ? 8 : 16;
+        for (t.ppt_y = top; t.ppt_y > 1; t.ppt_y /= 2)
             if (static_cast<double>(cols * ((rows + t.ppt_y - 1) / t.ppt_y) * planes) >= kWalkWaves * walked * t.ppt_y)
                 break;
         return t;
     };
     const bool fits = xr::walk_fits(filter, dtype, channels, in_w, out_w);
-    if (!exact && fits)
+    // copies of 4-byte pixels into large outputs: the per-tap strips stream as
+    // well and wait for no table (growing RGBA uint8, nearest: 0.73x to 1.03x
+    // their speed in the walk from 40 MB on, 1.1x to 1.7x below 25 MB)
+    const bool copies = c4 && dtype == XR_U8 && filter == XR_NEAREST && out_w >= in_w && out_h >= in_h &&
+                        static_cast<int64_t>(out_w) * rows * planes >= int64_t(1) << 23;
+    if (!exact && fits && !copies)
         return staged();
-    const bool up2 = exact && out_w == 2 * in_w;
+    if (!exact && copies)
+        t.kernel = XR_KERNEL_STRIP_ANY;
+    const bool up2 = (exact || copies) && out_w == 2 * in_w && out_h == 2 * in_h;
     if (up2) {
         t.block_w = 256;
         t.block_h = 1;
@@ -835,7 +852,7 @@ std::vector<xr_tile> tune_candidates(int32_t filter, const xr_image &src, const 
     const int tap_rows[] = {1, 2, 6, 14, 22, 30, 46, 62};
     const bool fits = xr::walk_fits(filter, dtype, channels, src.width, dst.width);
     const bool taps = !fits || channels * elem_size(dtype) >= 8 ||
-                      !xr::walk_default(channels, dst.width, (dst.rows + 1) / 2, dst.planes);
+                      !xr::walk_default(filter, dtype, channels, src.width, dst.width, (dst.rows + 1) / 2, dst.planes);
     const auto walks = [&](int ppx) { return fits && xr::walk_built(filter, dtype, channels, ppx); };
     strips(XR_KERNEL_STRIP, walk_rows, walks, 2);
     strips(XR_KERNEL_STRIP_ANY, tap_rows, [&](int ppx) { return several(ppx) && (taps || !walks(ppx)); }, 2);

@@ -513,6 +513,8 @@ template <int FILTER, typename T, int C, int PPX>
 hipError_t launch_walk_ppx(const ResizeArgs &a, const xr_tile &tile, hipStream_t stream, bool &taken, Route *only)
 {
     constexpr int K = Taps<FILTER>::K, PB = Pix<T, C>::kBytes;
+    constexpr int32_t kType = std::is_same_v<T, uint8_t> ? XR_U8 : std::is_same_v<T, float> ? XR_F32 : XR_F16;
+    constexpr int32_t kFilter = FILTER == kBicubic ? XR_BICUBIC : FILTER == kNearest ? XR_NEAREST : XR_BILINEAR;
     const int64_t row_bytes = walk_row_bytes(K, PB, PPX, a.in_w, a.out_w);
     // source rows a strip reads; offsets within them stay below 2^31
     const auto src_rows = [&](int64_t rows) { return std::min<int64_t>((rows - 1) * a.in_h / a.out_h + K + 1, a.in_h); };
@@ -532,7 +534,7 @@ hipError_t launch_walk_ppx(const ResizeArgs &a, const xr_tile &tile, hipStream_t
     // 44 above), shrinking float16 and float32 ones of one channel in taller
     // strips at 0.79 to 1.13 (one above); the other one-channel tiles at 0.96 to
     // 2.4, and so they walk.
-    if (tile.kernel == XR_KERNEL_STRIP && !walk_default(C, a.out_w, a.dst_rows, a.planes) &&
+    if (tile.kernel == XR_KERNEL_STRIP && !walk_default(kFilter, kType, C, a.in_w, a.out_w, a.dst_rows, a.planes) &&
         (C == 4 || (PB > 1 && a.in_h > a.out_h && tile.ppt_y > 2)))
         return hipSuccess;
     // fewer wavefronts a workgroup where those of the tile pass the LDS limit

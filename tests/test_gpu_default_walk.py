@@ -42,7 +42,7 @@ def _same(a, b):
 # (in_h, in_w, out_h, out_w), planes: growing, shrinking, shrinking past the
 # taps, one column tile more, and the edges' shapes in stacks
 DEFAULT = [((600, 500, 780, 650), 3), ((1500, 2100, 540, 756), 2), ((3000, 800, 430, 300), 5), ((900, 515, 1800, 513), 1),
-           ((1, 1, 5, 4), 500), ((3, 2, 7, 9), 400), ((19, 40, 25, 51), 100), ((90, 33, 13, 31), 200), ((12, 70, 75, 420), 30)]
+           ((1, 1, 5, 4), 720), ((3, 2, 7, 9), 520), ((19, 40, 25, 51), 150), ((90, 33, 13, 31), 280), ((12, 70, 75, 420), 30)]
 
 
 @pytest.mark.parametrize("mode", ["bilinear", "bicubic", "nearest"])
@@ -108,3 +108,18 @@ def test_adjoint_walk_with_infinities(mode, channels, dtype):
         calm = ~wild
         check = check_f32 if dtype == torch.float32 else check_f16_sum
         check(got[p:p + 1][calm], ref[calm], scale[calm], what=f"adjoint walk {ih}x{iw}-{oh}x{ow}")
+
+
+@pytest.mark.parametrize("channels", [1, 4])
+@pytest.mark.parametrize("out_h, out_w, row0, rows", [(1950, 1170, 301, 900), (260, 4500, 37, 203)])
+def test_default_walk_of_a_band(channels, out_h, out_w, row0, rows):
+    """A band of a 1500 x 900 image (growing; shrinking past the taps), from
+    the source rows that it needs."""
+    x = _data((1500, 900, channels), torch.uint8, 11)
+    assert route("bicubic", xr.XR_U8, (1500, 900), (rows, out_w), channels) == "walk"  # (by the band's size)
+    first, last = xr.needed_rows(1500, out_h, row0, rows, "bicubic")
+    got = torch.empty((rows, out_w, channels), dtype=torch.uint8, device=DEV)
+    whole = torch.empty((out_h, out_w, channels), dtype=torch.uint8, device=DEV)
+    xr.resize_into(x[first:last + 1], got, "bicubic", src_row0=first, src_height=1500, dst_row0=row0, dst_height=out_h)
+    xr.resize_into(x, whole, "bicubic", tile=GATHER)
+    assert torch.equal(got, whole[row0:row0 + rows])

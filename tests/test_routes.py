@@ -14,7 +14,7 @@ FORWARD = [
     ("x2", dict(mode="bicubic", dtype=U8, in_hw=(4096, 4096), out_hw=(8192, 8192), channels=4)),
     ("walk", dict(mode="bicubic", dtype=U8, in_hw=(4096, 4096), out_hw=(8192, 8192), src_data=SRC + 1)),
     ("walk", dict(mode="bicubic", dtype=U8, in_hw=(4096, 4096), out_hw=(8192, 8192), channels=4, mapping="paper")),
-    ("walk", dict(mode="nearest", dtype=U8, in_hw=(4096, 4096), out_hw=(8192, 8192), channels=4)),
+    ("walk", dict(mode="nearest", dtype=F16, in_hw=(4096, 4096), out_hw=(8192, 8192), channels=4)),
     ("x05", dict(mode="bicubic", dtype=F16, in_hw=(4096, 4096), out_hw=(2048, 2048), channels=4)),
     ("x2", dict(mode="bicubic", dtype=F32, in_hw=(64, 64), out_hw=(128, 128), dst_pitch=120 * MIB)),
     ("strip", dict(mode="bicubic", dtype=F32, in_hw=(64, 64), out_hw=(128, 128), dst_pitch=128 * MIB)),
@@ -27,6 +27,23 @@ FORWARD = [
     ("strip", dict(mode="bicubic", dtype=F32, in_hw=(1500, 100), out_hw=(2099, 128), channels=4)),
     ("walk", dict(mode="bicubic", dtype=F32, in_hw=(512, 512), out_hw=(768, 768), planes=48)),
     ("walk", dict(mode="bicubic", dtype=F32, in_hw=(3000, 4000), out_hw=(1080, 1440), channels=4)),
+    # (later where the per-tap strips are the faster ones)
+    ("walk", dict(mode="nearest", dtype=U8, in_hw=(1500, 200), out_hw=(2600, 256))),
+    ("strip", dict(mode="nearest", dtype=F16, in_hw=(1500, 200), out_hw=(2599, 256))),
+    ("walk", dict(mode="nearest", dtype=F32, in_hw=(1500, 200), out_hw=(1700, 256))),
+    ("walk", dict(mode="nearest", dtype=U8, in_hw=(1500, 100), out_hw=(3400, 128), channels=4)),
+    ("strip", dict(mode="nearest", dtype=F16, in_hw=(1500, 100), out_hw=(3399, 128), channels=4)),
+    ("walk", dict(mode="bilinear", dtype=F16, in_hw=(1500, 100), out_hw=(2600, 128), channels=4)),
+    ("strip", dict(mode="bilinear", dtype=F16, in_hw=(1500, 100), out_hw=(2599, 128), channels=4)),
+    ("walk", dict(mode="bicubic", dtype=F16, in_hw=(1500, 65), out_hw=(3500, 128), channels=4)),
+    ("strip", dict(mode="bicubic", dtype=F16, in_hw=(1500, 65), out_hw=(3499, 128), channels=4)),
+    ("walk", dict(mode="bicubic", dtype=F16, in_hw=(1500, 64), out_hw=(2100, 128), channels=4)),
+    ("strip", dict(mode="bilinear", dtype=F32, in_hw=(1500, 128), out_hw=(3499, 128), channels=4)),
+    ("walk", dict(mode="bilinear", dtype=F32, in_hw=(1500, 129), out_hw=(2100, 128), channels=4)),
+    # copies of RGBA bytes into outputs of 2^23 pixels and more
+    ("strip", dict(mode="nearest", dtype=U8, in_hw=(2000, 2000), out_hw=(2048, 4096), channels=4)),
+    ("walk", dict(mode="nearest", dtype=U8, in_hw=(2000, 2000), out_hw=(2047, 4096), channels=4)),
+    ("walk", dict(mode="nearest", dtype=U8, in_hw=(2000, 4097), out_hw=(2048, 4096), channels=4)),
     # row pitches past 4 MiB, rows too long for LDS, outputs narrower than a run
     ("walk", dict(mode="bicubic", dtype=U8, in_hw=(3000, 2000), out_hw=(4000, 2600), dst_pitch=4 * MIB)),
     ("strip", dict(mode="bicubic", dtype=U8, in_hw=(3000, 2000), out_hw=(4000, 2600), dst_pitch=5 * MIB)),
@@ -42,7 +59,7 @@ FORWARD = [
     # (on small outputs only where the walk is the faster one)
     ("strip", dict(mode="bicubic", dtype=F16, in_hw=(600, 800), out_hw=(200, 270), channels=4,
                    tile=xr.tile(xr.XR_KERNEL_STRIP, 64, 4, 2, 2))),
-    ("walk", dict(mode="bicubic", dtype=F16, in_hw=(600, 800), out_hw=(200, 270), channels=4, planes=4,
+    ("walk", dict(mode="bicubic", dtype=F16, in_hw=(600, 800), out_hw=(200, 270), channels=4, planes=6,
                   tile=xr.tile(xr.XR_KERNEL_STRIP, 64, 4, 2, 2))),
     ("strip", dict(mode="bicubic", dtype=F32, in_hw=(600, 800), out_hw=(200, 270),
                    tile=xr.tile(xr.XR_KERNEL_STRIP, 64, 4, 4, 6))),
@@ -102,3 +119,13 @@ def test_lds_tiles_are_taken_as_documented():
                         assert fits == (got != "error 11")
                         taken, refused = taken + fits, refused + (not fits)
     assert taken > 100 and refused > 100
+
+
+@pytest.mark.parametrize("mode, dtype, channels, in_hw, out_hw, ppt_x, rows", [
+    ("bicubic", U8, 1, (3507, 2479), (4559, 3223), 4, 16), ("bilinear", U8, 4, (800, 800), (4700, 4700), 2, 16),
+    ("nearest", F16, 4, (2600, 2860), (3380, 3716), 2, 8), ("bilinear", F16, 4, (2600, 2860), (3380, 3716), 2, 8),
+    ("bicubic", F16, 4, (2600, 2860), (3380, 3716), 2, 16), ("bilinear", F32, 4, (2600, 2860), (3380, 3716), 1, 16),
+    ("bicubic", F16, 4, (2600, 2860), (780, 856), 1, 2), ("bicubic", F16, 4, (2600, 2860), (1300, 1431), 2, 4)])
+def test_default_strips_of_the_walk(mode, dtype, channels, in_hw, out_hw, ppt_x, rows):
+    t = xr.get_tile(mode, dtype, channels, in_hw[1], in_hw[0], out_hw[1], out_hw[0])
+    assert t.as_tuple() == (xr.XR_KERNEL_STRIP, 64, 4, ppt_x, rows, 0)
