@@ -313,7 +313,27 @@ bool aa_walk_shape(const ResizeArgs &a, GatherShape &g)
     // tiles; 512 bicubic planes 300 x 90 -> 60 x 30: 69 and 105)
     if (p.kx > kGatherRegTaps && a.out_w < 24)
         return false;
-    const int64_t strip = gather_strip(C, a.out_w, a.dst_rows, a.planes, a.src_pitch, cap);
+    // One-channel columns of several samples, two to a lane, need more results
+    // than others to pay. The walk's speed over the tiles' at 280 / 340 / 420 / 520 /
+    // 700 thousand of one image: bicubic x0.35 (12 samples, from the table) float32
+    // 0.56 0.60 0.79 0.90 0.97, float16 0.60 0.65 0.86 0.98 1.06, uint8 0.82 0.88 1.16;
+    // x0.25 (17) float32 0.71 0.72 0.97 1.08, float16 0.64 0.87 0.95 1.07, uint8 0.86
+    // 0.97 1.29; x0.5 (9) float32 0.75 0.83 1.05, float16 0.84 0.92 1.11, uint8 1.15;
+    // bilinear x0.25 (9) float32 0.75 0.99 1.06; bicubic x0.15 (27) 1.27 up. In a stack
+    // of 24 planes bilinear 1.06 up. RGBA bicubic x0.7 and x0.9 of halves and floats
+    // 0.87 to 0.95, 1.14 up.
+    int64_t least = kGatherLeast;
+    const int size = static_cast<int>(sizeof(T));
+    const bool stack = a.planes >= 8;
+    if (C == 1 && R == 2 && p.kx > kGatherRegTaps)
+        least += p.kx > 20 ? 0 : size == 1 ? least / 2 : p.kx > 14 ? (size == 4 ? 3 * least / 4 : least / 2) : size == 4 ? 3 * least / 2 : 7 * least / 8;
+    else if (C == 1 && R == 2)
+        least += size == 1 ? 0 : least / 2;
+    else if (C == 1)
+        least += p.kx > 6 && p.kx <= kGatherRegTaps && size == 4 && !stack ? least / 4 : 0;
+    else if (R == 2)
+        least += p.kx <= 7 && size > 1 && !stack ? least / 5 : 0;
+    const int64_t strip = gather_strip(C, a.out_w, a.dst_rows, a.planes, a.src_pitch, least, cap);
     return strip > 0 && gather_shape(g, C, AaWalk<R>::kSlots, p.kx, p.win_w, Pix<T, C>::kBytes, strip, cap);
 }
 

@@ -410,14 +410,21 @@ xr_tile default_tile(int32_t filter, int32_t dtype, int32_t channels, int32_t in
         const int64_t wcols = (static_cast<int64_t>(out_w) + 64 * u.ppt_x - 1) / (64 * u.ppt_x);
         return wcols * ((static_cast<int64_t>(rows) + u.ppt_y - 1) / u.ppt_y) * planes;
     };
-    // (the x2 kernel's strips are whole eights of rows; 2048 wide RGBA uint8
-    // outputs: 7.1 us in 2,048 wavefronts of 4 columns, 6.3 us in 4,096 of 2)
+    // The x2 kernel's strips are whole eights of rows. Where those leave few
+    // wavefronts, fewer columns a thread, in 64 threads: RGBA 2048 wide, bicubic
+    // uint8 7.1 us in 2,048 wavefronts of 4 columns, 6.3 us in 4,096 of 2; float32
+    // gray 3000^2 1.11x. Not so bilinear RGBA uint8 (3600^2 0.91x in 3,600
+    // wavefronts), gray float16 (2048^2 and 3000^2 0.87x to 0.91x; 3600^2 0.96x and
+    // 1.06x) and, in the walk that small gray uint8 outputs take, 3600^2 0.89x and
+    // 0.92x (2400^2 1.06x and 1.10x).
+    const int64_t eights = c4 ? (elem_size(dtype) == 1 && filter == XR_BILINEAR ? 1500 : 4096)
+                              : elem_size(dtype) == 1 ? 2048 : dtype == XR_F16 && out_w <= 3072 ? 1024 : 4096;
     const int steps[] = {first, 16, 14, 8, 6, 4, 2, 1};
     for (int ppy : steps) {
         if (ppy > first || (up2 && ppy % 8 != 0))
             continue;
         t.ppt_y = ppy;
-        if (waves(t) >= (up2 && ppy == 8 ? 4096 : 8192))
+        if (waves(t) >= (up2 && ppy == 8 ? eights : 8192))
             return t;
     }
     // small outputs: one-byte pixels in runs of 4 columns take the staged walk

@@ -75,15 +75,16 @@ constexpr int64_t kGatherWindow = 8192;
 // 37.3 us; 192 bilinear planes 375 x 500 -> 224^2 (1536 at 64 rows, 2688 at
 // 32, 5376 at 16): 34.9, 24.8 and 27.5 us.
 //
-// 0: fewer than kGatherLeast results, too few wavefronts to hide that latency
-// even at 4 rows; kernels that spread one tile's rows over a workgroup are then
-// faster (44 antialiased resizes of 0.4 .. 8000 K results: 0.48x to 0.79x their
-// speed below 130 K where a walk was forced, 1.0x to 5.5x above 280 K).
+// 0: fewer than `least` results, too few wavefronts to hide that latency even at
+// 4 rows; kernels that spread one tile's rows over a workgroup are then faster
+// (0.48x to 0.79x their speed below 130 K results where a walk was forced). From
+// kGatherLeast on the walk is at 1.0x to 18x for RGBA and for one-channel images
+// but those for which its caller names more.
 constexpr int64_t gather_min_waves(int32_t channels) { return channels == 1 ? 2048 : 3072; }
 constexpr int64_t kGatherLeast = 1 << 18;
 template <class RowsCap>
 inline int64_t gather_strip(int32_t channels, int64_t res_w, int64_t res_rows, int64_t planes, int64_t pitch,
-                            RowsCap rows_cap)
+                            int64_t least, RowsCap rows_cap)
 {
     const int64_t wide = gather_cols(channels);
     const auto waves = [&](int64_t strip) {
@@ -92,7 +93,7 @@ inline int64_t gather_strip(int32_t channels, int64_t res_w, int64_t res_rows, i
     int64_t strip = 64;
     while (strip > 4 && (waves(strip) < gather_min_waves(channels) || rows_cap(strip) * pitch >= (int64_t(1) << 31)))
         strip /= 2;
-    return res_w * res_rows * planes < kGatherLeast || rows_cap(strip) * pitch >= (int64_t(1) << 31) ? 0 : strip;
+    return res_w * res_rows * planes < least || rows_cap(strip) * pitch >= (int64_t(1) << 31) ? 0 : strip;
 }
 
 // The launch of a walk whose sample rows hold at most win_px samples of

@@ -66,8 +66,10 @@ def test_default_launch_equals_gather(mode, channels, dtype):
                 assert not bool(out[:, :, :2].any()) and not bool(out[:, :, 2 + ow:].any())
 
 
-# one column; columns of 11 samples and more (24 of them, a tile, a tile and one)
-AA = [(9, 1, 6, 1), (30, 160, 7, 24), (20, 420, 5, 64), (20, 450, 5, 65), (12, 800, 11, 130)]
+# one column; unchanged rows, x0.5, 5 samples a column, the most in registers; 11
+# and more (24 columns, a tile, a tile and one, two tiles); growing columns
+AA = [(14, 1, 10, 1), (9, 13, 9, 13), (16, 24, 8, 12), (11, 29, 6, 13), (9, 129, 9, 64), (9, 131, 5, 65), (23, 60, 9, 24),
+      (30, 160, 7, 24), (20, 420, 5, 64), (20, 450, 5, 65), (12, 800, 11, 130), (70, 5, 67, 11)]
 
 
 @pytest.mark.parametrize("mode", ["bilinear_aa", "bicubic_aa"])
@@ -75,8 +77,8 @@ AA = [(9, 1, 6, 1), (30, 160, 7, 24), (20, 420, 5, 64), (20, 450, 5, 65), (12, 8
 @pytest.mark.parametrize("dtype", [torch.uint8, torch.float16, torch.float32])
 def test_antialiased_walk_equals_gather(mode, channels, dtype):
     for k, (ih, iw, oh, ow) in enumerate(AA):
-        planes = -(-(1 << 18) // (oh * ow))
-        assert route(mode, CODES[dtype], (ih, iw), (oh, ow), channels, planes) == "aa walk"
+        planes = min(60000, -(-660000 // (oh * ow)))
+        assert route(mode, CODES[dtype], (ih, iw), (oh, ow), channels, planes) == "aa walk", (ih, iw, oh, ow)
         x = _data((planes, ih, iw + 3, channels), dtype, 800 + k)[:, :, 1:1 + iw]
         got, ref = (torch.empty((planes, oh, ow, channels), dtype=dtype, device=DEV) for _ in range(2))
         xr.resize_into(x, got, mode)
@@ -88,8 +90,8 @@ def test_antialiased_walk_equals_gather(mode, channels, dtype):
 @pytest.mark.parametrize("channels", [1, 4])
 @pytest.mark.parametrize("dtype", [torch.float16, torch.float32])
 def test_adjoint_walk_with_infinities(mode, channels, dtype):
-    for k, (ih, iw, oh, ow) in enumerate([(40, 30, 60, 45), (40, 60, 30, 45), (60, 70, 9, 11)]):
-        planes = -(-(1 << 18) // (ih * iw))
+    for k, (ih, iw, oh, ow) in enumerate([(40, 30, 60, 45), (40, 60, 30, 45), (60, 70, 9, 11), (30, 40, 81, 110)]):
+        planes = -(-660000 // (ih * iw))
         assert route_backward(mode, CODES[dtype], (ih, iw), (oh, ow), channels, planes) == "adjoint walk"
         g = _data((planes, oh, ow, channels), dtype, 900 + k)
         got = xr.resize_backward(g, (ih, iw), mode, layout="hwc").float().cpu().numpy()

@@ -79,6 +79,21 @@ FORWARD = [
     ("aa tile", dict(mode="bicubic_aa", dtype=U8, in_hw=(511, 300), out_hw=(512, 600))),
     ("aa walk", dict(mode="bilinear_aa", dtype=U8, in_hw=(60, 200), out_hw=(30, 24), planes=512)),
     ("aa tile", dict(mode="bilinear_aa", dtype=U8, in_hw=(60, 200), out_hw=(30, 23), planes=512)),
+    # (from more results on for one-channel bicubic columns, by samples and type)
+    ("aa walk", dict(mode="bicubic_aa", dtype=F32, in_hw=(1820, 1820), out_hw=(640, 1024))),
+    ("aa tile", dict(mode="bicubic_aa", dtype=F32, in_hw=(1820, 2926), out_hw=(639, 1024))),
+    ("aa walk", dict(mode="bicubic_aa", dtype=F16, in_hw=(1380, 2926), out_hw=(480, 1024))),
+    ("aa tile", dict(mode="bicubic_aa", dtype=F16, in_hw=(1380, 2926), out_hw=(479, 1024))),
+    ("aa walk", dict(mode="bicubic_aa", dtype=F32, in_hw=(1800, 4096), out_hw=(448, 1024))),
+    ("aa tile", dict(mode="bicubic_aa", dtype=F32, in_hw=(1800, 4096), out_hw=(447, 1024))),
+    ("aa walk", dict(mode="bicubic_aa", dtype=U8, in_hw=(1800, 4096), out_hw=(384, 1024))),
+    ("aa tile", dict(mode="bicubic_aa", dtype=U8, in_hw=(1800, 4096), out_hw=(383, 1024))),
+    ("aa walk", dict(mode="bicubic_aa", dtype=F16, in_hw=(768, 2048), out_hw=(384, 1024))),
+    ("aa tile", dict(mode="bicubic_aa", dtype=F16, in_hw=(768, 2048), out_hw=(383, 1024))),
+    ("aa walk", dict(mode="bilinear_aa", dtype=F32, in_hw=(1280, 4096), out_hw=(320, 1024))),
+    ("aa tile", dict(mode="bilinear_aa", dtype=F32, in_hw=(1280, 4096), out_hw=(319, 1024))),
+    ("aa walk", dict(mode="bicubic_aa", dtype=F16, in_hw=(400, 1300), out_hw=(308, 1024), channels=4)),
+    ("aa tile", dict(mode="bicubic_aa", dtype=F16, in_hw=(400, 1300), out_hw=(307, 1024), channels=4)),
     ("aa gather", dict(mode="bicubic_aa", dtype=F32, in_hw=(8000, 500), out_hw=(20, 20), channels=4)),
 ]
 
@@ -93,6 +108,10 @@ def test_forward_route(want, call):
     ("adjoint walk", dict(mode="bilinear", dtype=F32, in_hw=(512, 512), out_hw=(768, 768))),
     ("adjoint owner", dict(mode="bilinear", dtype=F32, in_hw=(511, 512), out_hw=(768, 768))),
     ("adjoint walk", dict(mode="bicubic", dtype=F16, in_hw=(480, 640), out_hw=(360, 480), channels=4)),
+    ("adjoint walk", dict(mode="bicubic", dtype=F32, in_hw=(352, 1024), out_hw=(1100, 3000))),
+    ("adjoint owner", dict(mode="bicubic", dtype=F32, in_hw=(351, 1024), out_hw=(1100, 3000))),
+    ("adjoint walk", dict(mode="bicubic", dtype=F32, in_hw=(80, 1024), out_hw=(250, 3000), planes=8)),
+    ("adjoint owner", dict(mode="bicubic", dtype=F32, in_hw=(79, 1024), out_hw=(250, 3000), planes=8)),
 ])
 def test_adjoint_route(want, call):
     assert route_backward(**call) == want
