@@ -310,7 +310,8 @@ int xr_resize_backward(const xr_image *grad_dst, const xr_image *grad_src, int32
  * key (filter, dtype, channels, the scale class of each axis: x2, identity,
  * other up, x0.5, other down; and the size class of the output's
  * width x height x planes pixels: up to 2^16, 2^20, 2^24, 2^26, beyond; outputs
- * at general ratios too small for the staged walk's default are apart).
+ * at general ratios too small for the staged walk's default are apart, and so
+ * are x2 and x0.5 calls that the kernels for those scales do not take).
  * Overwrites the dsts.
  * candidates = NULL uses the built-in candidate list, whose first is the shape
  * that an untuned call takes: it is kept, and nothing remembered, unless
@@ -327,7 +328,9 @@ int32_t xr_tune_candidates(int32_t filter, int32_t dtype, int32_t channels, int3
 /*
  * The shape XR_KERNEL_AUTO resolves to for a key (images of one plane): the
  * tuned one if xr_autotune (or xr_set_tile) stored one, else the built-in
- * default. xr_set_tile with kernel XR_KERNEL_AUTO forgets the key's shape.
+ * default (xr_get_tile: for the pixel-centre map and aligned images).
+ * xr_set_tile stores a shape for either map; with kernel XR_KERNEL_AUTO it
+ * forgets the key's shape.
  */
 int xr_get_tile(int32_t filter, int32_t dtype, int32_t channels, int32_t in_w, int32_t in_h,
                 int32_t out_w, int32_t out_h, xr_tile *out);

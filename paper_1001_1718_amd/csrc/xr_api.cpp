@@ -299,13 +299,19 @@ using TuneKey = std::tuple<int, int, int, int, int, int>;
 // Outputs at general ratios that are too small for the staged walk's default
 // are size classes of their own (5 more): the per-tap shapes that are best there
 // are several times slower than the walk just above, and the walk's slower below.
+// So are calls at exactly x2 or x0.5 that the kernels for those scales do not
+// take (`general`: the printed map, unaligned images; 10 more): the shapes of the
+// one are poor for the others (bilinear x0.5 of 4096^2 RGBA uint8 under the printed
+// map 28 us in the shape tuned for pixel centres, 17 untuned).
 TuneKey tune_key(int32_t filter, int32_t dtype, int32_t channels, int32_t in_w, int32_t in_h,
-                 int32_t out_w, int32_t out_h, int32_t planes)
+                 int32_t out_w, int32_t out_h, int32_t planes, bool general)
 {
     const int x = scale_class(in_w, out_w), y = scale_class(in_h, out_h);
-    const bool exact = filter != XR_NEAREST && x == y && (x == 0 || x == 3);
-    const bool small = !exact && !is_aa(filter) && !xr::walk_default(filter, dtype, channels, in_w, out_w, out_h, std::max(planes, 1));
-    return TuneKey(filter, dtype, channels, x, y, size_class(out_w, out_h, planes) + (small ? 5 : 0));
+    const bool at_exact = filter != XR_NEAREST && !is_aa(filter) && x == y && (x == 0 || x == 3);
+    const bool small = !is_aa(filter) && (!at_exact || general) &&
+                       !xr::walk_default(filter, dtype, channels, in_w, out_w, out_h, std::max(planes, 1));
+    return TuneKey(filter, dtype, channels, x, y,
+                   size_class(out_w, out_h, planes) + (small ? 5 : 0) + (at_exact && general ? 10 : 0));
 }
 
 std::mutex g_tune_mu;
@@ -574,13 +580,19 @@ xr_tile aa_default_tile(int32_t filter, const xr_image &src, const xr_image &dst
     return walk ? xr_tile{XR_KERNEL_STRIP_LDS, 64, 4, 1, 1, 0} : xr_tile{XR_KERNEL_GATHER, 64, 4, 1, 1, 0};
 }
 
+// True when the kernels of the exact scales do not take the call.
+bool is_general(int32_t filter, const xr_image &src, const xr_image &dst, int32_t mapping)
+{
+    const xr_tile strip{XR_KERNEL_STRIP, 64, 1, 1, 1, 0};
+    return axis_mode(src, dst, strip, filter, mapping) == xr::kGeneral;
+}
+
 // The shape of an untuned call (antialiased: a strip shape, which means
 // aa_default_tile).
 xr_tile untuned_tile(int32_t filter, const xr_image &src, const xr_image &dst, int32_t mapping)
 {
-    const xr_tile strip{XR_KERNEL_STRIP, 64, 1, 1, 1, 0};
     return default_tile(filter, src.dtype, src.channels, src.width, src.height, dst.width, dst.rows, dst.height,
-                        dst.planes, axis_mode(src, dst, strip, filter, mapping) != xr::kGeneral);
+                        dst.planes, !is_general(filter, src, dst, mapping));
 }
 
 xr_tile resolve_tile(const xr_tile *tile, int32_t filter, const xr_image &src, const xr_image &dst, int32_t mapping)
@@ -588,7 +600,7 @@ xr_tile resolve_tile(const xr_tile *tile, int32_t filter, const xr_image &src, c
     if (tile && tile->kernel != XR_KERNEL_AUTO)
         return *tile;
     const TuneKey key = tune_key(filter, src.dtype, src.channels, src.width, src.height, dst.width,
-                                 dst.height, dst.planes);
+                                 dst.height, dst.planes, is_general(filter, src, dst, mapping));
     std::lock_guard<std::mutex> lock(g_tune_mu);
     auto it = g_tuned.find(key);
     // a tuned LDS shape applies only to sources it can stage (alignment is
@@ -1335,13 +1347,18 @@ int xr_resize_backward(const xr_image *grad_dst, const xr_image *grad_src, int32
 }
 
 // Not part of the interface: the kernel (xr::Route) that a call with these
-// arguments runs, or minus its error code. No HIP call.
+// arguments runs, or minus its error code, and the shape that it resolves to
+// (`shape` may be NULL). No HIP call.
 int32_t xr_internal_route(const xr_image *src, const xr_image *dst, int32_t filter, int32_t mapping,
-                          const xr_tile *tile)
+                          const xr_tile *tile, xr_tile *shape)
 {
     xr::Route r{};
     const int rc = resize_common(src, dst, tile, filter, mapping, nullptr, &r);
-    return rc ? -rc : static_cast<int32_t>(r);
+    if (rc)
+        return -rc;
+    if (shape)
+        *shape = resolve_tile(tile, filter, *src, *dst, mapping);
+    return static_cast<int32_t>(r);
 }
 
 int32_t xr_internal_route_backward(const xr_image *grad_dst, const xr_image *grad_src, int32_t filter)
@@ -1468,7 +1485,7 @@ int xr_autotune(const xr_image *srcs, const xr_image *dsts, int32_t n_pairs, int
     {
         std::lock_guard<std::mutex> lock(g_tune_mu);
         const TuneKey key = tune_key(filter, src->dtype, src->channels, src->width, src->height, dst->width,
-                                     dst->height, dst->planes);
+                                     dst->height, dst->planes, is_general(filter, *src, *dst, XR_MAP_HALF_PIXEL));
         if (candidates || best_k != 0)
             g_tuned[key] = cand[best_k];
         else
@@ -1495,7 +1512,7 @@ int xr_get_tile(int32_t filter, int32_t dtype, int32_t channels, int32_t in_w, i
     if (in_w < 1 || in_h < 1 || out_w < 1 || out_h < 1)
         return fail(XR_ERR_SHAPE, "sizes must be positive");
     std::lock_guard<std::mutex> lock(g_tune_mu);
-    auto it = g_tuned.find(tune_key(filter, dtype, channels, in_w, in_h, out_w, out_h, 1));
+    auto it = g_tuned.find(tune_key(filter, dtype, channels, in_w, in_h, out_w, out_h, 1, false));
     *out = it != g_tuned.end() ? it->second
                                : default_tile(filter, dtype, channels, in_w, in_h, out_w, out_h, out_h, 1,
                                               filter == XR_BILINEAR || filter == XR_BICUBIC);
@@ -1515,10 +1532,13 @@ int xr_set_tile(int32_t filter, int32_t dtype, int32_t channels, int32_t in_w, i
         return fail(XR_ERR_CHANNELS, "channels = %d", channels);
     if (in_w < 1 || in_h < 1 || out_w < 1 || out_h < 1)
         return fail(XR_ERR_SHAPE, "sizes must be positive");
-    const TuneKey key = tune_key(filter, dtype, channels, in_w, in_h, out_w, out_h, 1);
+    // (for either map and any alignment)
+    const TuneKey keys[] = {tune_key(filter, dtype, channels, in_w, in_h, out_w, out_h, 1, false),
+                            tune_key(filter, dtype, channels, in_w, in_h, out_w, out_h, 1, true)};
     std::lock_guard<std::mutex> lock(g_tune_mu);
     if (tile->kernel == XR_KERNEL_AUTO) {
-        g_tuned.erase(key);
+        for (const TuneKey &key : keys)
+            g_tuned.erase(key);
         return XR_OK;
     }
     int rc = check_tile(*tile, dtype, channels);
@@ -1526,7 +1546,8 @@ int xr_set_tile(int32_t filter, int32_t dtype, int32_t channels, int32_t in_w, i
         rc = check_lds(*tile, filter, dtype, channels, in_w, out_w);
     if (rc)
         return rc;
-    g_tuned[key] = *tile;
+    for (const TuneKey &key : keys)
+        g_tuned[key] = *tile;
     return XR_OK;
 }
 

@@ -11,6 +11,7 @@ if not torch.cuda.is_available():
     pytest.skip("no GPU", allow_module_level=True)
 
 import paper_1001_1718_amd as xr  # noqa: E402
+from route_util import SRC, shape  # noqa: E402
 
 DEV = "cuda:0"
 CODES = {torch.uint8: xr.XR_U8, torch.float16: xr.XR_F16, torch.float32: xr.XR_F32}
@@ -25,15 +26,15 @@ def test_autotune_keeps_results(mode, dtype, channels, in_hw, out_hw):
     gen.manual_seed(1)
     x = (torch.rand((*in_hw, channels), generator=gen, device=DEV) * 255).to(dtype)
     key = (mode, CODES[dtype], channels, in_hw[1], in_hw[0], out_hw[1], out_hw[0])
-    untuned = xr.get_tile(*key)
+    untuned = shape(mode, CODES[dtype], in_hw, out_hw, channels)
     before = xr.resize(x, out_hw, mode)
     out = torch.empty_like(before)
     try:
         best, ms = xr.autotune(x, out, mode, reps=2, groups=3)
         assert ms > 0 and torch.equal(out, before)
-        now = xr.get_tile(*key).as_tuple()
+        now = shape(mode, CODES[dtype], in_hw, out_hw, channels)  # (77 columns of bytes: not aligned)
         if mode.endswith("_aa"):  # (an untuned antialiased call is a strip shape by name)
-            assert now in (untuned.as_tuple(), best.as_tuple())
+            assert now in (untuned, best.as_tuple())
         else:
             assert now == best.as_tuple()
         assert torch.equal(xr.resize(x, out_hw, mode), before)
@@ -65,3 +66,19 @@ def test_batch_shapes_are_kept_per_size_of_batch():
     small[0][1].zero_()
     again.run()
     assert torch.equal(small[0][1], ref)
+
+
+def test_shapes_of_the_exact_kernels_stay_with_them():
+    """A shape tuned at x2 is neither the printed map's nor an unaligned image's."""
+    x = torch.zeros((300, 400), dtype=torch.uint8, device=DEV)
+    out = torch.empty((600, 800), dtype=torch.uint8, device=DEV)
+    call = ("bilinear", xr.XR_U8, (300, 400), (600, 800))
+    others = (dict(mapping="paper"), dict(src_data=SRC + 1))
+    untuned = [shape(*call, **k) for k in others]
+    best = xr.tile(xr.XR_KERNEL_STRIP, 128, 2, 8, 16)
+    xr.autotune(x, out, "bilinear", candidates=[best], reps=1, groups=1)
+    try:
+        assert shape(*call) == best.as_tuple()
+        assert [shape(*call, **k) for k in others] == untuned
+    finally:
+        xr.set_tile("bilinear", xr.XR_U8, 1, 400, 300, 800, 600, xr.tile(xr.XR_KERNEL_AUTO))

@@ -5,7 +5,7 @@ shape is not used across the size at which the default changes kernels."""
 import pytest
 
 import paper_1001_1718_amd as xr
-from route_util import route
+from route_util import SRC, route, shape
 
 U8, F16, F32 = xr.XR_U8, xr.XR_F16, xr.XR_F32
 
@@ -57,3 +57,17 @@ def test_stored_shapes_stop_at_the_walks_least_output():
             assert xr.get_tile(*other).as_tuple() == before[other]
         finally:
             xr.set_tile(*one, xr.tile(xr.XR_KERNEL_AUTO))
+
+
+def test_a_set_shape_holds_for_either_map():
+    key = ("bilinear", U8, 1, 1000, 1000, 2000, 2000)
+    call = ("bilinear", U8, (1000, 1000), (2000, 2000), 1)
+    kinds = (dict(), dict(mapping="paper"), dict(src_data=SRC + 1))
+    before = [shape(*call, **k) for k in kinds]
+    t = xr.tile(xr.XR_KERNEL_STRIP, 128, 2, 16, 8)
+    xr.set_tile(*key, t)
+    try:
+        assert [shape(*call, **k) for k in kinds] == [t.as_tuple()] * 3
+    finally:
+        xr.set_tile(*key, xr.tile(xr.XR_KERNEL_AUTO))
+    assert [shape(*call, **k) for k in kinds] == before
