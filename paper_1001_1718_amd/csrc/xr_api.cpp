@@ -348,7 +348,8 @@ xr_tile default_tile(int32_t filter, int32_t dtype, int32_t channels, int32_t in
         // (two float16 RGBA columns of a strongly shrinking row need so much LDS
         // that few wavefronts fit: bicubic x0.27 of 2860 x 2600 20.0 us, 15.9 with
         // one, bilinear 12.6 and 10.2; x0.45 20.3 and 18.5, 17.3 and 15.7)
-        if (c4 && dtype == XR_F16 && in_w / 2 >= out_w)
+        const bool narrow = c4 && dtype == XR_F16 && 5 * static_cast<int64_t>(in_w) >= 11 * static_cast<int64_t>(out_w);
+        if (narrow)
             t.ppt_x = 1;
         // a strip of h rows re-filters K - 1 source rows of its neighbour's,
         // but needs as many wavefronts for each row it walks: about one per
@@ -365,10 +366,11 @@ xr_tile default_tile(int32_t filter, int32_t dtype, int32_t channels, int32_t in
         }
         const double walked = std::max(1.0, static_cast<double>(in_h) / out_h);  // source rows per output row
         // (float16 RGBA of one and two taps, whose strips share one row or none, in 8
-        // rows at most: 56 growing resizes 1.00x to 1.31x the speed of 16. The other
+        // rows at most: 56 growing resizes 1.00x to 1.31x the speed of 16; strongly
+        // shrinking in 4: bilinear x0.45 of 6000 x 4000 46.8 us at 8, 43.7. The other
         // types have no such line: gray float16 and RGBA uint8 bilinear at 8 rows 0.76x
         // to 1.34x, by the output's pitch; bicubic 0.76x to 0.94x at 4)
-        const int top = c4 && dtype == XR_F16 && filter != XR_BICUBIC ? 8 : 16;
+        const int top = narrow ? 4 : c4 && dtype == XR_F16 && filter != XR_BICUBIC ? 8 : 16;
         for (t.ppt_y = top; t.ppt_y > 1; t.ppt_y /= 2)
             if (static_cast<double>(cols * ((rows + t.ppt_y - 1) / t.ppt_y) * planes) >= kWalkWaves * walked * t.ppt_y)
                 break;

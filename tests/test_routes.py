@@ -144,7 +144,8 @@ def test_lds_tiles_are_taken_as_documented():
     ("bicubic", U8, 1, (3507, 2479), (4559, 3223), 4, 16), ("bilinear", U8, 4, (800, 800), (4700, 4700), 2, 16),
     ("nearest", F16, 4, (2600, 2860), (3380, 3716), 2, 8), ("bilinear", F16, 4, (2600, 2860), (3380, 3716), 2, 8),
     ("bicubic", F16, 4, (2600, 2860), (3380, 3716), 2, 16), ("bilinear", F32, 4, (2600, 2860), (3380, 3716), 1, 16),
-    ("bicubic", F16, 4, (2600, 2860), (780, 856), 1, 2), ("bicubic", F16, 4, (2600, 2860), (1300, 1431), 2, 4)])
+    ("bicubic", F16, 4, (2600, 2860), (780, 856), 1, 2), ("bilinear", F16, 4, (4000, 6000), (1818, 2727), 1, 4),
+    ("bicubic", F16, 4, (2600, 2860), (1300, 1431), 2, 4)])
 def test_default_strips_of_the_walk(mode, dtype, channels, in_hw, out_hw, ppt_x, rows):
     t = xr.get_tile(mode, dtype, channels, in_hw[1], in_hw[0], out_hw[1], out_hw[0])
     assert t.as_tuple() == (xr.XR_KERNEL_STRIP, 64, 4, ppt_x, rows, 0)
