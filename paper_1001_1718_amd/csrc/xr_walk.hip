@@ -468,7 +468,7 @@ struct Interleave {
 // 700^2 75 and 57, 128 up to 1200^2 240 and 201, 128 up to 2048^2 493 and 424, 256
 // up to 2048^2 984 to 995 and 955; float16 64 up to 1000^2 135 and 124, 128 up to
 // 2048^2 913 and 790; float32 64 up to 1500^2 502 and 496, 256 up to 2048^2 2853
-// and 2640. (The 256 uint8 images take 940 to 990 us by box and process, for a
+// and 2640. (The 256 uint8 images take 940 to 990 us by card and process, for a
 // cause not found: kind by kind 980 to 1010.)
 // A batch of one kind has its own kernel, of fewer registers.
 struct BatchMix {
